@@ -111,24 +111,22 @@ typedef enum sqz_map_impl { SQZ_MAP_SCALAR = 0, SQZ_MAP_MFMA = 1 } sqz_map_impl;
  *                 LAUNCHES.  The resident run's fixed cost (loading and storing
  *                 every subtree once) pays from about 10 steps, measured on an
  *                 MI355X; sqz_run_form_auto reports the choice.
- *   SQZ_RUN_LAUNCHES: one kernel launch per group of up to
- *                 sqz_info.run_steps_per_launch steps, each reading its input
- *                 buffer whole and writing its output buffer whole (temporal
- *                 blocking within a launch, Section "Moving from Thread-level
- *                 to Block-level" for the tiles).
+ *   SQZ_RUN_LAUNCHES: one kernel launch per group of steps (at least
+ *                 sqz_info.run_steps_per_launch of them where the run has as
+ *                 many), each reading the state whole and writing it whole
+ *                 (temporal blocking within a launch, Section "Moving from
+ *                 Thread-level to Block-level" for the tiles).
  *   SQZ_RUN_RESIDENT: all steps in one launch, one workgroup per
- *                 level-M subtree and every subtree held in on-chip memory for
- *                 the whole run; every run_steps_per_launch steps the subtrees
- *                 exchange only the cells their neighbours read (through the
- *                 two caller buffers) at a grid-wide barrier.  Offered for
- *                 patterns with a bit-sliced tiled kernel whose subtrees all fit
- *                 on the chip at once (the level-16 triangle: 729 subtrees of
- *                 level 10).  Runs on one fractal must not overlap on the device
- *                 (each run uses the fractal's barrier counter) and need the
- *                 whole GPU: a run that overlaps another resident run, or
- *                 cannot get all its workgroups on the chip, gives up its
- *                 barrier waits after seconds; the next run call on the
- *                 fractal then returns SQZ_ERR_HIP. */
+ *                 subtree and every subtree held on the chip for the whole
+ *                 run; every few steps the subtrees exchange only the cells
+ *                 their neighbours read.  Offered for patterns with a
+ *                 bit-sliced tiled kernel whose subtrees all fit on the chip at
+ *                 once (the level-16 triangle: 243 subtrees of level 11).  Runs
+ *                 on one fractal must not overlap on the device (each run uses
+ *                 the fractal's exchange words) and need the whole GPU: a run
+ *                 that overlaps another resident run, or cannot get all its
+ *                 workgroups on the chip, gives up its waits after seconds; the
+ *                 next run call on the fractal then returns SQZ_ERR_HIP. */
 typedef enum sqz_run_form { SQZ_RUN_AUTO = 0, SQZ_RUN_LAUNCHES = 1, SQZ_RUN_RESIDENT = 2 } sqz_run_form;
 
 /* Storage type of the diffusion field. */
@@ -174,10 +172,10 @@ typedef struct sqz_info {
     uint64_t compact_h;  /* height, k^floor(r/2) (Section "Compacting NBB Fractals") */
     int32_t has_tile;    /* 1 if SQZ_IMPL_TILE is available for this pattern */
     int32_t xtile_level; /* level of the expanded tiles of SQZ_IMPL_XTILE (0 if none) */
-    int32_t run_steps_per_launch; /* Life steps per launch in sqz_compact_run with aligned buffers:
-                                     up to 10 with multi-step tiled kernels (temporal blocking;
-                                     16-byte alignment) or bit-row tiles (8-byte), 3 with
-                                     multi-step expanded tiles, else 1 */
+    int32_t run_steps_per_launch; /* Life steps a launch of sqz_compact_run can take at least, with
+                                     aligned buffers: up to 10 with multi-step tiled kernels
+                                     (temporal blocking; 16-byte alignment) or bit-row tiles
+                                     (8-byte), 3 with multi-step expanded tiles, else 1 */
     int32_t bits_level;  /* level M of the bit-row tiles of SQZ_IMPL_BITS (0 if none) */
     int32_t resident_run; /* 1 if sqz_compact_run_form offers SQZ_RUN_RESIDENT for this fractal */
 } sqz_info;

@@ -122,11 +122,15 @@ sqz_status sqz_fractal_create(int32_t s, int32_t k, const int32_t *offsets_xy, i
     f->h.tile = nullptr;
     f->h.xtile = nullptr;
     f->h.bitbox = nullptr;
+    f->h.slice = nullptr;
     f->h.mfma = mfma_prepare(f->h);  // null when the pattern does not fit int8 digits
     if (f->h.tile_kind) st = tile_prepare(f->h);
+    if (st == SQZ_OK) st = slice_prepare(f->h);
+    if (st == SQZ_OK) slice_prepare_resident(f->h);
     if (st == SQZ_OK) st = xtile_prepare(f->h);
     if (st == SQZ_OK) st = bitbox_prepare(f->h);
     if (st != SQZ_OK) {
+        slice_release(f->h);
         tile_release(f->h);
         xtile_release(f->h);
         bitbox_release(f->h);
@@ -142,6 +146,7 @@ sqz_status sqz_fractal_create(int32_t s, int32_t k, const int32_t *offsets_xy, i
 void sqz_fractal_destroy(sqz_fractal *f)
 {
     if (!f) return;
+    slice_release(f->h);
     tile_release(f->h);
     xtile_release(f->h);
     bitbox_release(f->h);
@@ -315,6 +320,12 @@ static bool auto_resident(const FractalHost &h, int32_t steps)
     return plan_launches(steps, K).size() > (size_t)((steps + K - 1) / K);
 }
 
+static sqz_status run_resident(const FractalHost &h, uint8_t *a, uint8_t *b, int32_t steps, hipStream_t st)
+{
+    if (slice_resident(h)) return slice_run_resident(h, a, b, steps, st);
+    return launch_life_tile_resident(h, a, b, steps, st);
+}
+
 sqz_status sqz_run_form_auto(const sqz_fractal *f, int32_t steps, sqz_run_form *form)
 {
     sqz_status st = check_handle(f);
@@ -340,10 +351,12 @@ sqz_status sqz_compact_run_form(const sqz_fractal *f, sqz_run_form form, uint8_t
         if (!tile_resident(f->h))
             return set_error(SQZ_ERR_UNSUPPORTED, "no resident run: the tiles of this fractal do not fit the chip at once");
         if (!aligned) return set_error(SQZ_ERR_INVALID, "the resident run needs 16-byte aligned buffers");
-        return launch_life_tile_resident(f->h, d_a, d_b, steps, (hipStream_t)stream);
+        return run_resident(f->h, d_a, d_b, steps, (hipStream_t)stream);
     }
     if (form == SQZ_RUN_AUTO && aligned && auto_resident(f->h, steps))
-        return launch_life_tile_resident(f->h, d_a, d_b, steps, (hipStream_t)stream);
+        return run_resident(f->h, d_a, d_b, steps, (hipStream_t)stream);
+    if (aligned && slice_available(f->h) && steps >= 2)
+        return slice_run_launches(f->h, d_a, d_b, steps, (hipStream_t)stream);
     const bool aligned8 = !(((uintptr_t)d_a | (uintptr_t)d_b) & 7);
     const bool tiled = f->h.tile_kind && aligned, bits = !tiled && f->h.bitbox && aligned8;
     const int K = tiled ? tile_steps_per_launch(f->h)

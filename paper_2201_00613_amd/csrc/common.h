@@ -197,6 +197,15 @@ int bitbox_steps_per_launch(const FractalHost &F);  // 0: none
 int32_t bitbox_level_of(const FractalHost &F);
 sqz_status launch_life_bitbox(const FractalHost &F, const uint8_t *in, uint8_t *out, int steps, hipStream_t st);
 
+// Tiles bit-sliced across subtrees (slice.hip)
+sqz_status slice_prepare(FractalHost &F);  // after tile_prepare
+void slice_prepare_resident(FractalHost &F);
+void slice_release(FractalHost &F);
+bool slice_available(const FractalHost &F);
+bool slice_resident(const FractalHost &F);
+sqz_status slice_run_resident(const FractalHost &F, uint8_t *a, uint8_t *b, int steps, hipStream_t st);
+sqz_status slice_run_launches(const FractalHost &F, uint8_t *a, uint8_t *b, int steps, hipStream_t st);
+
 // Batched Life (batch.hip)
 struct BatchHost;
 sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost **out);

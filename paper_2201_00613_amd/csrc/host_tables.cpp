@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <set>
 #include <utility>
 
 namespace sqz {
@@ -388,6 +389,178 @@ sqz_status tile_tables(const FractalHost &F, const TileSpec &S, TileTables &T)
     for (uint64_t j = 0; j < tile; ++j)
         if (used[j]) T.bound.push_back((uint32_t)j);
     return SQZ_OK;
+}
+
+// ---------------------------------------------------------------------------
+// Tiles bit-sliced across subtrees
+// ---------------------------------------------------------------------------
+typedef std::pair<int64_t, int64_t> Pos;
+
+// Positions outside a level-`level` subtree's box that touch a cell of it and
+// are cells themselves if the adjacent subtree they lie in exists.
+static std::vector<Pos> subtree_ring(const FractalHost &F, int level)
+{
+    const int64_t n = (int64_t)upow(F.s, level);
+    std::vector<Pos> out;
+    auto test = [&](int64_t x, int64_t y) {
+        if (host_nu(F, level, x - floor_div(x, n) * n, y - floor_div(y, n) * n) < 0) return;
+        for (int d = 0; d < 9; ++d)
+            if (host_nu(F, level, x + d % 3 - 1, y + d / 3 - 1) >= 0) {
+                out.emplace_back(x, y);
+                return;
+            }
+    };
+    for (int64_t x = -1; x <= n; ++x) {
+        test(x, -1);
+        test(x, n);
+    }
+    for (int64_t y = 0; y < n; ++y) {
+        test(-1, y);
+        test(n, y);
+    }
+    return out;
+}
+
+sqz_status slice_tables(const FractalHost &F, const SliceSpec &S, SliceTables &T)
+{
+    const int M = S.M, L = M - S.B;
+    const int64_t n = (int64_t)upow(F.s, M), sub = (int64_t)upow(F.s, L), rs = (int64_t)upow(F.s, S.RL);
+    const uint32_t nsub = (uint32_t)upow(F.k, S.B);
+    T.words = (uint32_t)upow(F.k, L);
+    T.nblk = (uint32_t)upow(F.k, L - S.J);
+    auto find = [](const std::vector<Pos> &v, const Pos &p) {
+        for (size_t i = 0; i < v.size(); ++i)
+            if (v[i] == p) return (int)i;
+        return -1;
+    };
+    const std::vector<Pos> hs = subtree_ring(F, L);
+    if (hs.size() > (size_t)S.nh) return set_error(SQZ_ERR_UNSUPPORTED, "subtile halo of %zu cells", hs.size());
+
+    // Ring subtrees: those holding the cells next to the tile; they cover K
+    // steps, K the last distance before a breadth-first walk over member cells
+    // outside the tile enters another subtree.
+    std::vector<Pos> key;
+    if (M < F.r) {
+        std::vector<Pos> cur = subtree_ring(F, M);
+        for (const Pos &p : cur) {
+            const Pos q(floor_div(p.first, rs), floor_div(p.second, rs));
+            if (find(key, q) < 0) key.push_back(q);
+        }
+        if (key.size() > (size_t)S.max_ring) return set_error(SQZ_ERR_UNSUPPORTED, "%zu ring subtrees", key.size());
+        std::set<Pos> seen(cur.begin(), cur.end());
+        bool other = false;
+        for (T.K = 1; T.K < (uint32_t)rs && !other; ++T.K) {  // cur: the cells at distance K
+            std::vector<Pos> next;
+            for (const Pos &p : cur)
+                for (int d = 0; d < 9; ++d) {
+                    const Pos q(p.first + d % 3 - 1, p.second + d / 3 - 1);
+                    if (q.first >= 0 && q.second >= 0 && q.first < n && q.second < n) continue;
+                    if (host_nu(F, M, q.first - floor_div(q.first, n) * n, q.second - floor_div(q.second, n) * n) < 0) continue;
+                    if (!seen.insert(q).second) continue;
+                    other |= find(key, Pos(floor_div(q.first, rs), floor_div(q.second, rs))) < 0;
+                    next.push_back(q);
+                }
+            if (other) break;
+            cur.swap(next);
+        }
+        T.rwords = (uint32_t)upow(F.k, S.RL);
+    }
+    T.nring = (uint32_t)key.size();
+    const uint32_t rblk = T.rwords / (uint32_t)S.nc;
+    std::vector<Pos> hr;
+    if (T.nring) hr = subtree_ring(F, S.RL);
+    if (hr.size() > (size_t)S.nh) return set_error(SQZ_ERR_UNSUPPORTED, "ring halo of %zu cells", hr.size());
+    for (const Pos &q : key) {
+        const int64_t dx = floor_div(q.first * rs, n), dy = floor_div(q.second * rs, n);
+        const int64_t c = host_nu(F, M - S.RL, q.first - dx * (n / rs), q.second - dy * (n / rs));
+        if (dx < -1 || dx > 1 || dy < -1 || dy > 1 || c < 0) return set_error(SQZ_ERR_UNSUPPORTED, "ring subtree out of reach");
+        const uint32_t off = (uint32_t)c * T.rwords;
+        size_t e = 0;
+        while (e < T.corner.size() && T.corner[e] != off) ++e;
+        if (e == T.corner.size()) T.corner.push_back(off);
+        T.ring.insert(T.ring.end(), {(int32_t)dx, (int32_t)dy, (int32_t)off, (int32_t)e});
+    }
+
+    // LDS source of the cell at (x, y) of the tile's plane: offset | bit << 16 | ring subtree << 24
+    const uint32_t none = S.zero | 0xFFu << 24;
+    bool ok = true;
+    auto source = [&](int64_t x, int64_t y) -> uint32_t {
+        uint32_t w, bit, s = 0xFF, b0 = 0;
+        if (x >= 0 && y >= 0 && x < n && y < n) {
+            const int64_t c = host_nu(F, M, x, y);
+            if (c < 0) return none;
+            w = (uint32_t)(c % T.words);
+            bit = (uint32_t)(c / T.words);
+        } else {
+            const Pos q(floor_div(x, rs), floor_div(y, rs));
+            const int i = find(key, q);
+            if (i < 0) return none;
+            const int64_t c = host_nu(F, S.RL, x - q.first * rs, y - q.second * rs);
+            if (c < 0) return none;
+            w = (uint32_t)c;
+            bit = s = (uint32_t)i;
+            b0 = T.nblk;
+        }
+        const int e = S.cell_exp[w % (uint32_t)S.nc];
+        if (e < 0) {
+            ok = false;
+            return none;
+        }
+        return (S.ex0 + (b0 + w / (uint32_t)S.nc) * S.pitch + 4u * (uint32_t)e) | bit << 16 | s << 24;
+    };
+    T.perm.assign((size_t)(S.passes + 1) * 64, none);
+    for (size_t h = 0; h < hs.size(); ++h)
+        for (uint32_t j = 0; j < nsub; ++j) {
+            int64_t x, y;
+            host_lambda(F, S.B, j, x, y);
+            T.perm[h * 32 + j] = source(x * sub + hs[h].first, y * sub + hs[h].second);
+        }
+    for (size_t h = 0; h < hr.size(); ++h)
+        for (uint32_t s = 0; s < T.nring; ++s)
+            T.perm[(size_t)S.passes * 64 + h * (size_t)S.max_ring + s] =
+                source(key[s].first * rs + hr[h].first, key[s].second * rs + hr[h].second);
+
+    // Lanes: the ring's blocks, then the blocks the halo ballots read or whose
+    // own halo leaves the subtile (all in the first wave), then the rest.
+    std::vector<uint8_t> special(T.nblk, 0);
+    for (uint32_t e : T.perm)
+        if ((e & 0xFFFFu) >= S.ex0) {
+            const uint32_t b = ((e & 0xFFFFu) - S.ex0) / S.pitch;
+            if (b < T.nblk) special[b] = 1;
+        }
+    auto block_halo = [&](int level, uint32_t b, uint32_t first, const std::vector<Pos> &ring, uint32_t ring_off,
+                          uint32_t *out) {
+        const int64_t side = (int64_t)upow(F.s, level - S.J);
+        int64_t bx, by;
+        bool leaves = false;
+        host_lambda(F, level - S.J, b, bx, by);
+        for (int h = 0; h < S.nh; ++h) {
+            const int64_t x = bx + S.h_dx[h], y = by + S.h_dy[h];
+            out[h] = S.zero;
+            if (x >= 0 && y >= 0 && x < side && y < side) {
+                const int64_t nb = host_nu(F, level - S.J, x, y);
+                if (nb >= 0) out[h] = S.ex0 + (first + (uint32_t)nb) * S.pitch + 4u * (uint32_t)S.h_exp[h];
+            } else {
+                const int i = find(ring, Pos(x * S.box + S.cell_x[S.h_idx[h]], y * S.box + S.cell_y[S.h_idx[h]]));
+                if (i >= 0) out[h] = ring_off + 4u * (uint32_t)i;
+                leaves |= i >= 0;
+            }
+        }
+        return leaves;
+    };
+    std::vector<uint32_t> halo((size_t)(T.nblk + rblk) * (size_t)S.nh);
+    for (uint32_t b = 0; b < T.nblk; ++b)
+        if (block_halo(L, b, 0, hs, S.halo, &halo[(size_t)b * S.nh])) special[b] = 1;
+    for (uint32_t b = 0; b < rblk; ++b) block_halo(S.RL, b, T.nblk, hr, S.rhalo, &halo[(size_t)(T.nblk + b) * S.nh]);
+    for (uint32_t b = 0; b < rblk; ++b) T.lane_block.push_back(T.nblk + b);
+    for (int pass = 1; pass >= 0; --pass) {
+        for (uint32_t b = 0; b < T.nblk; ++b)
+            if (special[b] == pass) T.lane_block.push_back(b);
+        if (pass && T.lane_block.size() > 64) return set_error(SQZ_ERR_UNSUPPORTED, "%zu lanes in the first wave", T.lane_block.size());
+    }
+    for (uint32_t b : T.lane_block)
+        T.lane_halo.insert(T.lane_halo.end(), halo.begin() + (size_t)b * S.nh, halo.begin() + (size_t)(b + 1) * S.nh);
+    return ok ? SQZ_OK : set_error(SQZ_ERR_UNSUPPORTED, "a halo cell is not published");
 }
 
 // ---------------------------------------------------------------------------

@@ -84,6 +84,7 @@ struct TileConfig;    // life_tile.hip
 struct XTileConfig;   // xtile.hip
 struct MfmaParams;    // mfma_maps.hip
 struct BitboxConfig;  // bitbox.hip
+struct SliceConfig;   // slice.hip
 
 struct FractalHost {
     int32_t s, k, r;
@@ -100,6 +101,7 @@ struct FractalHost {
     XTileConfig *xtile;           // expanded-tile kernels (any pattern), null if none
     MfmaParams *mfma;             // matrix-core map variants, null if unsupported (k > 127)
     BitboxConfig *bitbox;         // bit-row expanded tiles (dense s = 3 patterns), null if none
+    SliceConfig *slice;           // tiles bit-sliced across subtrees (several steps per launch), null if none
 };
 
 // ---------------------------------------------------------------------------
@@ -152,6 +154,33 @@ struct TileTables {
 
 // SQZ_ERR_UNSUPPORTED when ring 1 exceeds spec.max_tile_halo.
 sqz_status tile_tables(const FractalHost &F, const TileSpec &S, TileTables &T);
+
+// ---------------------------------------------------------------------------
+// Tables of the tiles bit-sliced across subtrees (slice_device.h has the
+// layout): tile level M, subtile level M - B, block level J, ring level RL.
+// ---------------------------------------------------------------------------
+struct SliceSpec {
+    int M, B, J, RL;
+    int nc, box;                  // words and side of a block
+    int nh;                       // halo slots of a block: cell h_idx of the block in direction (h_dx, h_dy)
+    int h_dx[16], h_dy[16], h_idx[16], h_exp[16];
+    int cell_exp[32];             // published slot of a block's cell, -1 if it is not published
+    int cell_x[32], cell_y[32];   // position of a block's cell in the block
+    int max_ring;                 // most ring subtrees
+    uint32_t zero, ex0, pitch, halo, rhalo;  // LDS byte offsets in a buffer
+    int passes;                   // ballots of the subtile halo
+};
+
+struct SliceTables {
+    uint32_t words = 0, nblk = 0, rwords = 0, nring = 0;
+    uint32_t K = 0;               // steps the ring subtrees cover (0: one tile, no ring)
+    std::vector<int32_t> ring;    // per ring subtree: tile dx, tile dy, first cell in that tile, corner
+    std::vector<uint32_t> corner; // first cell of each distinct corner subtree
+    std::vector<uint32_t> lane_block, lane_halo, perm;
+};
+
+// SQZ_ERR_UNSUPPORTED when the pattern does not fit the layout.
+sqz_status slice_tables(const FractalHost &F, const SliceSpec &S, SliceTables &T);
 
 // ---------------------------------------------------------------------------
 // Expanded-tile tables: the level-M subtree scattered into a P-pitch box with

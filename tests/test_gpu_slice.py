@@ -1,0 +1,68 @@
+"""GPU parity of the Life runs on tiles bit-sliced across subtrees (Section
+"Moving from Thread-level to Block-level"): both run forms around the step
+counts at which ring subtrees are exchanged or a launch ends (31 steps for the
+triangles, 27 for the Vicsek cross), launches whose last one updates in place,
+and every tile configuration.  Small fractals against the CPU oracle, larger
+ones against one-step launches; results are whole numbers, compared exactly."""
+import pytest
+
+from gpu_common import gpu_fractal, mismatch, oracle_fractal, to_np, torch_or_skip
+
+pytestmark = pytest.mark.gpu
+
+CASES = [("triangle", 5), ("triangle", 6), ("triangle", 8), ("triangle", 9), ("triangle", 11), ("triangle_paper", 9),
+         ("vicsek", 3), ("vicsek", 6), ("vicsek", 7)]
+
+
+def step_counts(name):
+    k = 27 if name == "vicsek" else 31
+    return [2, k - 1, k, k + 1, 2 * k, 2 * k + 1]
+
+
+@pytest.mark.parametrize("form", ["launches", "resident"])
+@pytest.mark.parametrize("name,r", CASES)
+def test_runs_against_oracle(name, r, form):
+    torch = torch_or_skip()
+    F, O = gpu_fractal(name, r), oracle_fractal(name, r)
+    want, at = O.fill_compact(31, 0.5), 0
+    start = F.fill_bernoulli(31, 0.5)
+    for steps in step_counts(name):
+        want, at = O.life_steps(want, steps - at), steps
+        a, b = start.clone(), torch.full_like(start, 7)  # the other buffer's contents must not matter
+        mismatch(to_np(F.compact_run(a, b, steps, form=form)), want, f"{name} r={r} {form} {steps} steps")
+
+
+@pytest.mark.parametrize("name,r", [("triangle", 13), ("triangle", 15), ("triangle", 16), ("triangle", 17),
+                                    ("triangle_paper", 16), ("triangle_paper", 17), ("vicsek", 10), ("vicsek", 11)])
+def test_runs_equal_single_steps(name, r):
+    torch = torch_or_skip()
+    F = gpu_fractal(name, r)
+    start = F.fill_bernoulli(5, 0.5)
+    x, y, at = start.clone(), torch.empty_like(start), 0
+    for steps in step_counts(name)[1:5]:
+        for _ in range(steps - at):
+            F.compact_step(x, y)
+            x, y = y, x
+        at = steps
+        for form in ["launches"] + (["resident"] if F.resident_run else []):
+            a, b = start.clone(), torch.full_like(start, 7)
+            assert torch.equal(F.compact_run(a, b, steps, form=form), x), (form, steps)
+
+
+def test_runs_one_cell_into_a_buffer():
+    """Subtiles start at odd addresses; the cells before and after the state stay as they were."""
+    torch = torch_or_skip()
+    F = gpu_fractal("triangle", 9)
+    start = F.fill_bernoulli(3, 0.5)
+    want = F.compact_run(start.clone(), torch.empty_like(start), 32, form="launches")
+    for form in ("launches", "resident"):
+        for steps in (32, 33):
+            a = torch.full((F.cells + 64,), 9, dtype=torch.uint8, device="cuda")
+            b = a.clone()
+            x, y = a[32:32 + F.cells], b[32:32 + F.cells]
+            x.copy_(start)
+            res = F.compact_run(x, y, steps, form=form)
+            if steps == 32:
+                assert torch.equal(res, want), form
+            for t in (a, b):
+                assert bool((t[:32] == 9).all()) and bool((t[32 + F.cells:] == 9).all()), (form, steps)
