@@ -123,14 +123,17 @@ sqz_status sqz_fractal_create(int32_t s, int32_t k, const int32_t *offsets_xy, i
     f->h.xtile = nullptr;
     f->h.bitbox = nullptr;
     f->h.slice = nullptr;
+    f->h.lane = nullptr;
     f->h.mfma = mfma_prepare(f->h);  // null when the pattern does not fit int8 digits
     if (f->h.tile_kind) st = tile_prepare(f->h);
     if (st == SQZ_OK) st = slice_prepare(f->h);
     if (st == SQZ_OK) slice_prepare_resident(f->h);
+    if (st == SQZ_OK) st = lane_prepare(f->h);
     if (st == SQZ_OK) st = xtile_prepare(f->h);
     if (st == SQZ_OK) st = bitbox_prepare(f->h);
     if (st != SQZ_OK) {
         slice_release(f->h);
+        lane_release(f->h);
         tile_release(f->h);
         xtile_release(f->h);
         bitbox_release(f->h);
@@ -147,6 +150,7 @@ void sqz_fractal_destroy(sqz_fractal *f)
 {
     if (!f) return;
     slice_release(f->h);
+    lane_release(f->h);
     tile_release(f->h);
     xtile_release(f->h);
     bitbox_release(f->h);
@@ -489,6 +493,8 @@ sqz_status sqz_diffuse_step(const sqz_fractal *f, const sqz_diffusion *d, uint64
     if (st != SQZ_OK) return st;
     if (!d_in || !d_out) return set_error(SQZ_ERR_INVALID, "NULL buffer");
     if (overlap(d_in, d_out, f->h.N * dtype_size(d->dtype))) return set_error(SQZ_ERR_INVALID, "d_in and d_out overlap");
+    if (d->impl == SQZ_IMPL_AUTO && d->steps_per_launch == 0 && lane_one_step(f->h))
+        return lane_diffuse_run(f->h, d->dtype, d->coef, d->rounding, d->seed, step, 1, d_in, d_out, (hipStream_t)stream);
     return launch_diffuse(f->h, d->dtype, d->coef, d->rounding, d->seed, step, d_in, d_out, d->impl != SQZ_IMPL_CELL,
                           (hipStream_t)stream);
 }
@@ -512,6 +518,9 @@ sqz_status sqz_diffuse_run(const sqz_fractal *f, const sqz_diffusion *d, uint64_
         }
         return st;
     }
+    // the default takes several steps per launch where the pattern has the kernel
+    if (K == 0 && d->impl == SQZ_IMPL_AUTO && (steps >= 2 ? lane_available(f->h) : lane_one_step(f->h)))
+        return lane_diffuse_run(f->h, d->dtype, d->coef, d->rounding, d->seed, first_step, steps, d_a, d_b, (hipStream_t)stream);
     for (int32_t i = 0; i < steps; ++i) {
         st = launch_diffuse(f->h, d->dtype, d->coef, d->rounding, d->seed, first_step + (uint64_t)i, (i & 1) ? d_b : d_a,
                             (i & 1) ? d_a : d_b, d->impl != SQZ_IMPL_CELL, (hipStream_t)stream);

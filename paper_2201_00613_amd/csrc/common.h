@@ -206,6 +206,15 @@ bool slice_resident(const FractalHost &F);
 sqz_status slice_run_resident(const FractalHost &F, uint8_t *a, uint8_t *b, int steps, hipStream_t st);
 sqz_status slice_run_launches(const FractalHost &F, uint8_t *a, uint8_t *b, int steps, hipStream_t st);
 
+// Diffusion with a block per lane (lane.hip)
+sqz_status lane_prepare(FractalHost &F);
+void lane_release(FractalHost &F);
+bool lane_available(const FractalHost &F);
+bool lane_one_step(const FractalHost &F);  // a single step is faster with these kernels too
+// steps >= 1 from a; the result in a (even) or b (odd); with one step a is not written
+sqz_status lane_diffuse_run(const FractalHost &F, int dtype, float coef, int rounding, uint64_t seed, uint64_t first,
+                            int steps, const void *a, void *b, hipStream_t st);
+
 // Batched Life (batch.hip)
 struct BatchHost;
 sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost **out);

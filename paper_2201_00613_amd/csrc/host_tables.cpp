@@ -6,6 +6,7 @@
 #include <stdio.h>
 #include <string.h>
 
+#include <map>
 #include <set>
 #include <utility>
 
@@ -561,6 +562,70 @@ sqz_status slice_tables(const FractalHost &F, const SliceSpec &S, SliceTables &T
     for (uint32_t b : T.lane_block)
         T.lane_halo.insert(T.lane_halo.end(), halo.begin() + (size_t)b * S.nh, halo.begin() + (size_t)(b + 1) * S.nh);
     return ok ? SQZ_OK : set_error(SQZ_ERR_UNSUPPORTED, "a halo cell is not published");
+}
+
+// ---------------------------------------------------------------------------
+// Tiles with one block per lane
+// ---------------------------------------------------------------------------
+void lane_tables(const FractalHost &F, const LaneSpec &S, LaneTables &T)
+{
+    const int M = S.M;
+    const int64_t n = (int64_t)upow(F.s, M), bs = (int64_t)upow(F.s, M - S.J), box = (int64_t)upow(F.s, S.J);
+    T.cells = upow(F.k, M);
+    T.nblk = (uint32_t)upow(F.k, M - S.J);
+    struct Block {
+        Pos at;        // position in blocks of the tile's plane
+        uint32_t src;  // lane_src entry
+    };
+    std::vector<Block> blk;
+    std::set<Pos> have;
+    for (uint32_t b = 0; b < T.nblk; ++b) {
+        int64_t x, y;
+        host_lambda(F, M - S.J, b, x, y);
+        blk.push_back({Pos(x, y), 8u << 28 | b});
+        have.insert(Pos(x, y));
+    }
+    auto add_ring = [&](int64_t x, int64_t y) {
+        const int64_t tx = floor_div(x, bs), ty = floor_div(y, bs);
+        const int64_t b = host_nu(F, M - S.J, x - tx * bs, y - ty * bs);
+        if (b < 0 || !have.insert(Pos(x, y)).second) return;
+        const int d = (int)((ty + 1) * 3 + (tx + 1));
+        blk.push_back({Pos(x, y), (uint32_t)(d < 4 ? d : d - 1) << 28 | (uint32_t)b});
+    };
+    if (M < F.r && S.frame) {
+        for (int64_t y = -S.frame; y < bs + S.frame; ++y)
+            for (int64_t x = -S.frame; x < bs + S.frame; ++x)
+                if (x < 0 || y < 0 || x >= bs || y >= bs) add_ring(x, y);
+    } else if (M < F.r) {
+        std::vector<Pos> cur = subtree_ring(F, M);
+        std::set<Pos> seen(cur.begin(), cur.end());
+        for (int d = 1;; ++d) {  // cur: the cells at distance d
+            for (const Pos &p : cur) add_ring(floor_div(p.first, box), floor_div(p.second, box));
+            if (d == S.steps) break;
+            std::vector<Pos> next;
+            for (const Pos &p : cur)
+                for (int e = 0; e < 9; ++e) {
+                    const Pos q(p.first + e % 3 - 1, p.second + e / 3 - 1);
+                    if (q.first >= 0 && q.second >= 0 && q.first < n && q.second < n) continue;
+                    if (host_nu(F, M, q.first - floor_div(q.first, n) * n, q.second - floor_div(q.second, n) * n) < 0) continue;
+                    if (seen.insert(q).second) next.push_back(q);
+                }
+            cur.swap(next);
+        }
+    }
+    if (M < F.r) T.K = S.steps;
+    std::map<Pos, uint32_t> lane;
+    for (const Block &b : blk) {
+        const uint32_t l = (uint32_t)lane.size();
+        lane[b.at] = l | (b.src >> 28) << 16;
+        if (l >= T.nblk) T.lane_src.push_back(b.src);
+    }
+    T.lanes = (uint32_t)blk.size();
+    for (const Block &b : blk)
+        for (int g = 0; g < S.ng; ++g) {
+            const auto it = lane.find(Pos(b.at.first + S.g_dx[g], b.at.second + S.g_dy[g]));
+            T.lane_nb.push_back(it == lane.end() ? ~0u : it->second);
+        }
 }
 
 // ---------------------------------------------------------------------------

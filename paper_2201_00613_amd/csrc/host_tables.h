@@ -85,6 +85,7 @@ struct XTileConfig;   // xtile.hip
 struct MfmaParams;    // mfma_maps.hip
 struct BitboxConfig;  // bitbox.hip
 struct SliceConfig;   // slice.hip
+struct LaneConfig;    // lane.hip
 
 struct FractalHost {
     int32_t s, k, r;
@@ -102,6 +103,7 @@ struct FractalHost {
     MfmaParams *mfma;             // matrix-core map variants, null if unsupported (k > 127)
     BitboxConfig *bitbox;         // bit-row expanded tiles (dense s = 3 patterns), null if none
     SliceConfig *slice;           // tiles bit-sliced across subtrees (several steps per launch), null if none
+    LaneConfig *lane;             // diffusion with a block per lane, null if none
 };
 
 // ---------------------------------------------------------------------------
@@ -181,6 +183,26 @@ struct SliceTables {
 
 // SQZ_ERR_UNSUPPORTED when the pattern does not fit the layout.
 sqz_status slice_tables(const FractalHost &F, const SliceSpec &S, SliceTables &T);
+
+// ---------------------------------------------------------------------------
+// Tables of the tiles with one level-J block per lane (lane_device.h).
+// ---------------------------------------------------------------------------
+struct LaneSpec {
+    int M, J;
+    int ng, g_dx[8], g_dy[8];  // adjacent blocks a block's halo reads
+    int steps;                 // steps the ring blocks have to cover
+    int frame;                 // ring: the frame of that many blocks around the tile (covers as many cells); 0: by search
+};
+
+struct LaneTables {
+    uint64_t cells = 0;        // of a tile
+    uint32_t nblk = 0, lanes = 0;
+    int K = 0;                 // steps covered (0: one tile, no ring)
+    std::vector<uint32_t> lane_src;  // per ring lane: adjacent tile (0..7) << 28 | block in it
+    std::vector<uint32_t> lane_nb;   // per lane and group: lane of the block | its tile (8: this one) << 16, ~0 if none
+};
+
+void lane_tables(const FractalHost &F, const LaneSpec &S, LaneTables &T);
 
 // ---------------------------------------------------------------------------
 // Expanded-tile tables: the level-M subtree scattered into a P-pitch box with
