@@ -30,6 +30,7 @@
 #include <vector>
 
 #include "bitbox_device.h"
+#include "slice_device.h"
 #include "tile_device.h"
 #include "xtile_device.h"
 
@@ -199,23 +200,22 @@ __device__ __forceinline__ uint32_t group_instance(const GroupArgs &G, uint64_t 
     return a;
 }
 
-template <class Pat, int K>
-__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8)))
-k_batch_tile(GroupArgs G, const uint8_t *__restrict__ in, uint8_t *__restrict__ out)
+// Tiles bit-sliced across subtrees: level-8 triangles (27 lanes and as many for
+// their ring) and level-6 Vicsek crosses, about 2.5 and 6 KB of LDS and 80
+// registers, six waves per SIMD of independent workgroups; up to 31 (27) steps
+// a launch.  512 mixed fractals, 50 steps: 3.86 ms with the 27-cell blocks
+// (five launches of ten, bound by vector issue) -> 1.41 ms, of which the
+// carpets' bit rows take 0.55.
+template <class P>
+__global__ void __launch_bounds__(SliceCfg<P>::LANES)
+k_batch_slice(GroupArgs G, const uint8_t *in, uint8_t *out, int32_t steps)
 {
-    using LDS = TileLds<Pat>;
-    __shared__ uint32_t s_buf[3][LDS::WORDS];
-    __shared__ __align__(16) uint32_t s_ring[kRingTab];
+    __shared__ __align__(16) uint32_t sm[SliceCfg<P>::LDS / 4];
     const uint64_t b = xcd_remap(blockIdx.x, gridDim.x);
     const uint32_t i = group_instance(G, b);
-    const TileArgs &A = reinterpret_cast<const TileArgs *>(G.args)[i];
-    const uint64_t t = b - G.tstart[i], base = G.base[i];
-    if constexpr (K == 1) {
-        tile_body<Pat>(A, in + base, out + base, t, s_buf[0], s_buf[1]);
-    } else {
-        uint32_t *const buf[3] = {s_buf[0], s_buf[1], s_buf[2]};
-        tile_bodyK<Pat, K>(A, in + base, out + base, t, buf, s_ring);
-    }
+    const SliceArgs A = reinterpret_cast<const SliceArgs *>(G.args)[i];
+    const uint64_t base = G.base[i];
+    slice_tile<P, false>(A, in + base, out + base, b - G.tstart[i], SliceRing{in + base, false}, steps, SliceRes{}, sm);
 }
 
 template <class Pat, int K>
@@ -240,7 +240,7 @@ struct TiledInst {
     uint64_t units;       // tiles
     uint64_t unit_cells;  // cells per tile
     uint64_t cost_start;  // first cost unit (cell) of the instance
-    TileArgs t;
+    SliceArgs t;
     BitboxArgs x;
 };
 
@@ -253,33 +253,16 @@ struct TiledArgs {
     uint64_t total_cost;
 };
 
-// LDS of a tile body: the bit-sliced layout (three state buffers, the ring
-// tables 16-byte aligned) or the bit-row layout (two row buffers, nine
-// bases, one flag word), whichever the kind uses; sizes in bytes.
-template <class Pat>
-__host__ __device__ constexpr size_t tiled_ring_offset()
-{
-    return (3 * (size_t)TileLds<Pat>::WORDS + 3) / 4 * 4;  // words
-}
-template <class Pat>
-__host__ __device__ constexpr size_t tiled_lds_bytes()
-{
-    return (tiled_ring_offset<Pat>() + kRingTab) * 4;
-}
+// LDS of a tile body: the bit-sliced tiles' words or the bit-row layout (two
+// row buffers, nine bases, one flag word), whichever the kind uses; bytes.
 constexpr size_t kBitsLds = 2 * (size_t)kBxBuf * 4 + 9 * 8 + 16;
 
-template <class Pat, int K>
-__device__ __forceinline__ void tiled_unit(const TileArgs &A, const uint8_t *in, uint8_t *out, uint64_t t,
+template <class P>
+__device__ __forceinline__ void tiled_unit(const SliceArgs &A, const uint8_t *in, uint8_t *out, uint64_t t, int32_t steps,
                                            unsigned char *smem)
 {
-    using LDS = TileLds<Pat>;
-    uint32_t *w = reinterpret_cast<uint32_t *>(smem);
-    if constexpr (K == 1) {
-        tile_body<Pat>(A, in, out, t, w, w + LDS::WORDS);
-    } else {
-        uint32_t *const buf[3] = {w, w + LDS::WORDS, w + 2 * LDS::WORDS};
-        tile_bodyK<Pat, K>(A, in, out, t, buf, w + tiled_ring_offset<Pat>());
-    }
+    slice_tile<P, false>(A, in, out, t, SliceRing{in, false}, steps, SliceRes{}, reinterpret_cast<uint32_t *>(smem));
+    __syncthreads();  // LDS is free for the next tile
 }
 
 template <int K>
@@ -300,9 +283,9 @@ __device__ __forceinline__ void tiled_run(const TiledInst &I, const uint8_t *in,
     const uint8_t *ii = in + I.base;
     uint8_t *oo = out + I.base;
     switch (I.kind) {
-    case kBTri: tiled_unit<PatTriangle, K>(I.t, ii, oo, j, smem); break;
-    case kBTriPaper: tiled_unit<PatTrianglePaper, K>(I.t, ii, oo, j, smem); break;
-    case kBVicsek: tiled_unit<PatVicsek, K>(I.t, ii, oo, j, smem); break;
+    case kBTri: tiled_unit<SliceTriSmall>(I.t, ii, oo, j, K, smem); break;
+    case kBTriPaper: tiled_unit<SlicePaperSmall>(I.t, ii, oo, j, K, smem); break;
+    case kBVicsek: tiled_unit<SliceVicsekSmall>(I.t, ii, oo, j, K, smem); break;
     default: bits_unit<K>(I.x, ii, oo, j, smem); break;
     }
 }
@@ -313,11 +296,10 @@ __device__ __forceinline__ void tiled_run(const TiledInst &I, const uint8_t *in,
 // cross; bit rows of the carpet).  Persistent (PerTile false): the sequence
 // is weighted by cells and workgroup b takes the tiles whose first cell falls
 // in the b-th equal share.  PerTile: one workgroup per tile, dealt to the
-// XCDs in contiguous runs, eight waves per SIMD; the persistent form at six
-// (its tile loop holds more registers).
+// XCDs in contiguous runs.
 template <int K, bool PerTile>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(PerTile ? 8 : 6)))
-k_batch_tiles(TiledArgs B, const uint8_t *__restrict__ in, uint8_t *__restrict__ out)
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
+k_batch_tiles(TiledArgs B, const uint8_t *in, uint8_t *out)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     if constexpr (PerTile) {
@@ -380,7 +362,9 @@ k_batch_tiles(TiledArgs B, const uint8_t *__restrict__ in, uint8_t *__restrict__
 // ---------------------------------------------------------------------------
 struct BatchGroup {
     uint32_t kind;  // kBTri, kBTriPaper, kBVicsek or kBBits
-    int K, K_max;   // steps per launch: chosen, most allowed
+    int K, K_max;   // steps per launch: chosen, most that can be chosen
+    int K_full;     // steps a launch can take at most (bit-sliced tiles: more than K_max; 0: any number)
+    unsigned threads;
     std::vector<uint32_t> members;
     uint64_t ntiles;
     void *d_args;
@@ -392,6 +376,7 @@ struct BatchHost {
     // (tiled_form 0), one persistent launch over all of them (1) or one launch
     // over all of them with a workgroup per tile (2); the autotuner picks
     std::vector<BatchGroup> groups;
+    std::vector<SliceConfig *> slices;  // tile configurations that are not a fractal's own
     int tiled_form;
     std::vector<TiledInst> tiled;
     TiledInst *d_tiled;
@@ -437,9 +422,9 @@ const FractalHost &fractal_host_of(const sqz_fractal *f);  // api.hip
 static uint32_t kind_of(const FractalHost &F)
 {
     if (F.bitbox) return kBBits;
-    if (F.tile_kind == 1) return kBTri;
-    if (F.tile_kind == 2) return kBTriPaper;
-    if (F.tile_kind == 3) return kBVicsek;
+    if (F.slice && F.tile_kind == 1) return kBTri;
+    if (F.slice && F.tile_kind == 2) return kBTriPaper;
+    if (F.slice && F.tile_kind == 3) return kBVicsek;
     if (F.xtile) return F.xtile->P == 84 ? kBX84 : (F.xtile->P == 68 ? kBX68 : kBXAny);
     return kBCell;
 }
@@ -485,6 +470,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
     H->cus = hipGetDeviceProperties(&prop, H->device) == hipSuccess ? prop.multiProcessorCount : 256;
     H->Kt_max = kMaxSteps;
     std::map<std::string, uint32_t> xcfg_ids;
+    std::map<const FractalHost *, SliceConfig *> slice_of;  // a fractal may occur many times
     std::vector<uint64_t> cell_start(count + 1);
     uint64_t off = 0, cstart = 0;
     size_t lds = 0, ldsk = 0;
@@ -515,12 +501,22 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                 H->Kt_max = std::min(H->Kt_max, bitbox_steps_per_launch(F));
                 H->tlds = std::max(H->tlds, kBitsLds);
             } else {
-                T.t = tile_args(F);
+                SliceConfig *&C = slice_of[&F];
+                if (!C) {
+                    bool own = true;
+                    const sqz_status st = slice_batch_config(F, &C, &own);
+                    if (st == SQZ_OK && !own) H->slices.push_back(C);
+                    if (st != SQZ_OK) {
+                        batch_destroy(H);
+                        return st;
+                    }
+                }
+                T.t = C->A;
                 T.units = T.t.ntiles;
-                T.unit_cells = T.t.tile;
+                T.unit_cells = T.t.cells;
                 H->Kt_max = std::min(H->Kt_max, tile_steps_per_launch(F));
-                H->tlds = std::max(H->tlds, I.kind == kBVicsek ? tiled_lds_bytes<PatVicsek>()
-                                                                : tiled_lds_bytes<PatTriangle>());
+                H->tlds = std::max<size_t>(H->tlds, I.kind == kBVicsek ? SliceCfg<SliceVicsekSmall>::LDS
+                                                                       : SliceCfg<SliceTriSmall>::LDS);
             }
             T.cost_start = H->tcost_total;
             H->tcost_total += T.units * T.unit_cells;
@@ -529,8 +525,15 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
             for (BatchGroup &g : H->groups)
                 if (g.kind == I.kind) G = &g;
             if (!G) {
-                H->groups.push_back(BatchGroup{I.kind, kMaxSteps, kMaxSteps, {}, 0, nullptr, nullptr, nullptr});
+                H->groups.push_back(BatchGroup{I.kind, kMaxSteps, kMaxSteps, 0, 0, {}, 0, nullptr, nullptr, nullptr});
                 G = &H->groups.back();
+            }
+            if (I.kind == kBBits) {
+                G->K_full = kMaxSteps;
+            } else {
+                const SliceConfig *C = slice_of[&F];
+                if (C->K) G->K_full = (int)C->K;  // the same for every fractal of more than one tile
+                G->threads = std::max(G->threads, (C->A.lanes + 63) / 64 * 64);
             }
             G->members.push_back((uint32_t)i);
             G->K_max = std::min(G->K_max, I.kind == kBBits ? bitbox_steps_per_launch(F) : tile_steps_per_launch(F));
@@ -677,7 +680,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
         BatchGroup &G = H->groups[g];
         const size_t m = G.members.size();
         const bool bits = G.kind == kBBits;
-        std::vector<TileArgs> ta(bits ? 0 : m);
+        std::vector<SliceArgs> ta(bits ? 0 : m);
         std::vector<BitboxArgs> ba(bits ? m : 0);
         std::vector<uint64_t> base(m), ts(m + 1);
         uint64_t tiles = 0;
@@ -689,13 +692,13 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                 ba[q] = bitbox_args(F);
                 tiles += ba[q].ntiles;
             } else {
-                ta[q] = tile_args(F);
+                ta[q] = slice_of[&F]->A;
                 tiles += ta[q].ntiles;
             }
         }
         ts[m] = tiles;
         G.ntiles = tiles;
-        const size_t asz = bits ? sizeof(BitboxArgs) * m : sizeof(TileArgs) * m;
+        const size_t asz = bits ? sizeof(BitboxArgs) * m : sizeof(SliceArgs) * m;
         e = hipMalloc(&G.d_args, asz);
         if (e == hipSuccess) e = hipMemcpy(G.d_args, bits ? (const void *)ba.data() : (const void *)ta.data(), asz,
                                            hipMemcpyHostToDevice);
@@ -704,7 +707,6 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
         if (e == hipSuccess) e = hipMalloc(&G.d_tstart, sizeof(uint64_t) * (m + 1));
         if (e == hipSuccess) e = hipMemcpy(G.d_tstart, ts.data(), sizeof(uint64_t) * (m + 1), hipMemcpyHostToDevice);
     }
-    if (e == hipSuccess) e = hipMalloc(&H->d_cost_start, sizeof(uint64_t) * (count + 1));
     H->xt_weight = 4;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
@@ -750,6 +752,7 @@ void batch_destroy(BatchHost *H)
     if (!H) return;
     if (H->gexec) (void)hipGraphExecDestroy(H->gexec);
     if (H->cap) (void)hipStreamDestroy(H->cap);
+    for (SliceConfig *S : H->slices) slice_free(S);
     (void)hipFree(H->d_inst);
     (void)hipFree(H->d_cost_start);
     (void)hipFree(H->d_tiled);
@@ -784,24 +787,6 @@ static sqz_status launch_batch(const BatchHost *H, unsigned wg_per_cu, const uin
     return e == hipSuccess ? SQZ_OK : hip_error(e, "batch launch");
 }
 
-template <class Pat>
-static void launch_tile_group(const GroupArgs &A, unsigned grid, const uint8_t *in, uint8_t *out, int steps,
-                              hipStream_t st)
-{
-    switch (steps) {
-    case 1: hipLaunchKernelGGL((k_batch_tile<Pat, 1>), dim3(grid), dim3(kBlock), 0, st, A, in, out); break;
-    case 2: hipLaunchKernelGGL((k_batch_tile<Pat, 2>), dim3(grid), dim3(kBlock), 0, st, A, in, out); break;
-    case 3: hipLaunchKernelGGL((k_batch_tile<Pat, 3>), dim3(grid), dim3(kBlock), 0, st, A, in, out); break;
-    case 4: hipLaunchKernelGGL((k_batch_tile<Pat, 4>), dim3(grid), dim3(kBlock), 0, st, A, in, out); break;
-    case 5: hipLaunchKernelGGL((k_batch_tile<Pat, 5>), dim3(grid), dim3(kBlock), 0, st, A, in, out); break;
-    case 6: hipLaunchKernelGGL((k_batch_tile<Pat, 6>), dim3(grid), dim3(kBlock), 0, st, A, in, out); break;
-    case 7: hipLaunchKernelGGL((k_batch_tile<Pat, 7>), dim3(grid), dim3(kBlock), 0, st, A, in, out); break;
-    case 8: hipLaunchKernelGGL((k_batch_tile<Pat, 8>), dim3(grid), dim3(kBlock), 0, st, A, in, out); break;
-    case 9: hipLaunchKernelGGL((k_batch_tile<Pat, 9>), dim3(grid), dim3(kBlock), 0, st, A, in, out); break;
-    default: hipLaunchKernelGGL((k_batch_tile<Pat, 10>), dim3(grid), dim3(kBlock), 0, st, A, in, out); break;
-    }
-}
-
 static void launch_bits_group(const GroupArgs &A, unsigned grid, const uint8_t *in, uint8_t *out, int steps,
                               hipStream_t st)
 {
@@ -820,15 +805,22 @@ static void launch_bits_group(const GroupArgs &A, unsigned grid, const uint8_t *
     }
 }
 
-// One launch of `steps` (1..G.K) steps for every instance of group G.
+// One launch of `steps` steps (bit rows: at most kMaxSteps, bit-sliced tiles:
+// at most K_full) for every instance of group G.
 static sqz_status launch_group(const BatchGroup &G, const uint8_t *in, uint8_t *out, int steps, hipStream_t st)
 {
     const GroupArgs A{G.d_args, G.d_base, G.d_tstart, (uint32_t)G.members.size()};
     const unsigned grid = (unsigned)G.ntiles;
     switch (G.kind) {
-    case kBTri: launch_tile_group<PatTriangle>(A, grid, in, out, steps, st); break;
-    case kBTriPaper: launch_tile_group<PatTrianglePaper>(A, grid, in, out, steps, st); break;
-    case kBVicsek: launch_tile_group<PatVicsek>(A, grid, in, out, steps, st); break;
+    case kBTri:
+        hipLaunchKernelGGL(k_batch_slice<SliceTriSmall>, dim3(grid), dim3(G.threads), 0, st, A, in, out, steps);
+        break;
+    case kBTriPaper:
+        hipLaunchKernelGGL(k_batch_slice<SlicePaperSmall>, dim3(grid), dim3(G.threads), 0, st, A, in, out, steps);
+        break;
+    case kBVicsek:
+        hipLaunchKernelGGL(k_batch_slice<SliceVicsekSmall>, dim3(grid), dim3(G.threads), 0, st, A, in, out, steps);
+        break;
     default: launch_bits_group(A, grid, in, out, steps, st); break;
     }
     const hipError_t e = hipGetLastError();
@@ -891,7 +883,9 @@ static sqz_status launch_all(const BatchHost *H, const uint8_t *a, const uint8_t
             s2 = launch_tiled(H, H->tiled_form, H->twg, (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
     } else {
         for (size_t g = 0; g < H->groups.size() && s2 == SQZ_OK; ++g) {
-            const std::vector<int> plan = plan_launches(steps, H->groups[g].K);
+            // the most the tiles can take, unless fewer were chosen
+            const BatchGroup &G = H->groups[g];
+            const std::vector<int> plan = plan_launches(steps, G.K < G.K_max ? G.K : G.K_full);
             for (size_t i = 0; i < plan.size() && s2 == SQZ_OK; ++i)
                 s2 = launch_group(H->groups[g], (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
         }

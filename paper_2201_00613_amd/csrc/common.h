@@ -114,21 +114,17 @@ __device__ __forceinline__ uint64_t splitmix64_at(uint64_t seed, uint64_t i)
 }
 
 // Launch sizes for `steps` steps with at most K per launch (temporal
-// blocking): launches of K steps and one of the remainder.  Every launch swaps
-// the two buffers, so the launch count must have the parity of `steps` for the
-// result to land where one-step launches would leave it; if it does not, the
-// last launch of two or more steps is split into (n - 1) + 1.
+// blocking; K < 1: any number): launches of nearly equal size.  Every launch
+// swaps the two buffers, so the launch count must have the parity of `steps`
+// for the result to land where one-step launches would leave it; if it does
+// not, there is one launch more.
 inline std::vector<int> plan_launches(int32_t steps, int K)
 {
-    std::vector<int> plan((size_t)(steps / K), K);
-    if (steps % K) plan.push_back(steps % K);
-    if ((plan.size() & 1) != (size_t)(steps & 1))
-        for (size_t i = plan.size(); i-- > 0;)
-            if (plan[i] >= 2) {
-                plan[i] -= 1;
-                plan.push_back(1);
-                break;
-            }
+    if (steps < 1) return {};
+    int n = K < 1 ? 1 : (int)(((int64_t)steps + K - 1) / K);
+    if ((n ^ steps) & 1) ++n;
+    std::vector<int> plan;
+    for (int i = 0; i < n; ++i) plan.push_back((int)((int64_t)steps * (i + 1) / n - (int64_t)steps * i / n));
     return plan;
 }
 

@@ -7,21 +7,21 @@
 
 namespace sqz {
 
-template <class P, int J>
-__global__ void __launch_bounds__((SliceCfg<P, J>::LANES))
+template <class P>
+__global__ void __launch_bounds__(SliceCfg<P>::LANES)
 k_slice(SliceArgs A, const uint8_t *in, uint8_t *out, SliceRing G, int32_t steps)
 {
-    __shared__ __align__(16) uint32_t sm[SliceCfg<P, J>::LDS / 4];
-    slice_tile<P, J, false>(A, in, out, xcd_remap(blockIdx.x, gridDim.x), G, steps, SliceRes{}, sm);
+    __shared__ __align__(16) uint32_t sm[SliceCfg<P>::LDS / 4];
+    slice_tile<P, false>(A, in, out, xcd_remap(blockIdx.x, gridDim.x), G, steps, SliceRes{}, sm);
 }
 
 // Resident run: one workgroup per tile, all on the chip at once.
-template <class P, int J>
-__global__ void __launch_bounds__((SliceCfg<P, J>::LANES))
+template <class P>
+__global__ void __launch_bounds__(SliceCfg<P>::LANES)
 k_slice_run(SliceArgs A, uint8_t *a, uint8_t *b, int32_t steps, SliceRes R)
 {
-    __shared__ __align__(16) uint32_t sm[SliceCfg<P, J>::LDS / 4];
-    slice_tile<P, J, true>(A, a, (steps & 1) ? b : a, xcd_remap(blockIdx.x, gridDim.x), SliceRing{a, false}, steps, R, sm);
+    __shared__ __align__(16) uint32_t sm[SliceCfg<P>::LDS / 4];
+    slice_tile<P, true>(A, a, (steps & 1) ? b : a, xcd_remap(blockIdx.x, gridDim.x), SliceRing{a, false}, steps, R, sm);
 }
 
 // Every tile's corner subtrees, kSliceCornerPitch bytes each: a wave per subtree.
@@ -61,45 +61,33 @@ __global__ void __launch_bounds__(256) k_slice_clear(uint32_t *p, uint64_t n)
     for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (uint64_t)gridDim.x * 256) p[i] = 0;
 }
 
-struct SliceConfig {
-    int kind;        // tile_kind_for's
-    int J;
-    uint32_t K;      // steps per launch and between exchanges (0: one tile, any number)
-    SliceArgs A;
-    uint32_t *d_tab; // lane_block, lane_halo, perm, nbtile
-    // resident run (null: not available): exchange words, epochs, loaded counts, timed-out word
-    uint32_t *d_res;
-    uint64_t res_words;
-    SliceRes R;
-};
-
 namespace {
 
-constexpr int kSliceBig = 17;  // level from which tiles are level 11 (triangles)
-
-// Tile and block levels.  Triangles to level 16: at most 243 tiles, one per
+// Tile level and kernel.  Triangles to level 16: at most 243 tiles, one per
 // CU, of at least level 8, with level-2 blocks (more waves per SIMD: at level
 // 16 three waves of 45 instructions per step rather than one of 121, which
-// alone on its SIMD issues at less than half the rate).  Above: level-11
-// tiles with level-3 blocks, several workgroups per CU, where the chip is
-// full anyway and the larger block publishes and reads a third of the words.
+// alone on its SIMD issues at less than half the rate: 70 against 87 us per
+// 100 steps).  Above: level-11 tiles with level-3 blocks, several workgroups
+// per CU, where the chip is full anyway and the larger block publishes and
+// reads a third of the words (level 20, 20 steps: 1.58 against 2.31 ms).
 // Vicsek crosses: level-6 tiles to level 9, level-7 above (at most 125 tiles
 // to level 10), level-1 and level-2 blocks in the same way.
-void slice_levels(int kind, int r, int &M, int &J)
+void slice_levels(int kind, int r, int &M, int &var)
 {
     if (kind == 3) {
         M = r <= 9 ? std::min(r, 6) : 7;
-        J = r <= 10 ? 1 : 2;
+        var = r <= 9 ? 0 : (r == 10 ? 1 : 2);
     } else {
-        M = r >= kSliceBig ? 11 : std::min(r, std::max(8, r - 5));
-        J = r >= kSliceBig ? 3 : 2;
+        M = r >= 17 ? 11 : std::min(r, std::max(8, r - 5));
+        var = r >= 17 ? 2 : (M <= 8 ? 0 : 1);
     }
 }
 
-template <class P, int J>
+template <class P>
 SliceSpec slice_spec(int M)
 {
-    using C = SliceCfg<P, J>;
+    using C = SliceCfg<P>;
+    constexpr int J = P::J;
     constexpr const SlicePlan &PL = C::PL;
     SliceSpec S{};
     S.M = M;
@@ -131,54 +119,64 @@ SliceSpec slice_spec(int M)
     return S;
 }
 
-// Calls f(pattern type, integral_constant J) for a configuration's kernel.
+// Calls f with the kernel's pattern type.
 template <class F>
-auto slice_dispatch(int kind, int J, F &&f)
+auto slice_dispatch(int kind, int var, F &&f)
 {
-    if (kind == 3) return J == 1 ? f(SliceVicsek{}, std::integral_constant<int, 1>{}) : f(SliceVicsek{}, std::integral_constant<int, 2>{});
-    if (kind == 2)
-        return J == 2 ? f(SliceTrianglePaper{}, std::integral_constant<int, 2>{})
-                      : f(SliceTrianglePaper{}, std::integral_constant<int, 3>{});
-    return J == 2 ? f(SliceTriangle{}, std::integral_constant<int, 2>{}) : f(SliceTriangle{}, std::integral_constant<int, 3>{});
+    switch (3 * kind + var) {
+    case 3: return f(SliceTriSmall{});
+    case 4: return f(SliceTri{});
+    case 5: return f(SliceTriWide{});
+    case 6: return f(SlicePaperSmall{});
+    case 7: return f(SlicePaper{});
+    case 8: return f(SlicePaperWide{});
+    case 9: return f(SliceVicsekSmall{});
+    case 10: return f(SliceVicsek{});
+    default: return f(SliceVicsekWide{});
+    }
 }
 
 unsigned slice_threads(const SliceConfig &S) { return (S.A.lanes + 63) / 64 * 64; }
 
 }  // namespace
 
+void slice_free(SliceConfig *S)
+{
+    if (!S) return;
+    (void)hipFree(S->d_tab);
+    if (S->d_res) (void)hipFree(S->d_res);
+    if (S->R.flag) (void)hipHostFree(S->R.flag);
+    delete S;
+}
+
 void slice_release(FractalHost &F)
 {
-    if (!F.slice) return;
-    (void)hipFree(F.slice->d_tab);
-    if (F.slice->d_res) (void)hipFree(F.slice->d_res);
-    if (F.slice->R.flag) (void)hipHostFree(F.slice->R.flag);
-    delete F.slice;
+    slice_free(F.slice);
     F.slice = nullptr;
 }
 
-// Every pattern with a bit-sliced tile from the level at which a subtile
-// holds a block; smaller fractals keep the kernels of tile_device.h alone.
-sqz_status slice_prepare(FractalHost &F)
+static int slice_kind(const FractalHost &F) { return F.tile_kind == 4 ? 1 : F.tile_kind; }
+
+// Tables of tiles of level M for kernel `var`; *out stays null where a subtile
+// would be smaller than a block.
+static sqz_status slice_build(const FractalHost &F, int M, int var, SliceConfig **out)
 {
-    F.slice = nullptr;
-    const int kind = F.tile_kind == 4 ? 1 : F.tile_kind;
-    if (!kind || !F.tile) return SQZ_OK;
-    int M, J;
-    slice_levels(kind, F.r, M, J);
-    if (M - (kind == 3 ? 2 : 3) < J) return SQZ_OK;
+    *out = nullptr;
+    const int kind = slice_kind(F);
+    SliceTables T;
+    bool small = false;
+    sqz_status st = slice_dispatch(kind, var, [&](auto p) {
+        using P = decltype(p);
+        small = M - P::B < P::J;
+        return small ? SQZ_OK : slice_tables(F, slice_spec<P>(M), T);
+    });
+    if (st != SQZ_OK || small) return st;
     SliceConfig *S = new SliceConfig();
     S->kind = kind;
-    S->J = J;
-    SliceTables T;
-    int passes = 0;
-    sqz_status st = slice_dispatch(kind, J, [&](auto p, auto j) {
-        const SliceSpec spec = slice_spec<decltype(p), decltype(j)::value>(M);
-        passes = spec.passes;
-        return slice_tables(F, spec, T);
-    });
+    S->var = var;
     MapParams Pc;
     void *d_coarse = nullptr;
-    if (st == SQZ_OK && T.nring) st = build_map_params(F, F.r - M, Pc, &d_coarse);
+    if (T.nring) st = build_map_params(F, F.r - M, Pc, &d_coarse);
     if (st != SQZ_OK) {
         delete S;
         return st;
@@ -232,8 +230,28 @@ sqz_status slice_prepare(FractalHost &F)
         delete S;
         return hip_error(e, "slice table setup");
     }
-    F.slice = S;
+    *out = S;
     return SQZ_OK;
+}
+
+// Every pattern with a bit-sliced tile from the level at which a subtile
+// holds a block.
+sqz_status slice_prepare(FractalHost &F)
+{
+    F.slice = nullptr;
+    if (!F.tile_kind || !F.tile) return SQZ_OK;
+    int M, var;
+    slice_levels(slice_kind(F), F.r, M, var);
+    return slice_build(F, M, var, &F.slice);
+}
+
+sqz_status slice_batch_config(const FractalHost &F, SliceConfig **out, bool *own)
+{
+    *own = true;
+    *out = F.slice;
+    if (!F.slice || F.slice->var == 0) return SQZ_OK;
+    *own = false;
+    return slice_build(F, slice_kind(F) == 3 ? 6 : 8, 0, out);
 }
 
 // State of the resident run, where the fractal offers one and all tiles are
@@ -244,25 +262,28 @@ void slice_prepare_resident(FractalHost &F)
     if (!S || !tile_resident(F)) return;
     const unsigned nt = slice_threads(*S);
     int per_cu = 0, cus = 0;
-    const hipError_t q = slice_dispatch(S->kind, S->J, [&](auto p, auto j) {
+    int nc = 0;
+    const hipError_t q = slice_dispatch(S->kind, S->var, [&](auto p) {
         using P = decltype(p);
-        constexpr int J = decltype(j)::value;
-        hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_slice_run<P, J>, (int)nt, 0);
+        nc = SlicePlanOf<P, P::J>::value.nc;
+        if constexpr (P::J == (P::B == 2 ? 2 : 3)) {
+            return hipErrorNotSupported;  // wide kernels: more tiles than the chip holds
+        } else {
+        hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_slice_run<P>, (int)nt, 0);
         hipFuncAttributes fa;
-        if (r == hipSuccess) r = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(k_slice_run<P, J>));
+        if (r == hipSuccess) r = hipFuncGetAttributes(&fa, reinterpret_cast<const void *>(k_slice_run<P>));
         if (r == hipSuccess) {  // a workgroup's waves are dealt to four SIMDs: the fullest one bounds the count
             const int vgprs = fa.numRegs > 0 ? (fa.numRegs + 7) / 8 * 8 : 512;
             per_cu = std::min(per_cu, std::min(8, 512 / vgprs) / (int)((nt / 64 + 3) / 4));
         }
         return r;
+        }
     });
     if (q != hipSuccess || hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, F.device) != hipSuccess) {
         (void)hipGetLastError();
         return;
     }
     if (per_cu < 1 || S->A.ntiles > (uint64_t)per_cu * (uint64_t)cus) return;
-    int nc = 1;
-    for (int i = 0; i < S->J; ++i) nc *= F.k;
     const uint64_t nx = 2 * S->A.ntiles * S->A.ncorner * (S->A.rwords / (uint32_t)nc);
     S->res_words = nx + 2 * S->A.ntiles + 1;
     uint32_t *d = nullptr, *h = nullptr;
@@ -297,9 +318,11 @@ sqz_status slice_run_resident(const FractalHost &F, uint8_t *a, uint8_t *b, int 
         return set_error(SQZ_ERR_HIP, "a wait of an earlier resident run timed out: its result is invalid");
     }
     if (steps < 1) return SQZ_OK;
-    slice_dispatch(S.kind, S.J, [&](auto p, auto j) {
-        hipLaunchKernelGGL((k_slice_run<decltype(p), decltype(j)::value>), dim3((unsigned)S.A.ntiles),
-                           dim3(slice_threads(S)), 0, st, S.A, a, b, steps, S.R);
+    slice_dispatch(S.kind, S.var, [&](auto p) {
+        using P = decltype(p);
+        if constexpr (P::J < (P::B == 2 ? 2 : 3))
+            hipLaunchKernelGGL(k_slice_run<P>, dim3((unsigned)S.A.ntiles), dim3(slice_threads(S)), 0, st, S.A, a, b,
+                               steps, S.R);
         return 0;
     });
     const hipError_t e = hipGetLastError();
@@ -325,9 +348,9 @@ sqz_status slice_run_launches(const FractalHost &F, uint8_t *a, uint8_t *b, int 
                                S.A, cur, other);
         const SliceRing G{in_place ? other : cur, in_place};
         uint8_t *dst = in_place ? cur : other;
-        slice_dispatch(S.kind, S.J, [&](auto p, auto j) {
-            hipLaunchKernelGGL((k_slice<decltype(p), decltype(j)::value>), dim3((unsigned)S.A.ntiles),
-                               dim3(slice_threads(S)), 0, st, S.A, cur, dst, G, k);
+        slice_dispatch(S.kind, S.var, [&](auto p) {
+            hipLaunchKernelGGL(k_slice<decltype(p)>, dim3((unsigned)S.A.ntiles), dim3(slice_threads(S)), 0, st, S.A,
+                               cur, dst, G, k);
             return 0;
         });
         const hipError_t e = hipGetLastError();

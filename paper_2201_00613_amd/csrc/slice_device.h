@@ -43,16 +43,42 @@
 
 namespace sqz {
 
-// Bit level B (k^B subtiles per tile) and ring level RL of a pattern; LMAX(J):
-// largest subtile level with lanes of level-J blocks.
-struct SliceTriangle : PatTriangle {
-    static constexpr int B = 3, RL = 5, LMAX = 8;
+// Bit level B (k^B subtiles per tile), ring level RL, block level J and largest
+// subtile level LMAX of a kernel.  *Small: subtiles of at most 243 (625) words,
+// always loaded four cells a lane (fewer registers and less LDS, so more
+// workgroups per CU: batches).
+struct SliceTri : PatTriangle {
+    static constexpr int B = 3, RL = 5, J = 2, LMAX = 8;
+    static constexpr bool SMALL = false;
 };
-struct SliceTrianglePaper : PatTrianglePaper {
-    static constexpr int B = 3, RL = 5, LMAX = 8;
+struct SliceTriSmall : SliceTri {
+    static constexpr int LMAX = 5;
+    static constexpr bool SMALL = true;
+};
+struct SliceTriWide : SliceTri {
+    static constexpr int J = 3;
+};
+struct SlicePaper : PatTrianglePaper {
+    static constexpr int B = 3, RL = 5, J = 2, LMAX = 8;
+    static constexpr bool SMALL = false;
+};
+struct SlicePaperSmall : SlicePaper {
+    static constexpr int LMAX = 5;
+    static constexpr bool SMALL = true;
+};
+struct SlicePaperWide : SlicePaper {
+    static constexpr int J = 3;
 };
 struct SliceVicsek : PatVicsek {
-    static constexpr int B = 2, RL = 3, LMAX = 5;
+    static constexpr int B = 2, RL = 3, J = 1, LMAX = 5;
+    static constexpr bool SMALL = false;
+};
+struct SliceVicsekSmall : SliceVicsek {
+    static constexpr int LMAX = 4;
+    static constexpr bool SMALL = true;
+};
+struct SliceVicsekWide : SliceVicsek {
+    static constexpr int J = 2;
 };
 
 // ---------------------------------------------------------------------------
@@ -156,8 +182,9 @@ constexpr int kSliceMaxRing = 8;  // ring subtrees per tile
 // a zero word, the published words of every block (odd pitch, so that lanes
 // of consecutive blocks hit different banks), the subtile halo, the ring
 // subtrees' halo.
-template <class P, int J>
+template <class P>
 struct SliceCfg {
+    static constexpr int J = P::J;
     static constexpr const SlicePlan &PL = SlicePlanOf<P, J>::value;
     static constexpr int KB = cpow(P::K, P::B);
     static constexpr int NG = (KB + 7) / 8;  // byte groups of a word
@@ -409,11 +436,12 @@ __device__ __forceinline__ void slice_wait(const SliceRes &R, F &&ready)
 // One tile, `steps` >= 1 steps (at most K without RES; any number when the
 // fractal is one tile).  in, out: the whole compact arrays, the same one for
 // an update in place.  Every lane of the workgroup calls it.
-template <class P, int J, bool RES>
+template <class P, bool RES>
 __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in, uint8_t *out, uint64_t t,
                                            const SliceRing &G, int32_t steps, const SliceRes &R, uint32_t *sm)
 {
-    using C = SliceCfg<P, J>;
+    using C = SliceCfg<P>;
+    constexpr int J = C::J;
     using PO = SlicePlanOf<P, J>;
     constexpr int NC = PO::value.nc, NH = PO::value.nh, NE = PO::value.ne, NPT = C::NPT;
     const uint32_t tid = threadIdx.x, NT = blockDim.x;
@@ -450,11 +478,11 @@ __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in
         const uint8_t *src = in + t * A.cells;
         const uint32_t rt = A.nring ? (A.rwords + 3) / 4 : 0u;
         // four cells per task where that fills the lanes in one pass, else sixteen
-        if (A.words <= 4 * NT) {
+        if (P::SMALL || A.words <= 4 * NT) {
             const uint32_t n = (A.words + 3) / 4;
             for (uint32_t k = tid; k < n; k += NT)
                 slice_load_words<C, 1>(src, A.words, 4 * k + 4 <= A.words ? 4 * k : A.words - 4, sm);
-        } else {
+        } else if constexpr (!P::SMALL) {
             const uint32_t n = (A.words + 15) / 16;
             for (uint32_t k = tid; k < n; k += NT)
                 slice_load_words<C, 4>(src, A.words, 16 * k + 16 <= A.words ? 16 * k : A.words - 16, sm);
@@ -595,15 +623,33 @@ __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in
     // fits it and is read again by the next run: plain ones (level 16: 70.1 us
     // per 100 steps, 71.4 nontemporal).
     uint8_t *dst = out + t * A.cells;
-    if (A.words <= 4 * NT) {
+    if (P::SMALL || A.words <= 4 * NT) {
         const uint32_t n = (A.words + 3) / 4;
         for (uint32_t k = tid; k < n; k += NT)
             slice_store_words<C, 1, false>(dst, A.words, 4 * k + 4 <= A.words ? 4 * k : A.words - 4, sm);
-    } else {
+    } else if constexpr (!P::SMALL) {
         const uint32_t n = (A.words + 15) / 16;
         for (uint32_t k = tid; k < n; k += NT)
             slice_store_words<C, 4, !RES>(dst, A.words, 16 * k + 16 <= A.words ? 16 * k : A.words - 16, sm);
     }
 }
+
+// Host side (slice.hip): one tile configuration of a fractal.
+struct SliceConfig {
+    int kind, var;   // pattern (tile_kind_for), kernel (0 small, 1, 2 wide)
+    uint32_t K;      // steps per launch and between exchanges (0: one tile, any number)
+    SliceArgs A;
+    uint32_t *d_tab; // lane_block, lane_halo, perm, nbtile
+    // resident run (null: not available): exchange words, epochs, loaded counts, timed-out word
+    uint32_t *d_res;
+    uint64_t res_words;
+    SliceRes R;
+};
+
+// A batch's tiles: small ones (level-8 triangles, level-6 Vicsek crosses at
+// most), many per CU.  *own is true where the configuration is the fractal's
+// own one, else the caller frees it (slice_free).
+sqz_status slice_batch_config(const FractalHost &F, SliceConfig **out, bool *own);
+void slice_free(SliceConfig *S);
 
 }  // namespace sqz

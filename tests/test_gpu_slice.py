@@ -66,3 +66,19 @@ def test_runs_one_cell_into_a_buffer():
                 assert torch.equal(res, want), form
             for t in (a, b):
                 assert bool((t[:32] == 9).all()) and bool((t[32 + F.cells:] == 9).all()), (form, steps)
+
+
+@pytest.mark.parametrize("steps", [1, 27, 31, 32, 63])
+def test_batch_equals_single_runs(steps):
+    """A batch's own tiles (level 8, level 6): fractals whose single runs use larger ones included."""
+    torch = torch_or_skip()
+    import paper_2201_00613_amd as sqz
+
+    fr = [gpu_fractal(n, r) for n, r in [("triangle", 5), ("triangle", 9), ("triangle", 14), ("triangle", 15),
+                                         ("triangle_paper", 14), ("vicsek", 4), ("vicsek", 7), ("vicsek", 10)]]
+    B = sqz.Batch(fr)
+    a = B.fill_bernoulli([11 * i for i in range(len(fr))], 0.5)
+    res = B.run(a, B.empty_state(), steps)
+    for i, F in enumerate(fr):
+        x = F.fill_bernoulli(11 * i, 0.5)
+        assert torch.equal(B.instance(res, i), F.compact_run(x, torch.empty_like(x), steps)), (i, steps)
