@@ -63,7 +63,8 @@ typedef enum sqz_layout { SQZ_LAYOUT_COMPACT = 0, SQZ_LAYOUT_EXPANDED = 1 } sqz_
 /* Implementation of the compact stencil.
  *   SQZ_IMPL_AUTO: TILE when the pattern has a bit-sliced tiled kernel and the
  *                  buffers are 16-byte aligned, else BITS when it has bit-row
- *                  tiles and the buffers are 8-byte aligned, else XTILE, else CELL.
+ *                  tiles and the buffers are 8-byte aligned, else expanded tiles
+ *                  (as bit rows where cells are sparse in them, else XTILE), else CELL.
  *   SQZ_IMPL_CELL: thread-level Squeeze: one lambda and eight nu per cell
  *                  (Section "Exploring Compact Fractal Space").
  *   SQZ_IMPL_TILE: block-level Squeeze (Section "Moving from Thread-level to

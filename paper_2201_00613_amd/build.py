@@ -19,7 +19,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(ROOT, "include")
 LIB = os.path.join(PKG, "libsqueeze.so")
 OBJDIR = os.path.join(ROOT, "_build", "obj")
-SOURCES = ["api.hip", "maps.hip", "mfma_maps.hip", "blocks.hip", "bb.hip", "life_tile.hip", "xtile.hip", "bitbox.hip", "slice.hip", "lane.hip",
+SOURCES = ["api.hip", "maps.hip", "mfma_maps.hip", "blocks.hip", "bb.hip", "life_tile.hip", "xtile.hip", "bitbox.hip", "slice.hip", "lane.hip", "gbox.hip",
            "batch.hip"]
 HOST_SOURCES = ["host_tables.cpp"]
 ARCH = os.environ.get("SQZ_OFFLOAD_ARCH", "gfx950")

@@ -124,6 +124,7 @@ sqz_status sqz_fractal_create(int32_t s, int32_t k, const int32_t *offsets_xy, i
     f->h.bitbox = nullptr;
     f->h.slice = nullptr;
     f->h.lane = nullptr;
+    f->h.gbox = nullptr;
     f->h.mfma = mfma_prepare(f->h);  // null when the pattern does not fit int8 digits
     if (f->h.tile_kind) st = tile_prepare(f->h);
     if (st == SQZ_OK) st = slice_prepare(f->h);
@@ -131,9 +132,11 @@ sqz_status sqz_fractal_create(int32_t s, int32_t k, const int32_t *offsets_xy, i
     if (st == SQZ_OK) st = lane_prepare(f->h);
     if (st == SQZ_OK) st = xtile_prepare(f->h);
     if (st == SQZ_OK) st = bitbox_prepare(f->h);
+    if (st == SQZ_OK) st = gbox_prepare(f->h);
     if (st != SQZ_OK) {
         slice_release(f->h);
         lane_release(f->h);
+        gbox_release(f->h);
         tile_release(f->h);
         xtile_release(f->h);
         bitbox_release(f->h);
@@ -151,6 +154,7 @@ void sqz_fractal_destroy(sqz_fractal *f)
     if (!f) return;
     slice_release(f->h);
     lane_release(f->h);
+    gbox_release(f->h);
     tile_release(f->h);
     xtile_release(f->h);
     bitbox_release(f->h);
@@ -279,6 +283,7 @@ sqz_status sqz_compact_step_impl(const sqz_fractal *f, sqz_impl impl, const uint
         // words; unaligned buffers skip them
         if (f->h.tile_kind && aligned) return launch_life_tile(f->h, d_in, d_out, s);
         if (f->h.bitbox && aligned8) return launch_life_bitbox(f->h, d_in, d_out, 1, s);
+        if (gbox_one_step(f->h)) return launch_life_gbox(f->h, d_in, d_out, 1, s);
         if (f->h.xtile) return launch_life_xtile(f->h, d_in, d_out, s);
         return launch_life_cell(f->h.P, d_in, d_out, s);
     case SQZ_IMPL_BITS:
@@ -361,6 +366,16 @@ sqz_status sqz_compact_run_form(const sqz_fractal *f, sqz_run_form form, uint8_t
         return run_resident(f->h, d_a, d_b, steps, (hipStream_t)stream);
     if (aligned && slice_available(f->h) && steps >= 2)
         return slice_run_launches(f->h, d_a, d_b, steps, (hipStream_t)stream);
+    if (f->h.gbox && steps >= 2) {
+        const std::vector<int> plan = plan_launches(steps, gbox_steps_per_launch(f->h));
+        for (size_t i = 0; i < plan.size() && st == SQZ_OK; ++i) {
+            const uint8_t *in = (i & 1) ? d_b : d_a;
+            uint8_t *out = (i & 1) ? d_a : d_b;
+            st = plan[i] == 1 && !gbox_one_step(f->h) ? launch_life_xtile(f->h, in, out, (hipStream_t)stream)
+                                                      : launch_life_gbox(f->h, in, out, plan[i], (hipStream_t)stream);
+        }
+        return st;
+    }
     const bool aligned8 = !(((uintptr_t)d_a | (uintptr_t)d_b) & 7);
     const bool tiled = f->h.tile_kind && aligned, bits = !tiled && f->h.bitbox && aligned8;
     const int K = tiled ? tile_steps_per_launch(f->h)

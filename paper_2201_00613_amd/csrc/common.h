@@ -211,6 +211,13 @@ bool lane_one_step(const FractalHost &F);  // a single step is faster with these
 sqz_status lane_diffuse_run(const FractalHost &F, int dtype, float coef, int rounding, uint64_t seed, uint64_t first,
                             int steps, const void *a, void *b, hipStream_t st);
 
+// Bit rows of an expanded tile for patterns without a kernel of their own (gbox.hip)
+sqz_status gbox_prepare(FractalHost &F);  // after the other Life kernels
+void gbox_release(FractalHost &F);
+bool gbox_one_step(const FractalHost &F);  // a single step is faster with it too
+int gbox_steps_per_launch(const FractalHost &F);  // 0: any number (one tile); -1: no bit box
+sqz_status launch_life_gbox(const FractalHost &F, const uint8_t *in, uint8_t *out, int steps, hipStream_t st);
+
 // Batched Life (batch.hip)
 struct BatchHost;
 sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost **out);

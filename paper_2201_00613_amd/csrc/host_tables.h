@@ -86,6 +86,7 @@ struct MfmaParams;    // mfma_maps.hip
 struct BitboxConfig;  // bitbox.hip
 struct SliceConfig;   // slice.hip
 struct LaneConfig;    // lane.hip
+struct GboxConfig;    // gbox.hip
 
 struct FractalHost {
     int32_t s, k, r;
@@ -104,6 +105,7 @@ struct FractalHost {
     BitboxConfig *bitbox;         // bit-row expanded tiles (dense s = 3 patterns), null if none
     SliceConfig *slice;           // tiles bit-sliced across subtrees (several steps per launch), null if none
     LaneConfig *lane;             // diffusion with a block per lane, null if none
+    GboxConfig *gbox;             // bit rows of an expanded tile, patterns without a kernel of their own, null if none
 };
 
 // ---------------------------------------------------------------------------
