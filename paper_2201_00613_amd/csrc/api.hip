@@ -163,6 +163,12 @@ void sqz_fractal_destroy(sqz_fractal *f)
     delete f;
 }
 
+static bool small(const FractalHost &h) { return h.N <= kSmallCells; }
+
+// The resident run is offered for patterns with a bit-sliced tile whose tiles
+// are few enough (a fractal of one workgroup always).
+static bool resident(const FractalHost &h) { return h.tile_kind && tile_few(h) && (small(h) || slice_resident(h)); }
+
 sqz_status sqz_fractal_info(const sqz_fractal *f, sqz_info *out)
 {
     if (!f || !out) return set_error(SQZ_ERR_INVALID, "NULL argument");
@@ -176,7 +182,7 @@ sqz_status sqz_fractal_info(const sqz_fractal *f, sqz_info *out)
                   kx = xtile_steps_per_launch(f->h);
         const int k = f->h.tile_kind ? kt : (f->h.bitbox ? kb : kx);
         out->run_steps_per_launch = k > 1 ? k : 1;
-        out->resident_run = tile_resident(f->h) ? 1 : 0;
+        out->resident_run = resident(f->h) ? 1 : 0;
     }
     return SQZ_OK;
 }
@@ -323,7 +329,7 @@ constexpr int32_t kAutoResidentSteps = 10;
 
 static bool auto_resident(const FractalHost &h, int32_t steps)
 {
-    if (steps < 2 || !tile_resident(h)) return false;
+    if (steps < 2 || !resident(h)) return false;
     if (steps >= kAutoResidentSteps) return true;
     const int K = tile_steps_per_launch(h);
     return plan_launches(steps, K).size() > (size_t)((steps + K - 1) / K);
@@ -331,8 +337,9 @@ static bool auto_resident(const FractalHost &h, int32_t steps)
 
 static sqz_status run_resident(const FractalHost &h, uint8_t *a, uint8_t *b, int32_t steps, hipStream_t st)
 {
-    if (slice_resident(h)) return slice_run_resident(h, a, b, steps, st);
-    return launch_life_tile_resident(h, a, b, steps, st);
+    if (steps < 1) return SQZ_OK;
+    if (small(h)) return launch_life_small(h.P, a, (steps & 1) ? b : a, steps, st);
+    return slice_run_resident(h, a, b, steps, st);
 }
 
 sqz_status sqz_run_form_auto(const sqz_fractal *f, int32_t steps, sqz_run_form *form)
@@ -357,13 +364,15 @@ sqz_status sqz_compact_run_form(const sqz_fractal *f, sqz_run_form form, uint8_t
     if (overlap(d_a, d_b, f->h.N)) return set_error(SQZ_ERR_INVALID, "d_a and d_b overlap");
     const bool aligned = !(((uintptr_t)d_a | (uintptr_t)d_b) & 15);
     if (form == SQZ_RUN_RESIDENT) {
-        if (!tile_resident(f->h))
+        if (!resident(f->h))
             return set_error(SQZ_ERR_UNSUPPORTED, "no resident run: the tiles of this fractal do not fit the chip at once");
         if (!aligned) return set_error(SQZ_ERR_INVALID, "the resident run needs 16-byte aligned buffers");
         return run_resident(f->h, d_a, d_b, steps, (hipStream_t)stream);
     }
     if (form == SQZ_RUN_AUTO && aligned && auto_resident(f->h, steps))
         return run_resident(f->h, d_a, d_b, steps, (hipStream_t)stream);
+    if (small(f->h) && steps >= 2)
+        return launch_life_small(f->h.P, d_a, (steps & 1) ? d_b : d_a, steps, (hipStream_t)stream);
     if (aligned && slice_available(f->h) && steps >= 2)
         return slice_run_launches(f->h, d_a, d_b, steps, (hipStream_t)stream);
     if (f->h.gbox && steps >= 2) {
@@ -377,18 +386,15 @@ sqz_status sqz_compact_run_form(const sqz_fractal *f, sqz_run_form form, uint8_t
         return st;
     }
     const bool aligned8 = !(((uintptr_t)d_a | (uintptr_t)d_b) & 7);
-    const bool tiled = f->h.tile_kind && aligned, bits = !tiled && f->h.bitbox && aligned8;
-    const int K = tiled ? tile_steps_per_launch(f->h)
-                        : (bits ? bitbox_steps_per_launch(f->h) : xtile_steps_per_launch(f->h));
+    const bool bits = f->h.bitbox && aligned8;
+    const int K = bits ? bitbox_steps_per_launch(f->h) : (f->h.tile_kind && aligned ? 1 : xtile_steps_per_launch(f->h));
     if (K >= 2) {
         const std::vector<int> plan = plan_launches(steps, K);
         const hipStream_t s = (hipStream_t)stream;
         for (size_t i = 0; i < plan.size() && st == SQZ_OK; ++i) {
             const uint8_t *in = (i & 1) ? d_b : d_a;
             uint8_t *out = (i & 1) ? d_a : d_b;
-            if (tiled)
-                st = launch_life_tile_steps(f->h, in, out, plan[i], s);
-            else if (bits)
+            if (bits)
                 st = launch_life_bitbox(f->h, in, out, plan[i], s);
             else
                 st = launch_life_xtile_steps(f->h, in, out, plan[i], s);

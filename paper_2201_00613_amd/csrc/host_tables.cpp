@@ -6,8 +6,6 @@
 #include <stdio.h>
 #include <string.h>
 
-#include <map>
-#include <set>
 #include <utility>
 
 namespace sqz {
@@ -123,6 +121,30 @@ static int nu_chunk(int s, int k)
     return c;
 }
 
+// Cells of a level's box by position (x + side*y), kNuHole32 for a hole: one
+// level at a time, each a copy of the one below per replica.
+static std::vector<uint32_t> nu_square(const FractalHost &F, int levels)
+{
+    const uint64_t s = (uint64_t)F.s, side = upow(s, levels);
+    std::vector<uint32_t> t(side * side, kNuHole32);
+    t[0] = 0;
+    uint64_t sp = 1, kp = 1;  // the sp x sp corner holds the levels done so far
+    for (int i = 0; i < levels; ++i) {
+        for (int q = (int)(s * s) - 1; q >= 0; --q) {
+            const int j = F.hnu[q];
+            const uint64_t x0 = (uint64_t)q % s * sp, y0 = (uint64_t)q / s * sp;
+            for (uint64_t y = 0; y < sp; ++y)
+                for (uint64_t x = 0; x < sp; ++x) {
+                    const uint32_t v = t[x + side * y];
+                    t[x0 + x + side * (y0 + y)] = j < 0 || v == kNuHole32 ? kNuHole32 : v + (uint32_t)(j * kp);
+                }
+        }
+        sp *= s;
+        kp *= (uint64_t)F.k;
+    }
+    return t;
+}
+
 void map_tables(const FractalHost &F, int level, MapParams &P, MapTables &T)
 {
     const int s = F.s, k = F.k;
@@ -146,44 +168,21 @@ void map_tables(const FractalHost &F, int level, MapParams &P, MapTables &T)
     P.dklam32 = make_div32(P.klam);
     P.dsnu = make_div32(P.snu);
 
-    // lambda tables: digit chunk -> packed (x | y << 16)
+    // lambda tables: digit chunk -> packed (x | y << 16), one level at a time
     auto lam_table = [&](int levels, std::vector<uint32_t> &t) {
-        const uint64_t cnt = upow(k, levels);
-        t.resize(cnt);
-        for (uint64_t d = 0; d < cnt; ++d) {
-            uint64_t v = d, sp = 1, x = 0, y = 0;
-            for (int i = 0; i < levels; ++i) {
-                const int beta = (int)(v % k);
-                v /= k;
-                x += F.ox[beta] * sp;
-                y += F.oy[beta] * sp;
-                sp *= s;
+        t.assign(upow(k, levels), 0);
+        uint64_t cnt = 1, sp = 1;
+        for (int i = 0; i < levels; ++i) {
+            for (int j = k - 1; j >= 0; --j) {
+                const uint32_t o = (uint32_t)(F.ox[j] * sp) + ((uint32_t)(F.oy[j] * sp) << 16);
+                for (uint64_t d = 0; d < cnt; ++d) t[j * cnt + d] = t[d] + o;
             }
-            t[d] = (uint32_t)(x | (y << 16));
+            cnt *= (uint64_t)k;
+            sp *= (uint64_t)s;
         }
     };
     // nu tables: (xc + side*yc) -> base-k replica digits, or hole
-    auto nu_table = [&](int levels, std::vector<uint32_t> &t) {
-        const uint64_t side = upow(s, levels);
-        t.resize(side * side);
-        for (uint64_t yc = 0; yc < side; ++yc)
-            for (uint64_t xc = 0; xc < side; ++xc) {
-                uint64_t v = 0, kp = 1, sx = xc, sy = yc;
-                bool hole = false;
-                for (int i = 0; i < levels; ++i) {
-                    const int j = F.hnu[(sx % s) + s * (sy % s)];
-                    sx /= s;
-                    sy /= s;
-                    if (j < 0) {
-                        hole = true;
-                        break;
-                    }
-                    v += (uint64_t)j * kp;
-                    kp *= k;
-                }
-                t[xc + side * yc] = hole ? kNuHole32 : (uint32_t)v;
-            }
-    };
+    auto nu_table = [&](int levels, std::vector<uint32_t> &t) { t = nu_square(F, levels); };
     std::vector<uint32_t> parts[4];
     if (level > 0) {
         lam_table(CL, parts[0]);
@@ -201,38 +200,103 @@ void map_tables(const FractalHost &F, int level, MapParams &P, MapTables &T)
     P.ntab = (uint32_t)T.all.size();
 }
 
-void host_lambda(const FractalHost &F, int level, uint64_t c, int64_t &x, int64_t &y)
+// The side is a compile-time constant in the two patterns' sides: the table
+// builders evaluate these maps by the hundred thousand.
+template <int SC>
+static void lambda_side(const FractalHost &F, int level, uint64_t c, int64_t &x, int64_t &y)
 {
+    const int64_t s = SC ? SC : F.s;
+    const uint32_t k = (uint32_t)F.k;
     int64_t px = 0, py = 0, sp = 1;
-    for (int mu = 1; mu <= level; ++mu) {
-        const int b = (int)(c % (uint64_t)F.k);
-        c /= (uint64_t)F.k;
+    for (int mu = 0; mu < level; ++mu) {
+        const uint64_t q = (c >> 32) ? c / k : (uint32_t)c / k;
+        const uint32_t b = (uint32_t)(c - q * k);
+        c = q;
         px += F.ox[b] * sp;
         py += F.oy[b] * sp;
-        sp *= F.s;
+        sp *= s;
     }
     x = px;
     y = py;
 }
 
-int64_t host_nu(const FractalHost &F, int level, int64_t x, int64_t y)
+template <int SC>
+static int64_t nu_side(const FractalHost &F, int level, int64_t x0, int64_t y0)
 {
+    const uint32_t s = SC ? (uint32_t)SC : (uint32_t)F.s;
     int64_t side = 1;
-    for (int i = 0; i < level; ++i) side *= F.s;
-    if (x < 0 || y < 0 || x >= side || y >= side) return -1;
+    for (int i = 0; i < level; ++i) side *= s;
+    if (x0 < 0 || y0 < 0 || x0 >= side || y0 >= side) return -1;
+    uint32_t x = (uint32_t)x0, y = (uint32_t)y0;  // side < 2^31
     int64_t c = 0, kp = 1;
-    for (int mu = 1; mu <= level; ++mu) {
-        const int j = F.hnu[(int)(x % F.s) + F.s * (int)(y % F.s)];
+    for (int mu = 0; mu < level; ++mu) {
+        const uint32_t qx = x / s, qy = y / s;
+        const int j = F.hnu[x - qx * s + s * (y - qy * s)];
         if (j < 0) return -1;
         c += j * kp;
         kp *= F.k;
-        x /= F.s;
-        y /= F.s;
+        x = qx;
+        y = qy;
     }
     return c;
 }
 
+void host_lambda(const FractalHost &F, int level, uint64_t c, int64_t &x, int64_t &y)
+{
+    if (F.s == 2) return lambda_side<2>(F, level, c, x, y);
+    if (F.s == 3) return lambda_side<3>(F, level, c, x, y);
+    lambda_side<0>(F, level, c, x, y);
+}
+
+int64_t host_nu(const FractalHost &F, int level, int64_t x, int64_t y)
+{
+    if (F.s == 2) return nu_side<2>(F, level, x, y);
+    if (F.s == 3) return nu_side<3>(F, level, x, y);
+    return nu_side<0>(F, level, x, y);
+}
+
 static int64_t floor_div(int64_t a, int64_t b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
+
+typedef std::pair<int64_t, int64_t> Pos;
+
+// Positions outside a level-`level` subtree's box that touch a cell of it and
+// are cells themselves if the adjacent subtree they lie in exists.
+static std::vector<Pos> subtree_ring(const FractalHost &F, int level)
+{
+    const int64_t n = (int64_t)upow(F.s, level);
+    std::vector<Pos> out;
+    auto test = [&](int64_t x, int64_t y) {
+        if (host_nu(F, level, x - floor_div(x, n) * n, y - floor_div(y, n) * n) < 0) return;
+        for (int d = 0; d < 9; ++d)
+            if (host_nu(F, level, x + d % 3 - 1, y + d / 3 - 1) >= 0) {
+                out.emplace_back(x, y);
+                return;
+            }
+    };
+    for (int64_t x = -1; x <= n; ++x) {
+        test(x, -1);
+        test(x, n);
+    }
+    for (int64_t y = 0; y < n; ++y) {
+        test(-1, y);
+        test(n, y);
+    }
+    return out;
+}
+
+// Positions, in boxes of side rs, of the subtrees that hold the cells next to
+// a level-`level` subtree.
+static std::vector<Pos> ring_subtrees(const FractalHost &F, int level, int64_t rs)
+{
+    std::vector<Pos> key;
+    for (const Pos &p : subtree_ring(F, level)) {
+        const Pos q(floor_div(p.first, rs), floor_div(p.second, rs));
+        bool have = false;
+        for (const Pos &e : key) have |= e == q;
+        if (!have) key.push_back(q);
+    }
+    return key;
+}
 
 // ---------------------------------------------------------------------------
 // Bit-sliced tiles
@@ -259,17 +323,10 @@ sqz_status tile_tables(const FractalHost &F, const TileSpec &S, TileTables &T)
         tdy = qy < 0 ? -1 : (qy >= side ? 1 : 0);
         return host_nu(F, M, qx - tdx * side, qy - tdy * side);
     };
-    for (uint64_t c = 0; c < tile; ++c) {
-        int64_t x, y;
-        host_lambda(F, M, c, x, y);
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                const int64_t qx = x + dx, qy = y + dy;
-                if (qx >= 0 && qy >= 0 && qx < side && qy < side) continue;
-                int tdx, tdy;
-                const int64_t j = outside_member(qx, qy, tdx, tdy);
-                if (j >= 0 && find(qx, qy) < 0) ring.push_back(Slot{tdx, tdy, j, qx, qy});
-            }
+    for (const Pos &p : subtree_ring(F, M)) {
+        int tdx, tdy;
+        const int64_t j = outside_member(p.first, p.second, tdx, tdy);
+        ring.push_back(Slot{tdx, tdy, j, p.first, p.second});
     }
     if (ring.size() > (size_t)S.max_tile_halo)
         return set_error(SQZ_ERR_UNSUPPORTED, "tile halo of %zu cells exceeds %d", ring.size(), S.max_tile_halo);
@@ -395,33 +452,6 @@ sqz_status tile_tables(const FractalHost &F, const TileSpec &S, TileTables &T)
 // ---------------------------------------------------------------------------
 // Tiles bit-sliced across subtrees
 // ---------------------------------------------------------------------------
-typedef std::pair<int64_t, int64_t> Pos;
-
-// Positions outside a level-`level` subtree's box that touch a cell of it and
-// are cells themselves if the adjacent subtree they lie in exists.
-static std::vector<Pos> subtree_ring(const FractalHost &F, int level)
-{
-    const int64_t n = (int64_t)upow(F.s, level);
-    std::vector<Pos> out;
-    auto test = [&](int64_t x, int64_t y) {
-        if (host_nu(F, level, x - floor_div(x, n) * n, y - floor_div(y, n) * n) < 0) return;
-        for (int d = 0; d < 9; ++d)
-            if (host_nu(F, level, x + d % 3 - 1, y + d / 3 - 1) >= 0) {
-                out.emplace_back(x, y);
-                return;
-            }
-    };
-    for (int64_t x = -1; x <= n; ++x) {
-        test(x, -1);
-        test(x, n);
-    }
-    for (int64_t y = 0; y < n; ++y) {
-        test(-1, y);
-        test(n, y);
-    }
-    return out;
-}
-
 sqz_status slice_tables(const FractalHost &F, const SliceSpec &S, SliceTables &T)
 {
     const int M = S.M, L = M - S.B;
@@ -437,33 +467,12 @@ sqz_status slice_tables(const FractalHost &F, const SliceSpec &S, SliceTables &T
     const std::vector<Pos> hs = subtree_ring(F, L);
     if (hs.size() > (size_t)S.nh) return set_error(SQZ_ERR_UNSUPPORTED, "subtile halo of %zu cells", hs.size());
 
-    // Ring subtrees: those holding the cells next to the tile; they cover K
-    // steps, K the last distance before a breadth-first walk over member cells
-    // outside the tile enters another subtree.
+    // Ring subtrees: those holding the cells next to the tile
     std::vector<Pos> key;
     if (M < F.r) {
-        std::vector<Pos> cur = subtree_ring(F, M);
-        for (const Pos &p : cur) {
-            const Pos q(floor_div(p.first, rs), floor_div(p.second, rs));
-            if (find(key, q) < 0) key.push_back(q);
-        }
+        key = ring_subtrees(F, M, rs);
         if (key.size() > (size_t)S.max_ring) return set_error(SQZ_ERR_UNSUPPORTED, "%zu ring subtrees", key.size());
-        std::set<Pos> seen(cur.begin(), cur.end());
-        bool other = false;
-        for (T.K = 1; T.K < (uint32_t)rs && !other; ++T.K) {  // cur: the cells at distance K
-            std::vector<Pos> next;
-            for (const Pos &p : cur)
-                for (int d = 0; d < 9; ++d) {
-                    const Pos q(p.first + d % 3 - 1, p.second + d / 3 - 1);
-                    if (q.first >= 0 && q.second >= 0 && q.first < n && q.second < n) continue;
-                    if (host_nu(F, M, q.first - floor_div(q.first, n) * n, q.second - floor_div(q.second, n) * n) < 0) continue;
-                    if (!seen.insert(q).second) continue;
-                    other |= find(key, Pos(floor_div(q.first, rs), floor_div(q.second, rs))) < 0;
-                    next.push_back(q);
-                }
-            if (other) break;
-            cur.swap(next);
-        }
+        T.K = (uint32_t)S.steps;
         T.rwords = (uint32_t)upow(F.k, S.RL);
     }
     T.nring = (uint32_t)key.size();
@@ -570,89 +579,89 @@ sqz_status slice_tables(const FractalHost &F, const SliceSpec &S, SliceTables &T
 void lane_tables(const FractalHost &F, const LaneSpec &S, LaneTables &T)
 {
     const int M = S.M;
-    const int64_t n = (int64_t)upow(F.s, M), bs = (int64_t)upow(F.s, M - S.J), box = (int64_t)upow(F.s, S.J);
+    const int64_t bs = (int64_t)upow(F.s, M - S.J);
     T.cells = upow(F.k, M);
     T.nblk = (uint32_t)upow(F.k, M - S.J);
-    struct Block {
-        Pos at;        // position in blocks of the tile's plane
-        uint32_t src;  // lane_src entry
-    };
-    std::vector<Block> blk;
-    std::set<Pos> have;
+    // lane of every block position of the tile's plane within `edge` blocks of
+    // the tile: lane | tile << 16 (0..7 adjacent, 8 this one), ~0 if none
+    const int64_t rb = S.frame ? S.frame : (int64_t)upow(F.s, S.RL - S.J), edge = M < F.r ? rb : 1, W = bs + 2 * edge;
+    std::vector<uint32_t> grid((size_t)(W * W), ~0u);
+    std::vector<Pos> pos;
+    auto at = [&](int64_t x, int64_t y) -> uint32_t & { return grid[(size_t)((y + edge) * W + x + edge)]; };
     for (uint32_t b = 0; b < T.nblk; ++b) {
         int64_t x, y;
         host_lambda(F, M - S.J, b, x, y);
-        blk.push_back({Pos(x, y), 8u << 28 | b});
-        have.insert(Pos(x, y));
+        at(x, y) = b | 8u << 16;
+        pos.emplace_back(x, y);
     }
     auto add_ring = [&](int64_t x, int64_t y) {
         const int64_t tx = floor_div(x, bs), ty = floor_div(y, bs);
         const int64_t b = host_nu(F, M - S.J, x - tx * bs, y - ty * bs);
-        if (b < 0 || !have.insert(Pos(x, y)).second) return;
+        if (b < 0) return;
         const int d = (int)((ty + 1) * 3 + (tx + 1));
-        blk.push_back({Pos(x, y), (uint32_t)(d < 4 ? d : d - 1) << 28 | (uint32_t)b});
+        const uint32_t d8 = (uint32_t)(d < 4 ? d : d - 1);
+        at(x, y) = (uint32_t)pos.size() | d8 << 16;
+        pos.emplace_back(x, y);
+        T.lane_src.push_back(d8 << 28 | (uint32_t)b);
     };
     if (M < F.r && S.frame) {
-        for (int64_t y = -S.frame; y < bs + S.frame; ++y)
-            for (int64_t x = -S.frame; x < bs + S.frame; ++x)
+        for (int64_t y = -edge; y < bs + edge; ++y)
+            for (int64_t x = -edge; x < bs + edge; ++x)
                 if (x < 0 || y < 0 || x >= bs || y >= bs) add_ring(x, y);
     } else if (M < F.r) {
-        std::vector<Pos> cur = subtree_ring(F, M);
-        std::set<Pos> seen(cur.begin(), cur.end());
-        for (int d = 1;; ++d) {  // cur: the cells at distance d
-            for (const Pos &p : cur) add_ring(floor_div(p.first, box), floor_div(p.second, box));
-            if (d == S.steps) break;
-            std::vector<Pos> next;
-            for (const Pos &p : cur)
-                for (int e = 0; e < 9; ++e) {
-                    const Pos q(p.first + e % 3 - 1, p.second + e / 3 - 1);
-                    if (q.first >= 0 && q.second >= 0 && q.first < n && q.second < n) continue;
-                    if (host_nu(F, M, q.first - floor_div(q.first, n) * n, q.second - floor_div(q.second, n) * n) < 0) continue;
-                    if (seen.insert(q).second) next.push_back(q);
-                }
-            cur.swap(next);
-        }
+        for (const Pos &q : ring_subtrees(F, M, (int64_t)upow(F.s, S.RL)))
+            for (uint32_t b = 0; b < upow(F.k, S.RL - S.J); ++b) {
+                int64_t x, y;
+                host_lambda(F, S.RL - S.J, b, x, y);
+                add_ring(q.first * rb + x, q.second * rb + y);
+            }
     }
     if (M < F.r) T.K = S.steps;
-    std::map<Pos, uint32_t> lane;
-    for (const Block &b : blk) {
-        const uint32_t l = (uint32_t)lane.size();
-        lane[b.at] = l | (b.src >> 28) << 16;
-        if (l >= T.nblk) T.lane_src.push_back(b.src);
-    }
-    T.lanes = (uint32_t)blk.size();
-    for (const Block &b : blk)
+    T.lanes = (uint32_t)pos.size();
+    T.lane_nb.reserve((size_t)T.lanes * S.ng);
+    for (const Pos &p : pos)
         for (int g = 0; g < S.ng; ++g) {
-            const auto it = lane.find(Pos(b.at.first + S.g_dx[g], b.at.second + S.g_dy[g]));
-            T.lane_nb.push_back(it == lane.end() ? ~0u : it->second);
+            const int64_t x = p.first + S.g_dx[g], y = p.second + S.g_dy[g];
+            T.lane_nb.push_back(x < -edge || y < -edge || x >= bs + edge || y >= bs + edge ? ~0u : at(x, y));
         }
 }
 
 // ---------------------------------------------------------------------------
 // Expanded tiles
 // ---------------------------------------------------------------------------
+// Adjacent tile (0..8, 4: this one) of a position of the tile's plane, and the
+// cell of that tile's box there (kNuHole32: none, or beyond the adjacent tiles).
+static int tile_cell(const std::vector<uint32_t> &nu, int64_t side, int64_t x, int64_t y, uint32_t &cell)
+{
+    const int tdx = x < 0 ? -1 : (x >= side ? 1 : 0), tdy = y < 0 ? -1 : (y >= side ? 1 : 0);
+    const int64_t bx = x - tdx * side, by = y - tdy * side;
+    cell = bx < 0 || by < 0 || bx >= side || by >= side ? kNuHole32 : nu[(size_t)(bx + side * by)];
+    return (tdy + 1) * 3 + (tdx + 1);
+}
+
+static uint32_t dir8(int d) { return (uint32_t)(d < 4 ? d : d - 1); }
+
 void xtile_ring_slots(const FractalHost &F, int M, uint32_t P, std::vector<XRingSlot> &out)
 {
     const int64_t side = (int64_t)upow(F.s, M);
     const uint64_t KM = upow(F.k, M);
+    const std::vector<uint32_t> nu = nu_square(F, M);
     std::vector<uint8_t> seen((size_t)P * P, 0);
     out.clear();
     for (uint64_t c = 0; c < KM; ++c) {
         int64_t x, y;
         host_lambda(F, M, c, x, y);
+        if (x > 0 && y > 0 && x < side - 1 && y < side - 1) continue;
         for (int dy = -1; dy <= 1; ++dy)
             for (int dx = -1; dx <= 1; ++dx) {
                 const int64_t qx = x + dx, qy = y + dy;
-                if (qx >= 0 && qy >= 0 && qx < side && qy < side) continue;
-                const int tdx = qx < 0 ? -1 : (qx >= side ? 1 : 0), tdy = qy < 0 ? -1 : (qy >= side ? 1 : 0);
-                const int64_t j = host_nu(F, M, qx - tdx * side, qy - tdy * side);
-                if (j < 0) continue;
+                uint32_t j;
+                const int d = tile_cell(nu, side, qx, qy, j);
+                if (d == 4 || j == kNuHole32) continue;
                 const uint32_t pos = (uint32_t)((qy + 1) * P + (qx + 1));
                 if (seen[pos]) continue;
                 seen[pos] = 1;
-                const int d = (tdy + 1) * 3 + (tdx + 1);
-                const uint32_t d8 = (uint32_t)(d < 4 ? d : d - 1);
-                out.push_back(XRingSlot{(uint16_t)pos, (d8 << 16) | (uint32_t)j});
+                out.push_back(XRingSlot{(uint16_t)pos, (dir8(d) << 16) | j});
             }
     }
 }
@@ -662,33 +671,27 @@ void xtile_cell_entries(const FractalHost &F, int M, uint32_t P, const int field
 {
     const int64_t side = (int64_t)upow(F.s, M);
     const uint64_t KM = upow(F.k, M);
+    const std::vector<uint32_t> nu = nu_square(F, M);
     lam.assign(KM, 0);
     ent.assign(KM, 0);
-    for (uint64_t c = 0; c < KM; ++c) {
-        int64_t x, y;
-        host_lambda(F, M, c, x, y);
-        lam[c] = (uint16_t)((y + 1) * P + (x + 1));
-        // member neighbours inside the tile, and per adjacent tile the member
-        // cells of that tile (its own copy of the level-M pattern) it touches
-        uint32_t inner = 0, cnt[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-        for (int dy = -1; dy <= 1; ++dy)
-            for (int dx = -1; dx <= 1; ++dx) {
-                if (dx == 0 && dy == 0) continue;
-                const int64_t qx = x + dx, qy = y + dy;
-                const int tdx = qx < 0 ? -1 : (qx >= side ? 1 : 0), tdy = qy < 0 ? -1 : (qy >= side ? 1 : 0);
-                const bool member = host_nu(F, M, qx - tdx * side, qy - tdy * side) >= 0;
-                if (!member) continue;
-                if (tdx == 0 && tdy == 0) {
-                    ++inner;
-                } else {
-                    const int d = (tdy + 1) * 3 + (tdx + 1);
-                    ++cnt[d < 4 ? d : d - 1];
-                }
+    for (int64_t y = 0; y < side; ++y)
+        for (int64_t x = 0; x < side; ++x) {
+            const uint32_t c = nu[(size_t)(x + side * y)];
+            if (c == kNuHole32) continue;
+            lam[c] = (uint16_t)((y + 1) * P + (x + 1));
+            // member neighbours inside the tile, and per adjacent tile the member
+            // cells of that tile (its own copy of the level-M pattern) it touches
+            uint32_t cnt[9] = {0, 0, 0, 0, 0, 0, 0, 0, 0}, q;
+            for (int n = 0; n < 9; ++n) {
+                if (n == 4) continue;
+                const int d = tile_cell(nu, side, x + n % 3 - 1, y + n / 3 - 1, q);
+                cnt[d] += q != kNuHole32;
             }
-        uint32_t e = lam[c] | inner << 16;
-        for (int d8 = 0; d8 < 8; ++d8) e |= cnt[d8] << field_shift[d8];  // sides <= 3, corners <= 1
-        ent[c] = e;
-    }
+            uint32_t e = lam[c] | cnt[4] << 16;
+            for (int d = 0; d < 9; ++d)
+                if (d != 4) e |= cnt[d] << field_shift[dir8(d)];  // sides <= 3, corners <= 1
+            ent[c] = e;
+        }
 }
 
 void xtile_layer_tables(const FractalHost &F, int M, int K, uint32_t P, uint32_t rows,
@@ -697,33 +700,32 @@ void xtile_layer_tables(const FractalHost &F, int M, int K, uint32_t P, uint32_t
 {
     const int64_t B = (int64_t)upow(F.s, M);
     const uint64_t KM = upow(F.k, M);
+    const std::vector<uint32_t> nu = nu_square(F, M);
     ring.clear();
     start.assign(1, 0);
     // ring slots by layer: member cells of the adjacent tiles within K of the box
-    for (int d = 1; d <= K; ++d) {
-        for (int64_t qy = -K; qy < B + K; ++qy)
-            for (int64_t qx = -K; qx < B + K; ++qx) {
-                const int64_t ex = qx < 0 ? -qx : (qx >= B ? qx - B + 1 : 0);
-                const int64_t ey = qy < 0 ? -qy : (qy >= B ? qy - B + 1 : 0);
-                if ((ex > ey ? ex : ey) != d) continue;
-                const int tdx = qx < 0 ? -1 : (qx >= B ? 1 : 0), tdy = qy < 0 ? -1 : (qy >= B ? 1 : 0);
-                const int64_t j = host_nu(F, M, qx - tdx * B, qy - tdy * B);
-                if (j < 0) continue;
-                const int dd = (tdy + 1) * 3 + (tdx + 1);
-                const uint32_t d8 = (uint32_t)(dd < 4 ? dd : dd - 1);
-                ring.push_back(XRingSlot{(uint16_t)((qy + K) * P + (qx + K)), (d8 << 16) | (uint32_t)j});
+    for (int64_t d = 1; d <= K; ++d) {
+        for (int64_t qy = -d; qy < B + d; ++qy) {
+            const bool whole = qy == -d || qy == B + d - 1;  // a whole row of the layer, or its two ends
+            for (int64_t qx = -d; qx < B + d; qx += whole ? 1 : B + 2 * d - 1) {
+                uint32_t j;
+                const int dd = tile_cell(nu, B, qx, qy, j);
+                if (j == kNuHole32) continue;
+                ring.push_back(XRingSlot{(uint16_t)((qy + K) * P + (qx + K)), (dir8(dd) << 16) | j});
             }
+        }
         start.push_back((uint32_t)ring.size());
     }
     // box positions of the tile's cells and their membership
     lam.assign(KM, 0);
     mem.assign((size_t)P * rows, 0);
-    for (uint64_t c = 0; c < KM; ++c) {
-        int64_t x, y;
-        host_lambda(F, M, c, x, y);
-        lam[c] = (uint16_t)((y + K) * P + (x + K));
-        mem[lam[c]] = 1;
-    }
+    for (int64_t y = 0; y < B; ++y)
+        for (int64_t x = 0; x < B; ++x) {
+            const uint32_t c = nu[(size_t)(x + B * y)];
+            if (c == kNuHole32) continue;
+            lam[c] = (uint16_t)((y + K) * P + (x + K));
+            mem[lam[c]] = 1;
+        }
 }
 
 // ---------------------------------------------------------------------------

@@ -165,6 +165,7 @@ sqz_status tile_tables(const FractalHost &F, const TileSpec &S, TileTables &T);
 // ---------------------------------------------------------------------------
 struct SliceSpec {
     int M, B, J, RL;
+    int steps;                    // steps the ring subtrees cover (see below)
     int nc, box;                  // words and side of a block
     int nh;                       // halo slots of a block: cell h_idx of the block in direction (h_dx, h_dy)
     int h_dx[16], h_dy[16], h_idx[16], h_exp[16];
@@ -192,8 +193,9 @@ sqz_status slice_tables(const FractalHost &F, const SliceSpec &S, SliceTables &T
 struct LaneSpec {
     int M, J;
     int ng, g_dx[8], g_dy[8];  // adjacent blocks a block's halo reads
-    int steps;                 // steps the ring blocks have to cover
-    int frame;                 // ring: the frame of that many blocks around the tile (covers as many cells); 0: by search
+    int frame;                 // ring: the frame of that many blocks around the tile (covers as many cells)
+    int RL;                    // frame 0: the level-RL subtrees that hold the cells next to the tile
+    int steps;                 // steps the ring blocks cover
 };
 
 struct LaneTables {

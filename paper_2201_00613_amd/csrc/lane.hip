@@ -104,6 +104,7 @@ sqz_status lane_prepare(FractalHost &F)
             S.g_dy[g] = PO::value.g_dy[g];
         }
         S.steps = P::STEPS;
+        S.RL = P::RL;
         S.frame = P::FRAME;
         most = P::LANES - 1;
         return 0;

@@ -173,22 +173,23 @@ struct LanePlanOf {
 // Patterns: block level J, largest tile level MMAX, lanes (a multiple of 64,
 // more than tile and ring need: the last lane's LDS column stays zero).
 // FRAME blocks: the ring is the frame of that many blocks around the tile
-// (dense patterns: STEPS is the frame's width in cells); 0: the blocks within
-// STEPS steps by breadth-first search.
+// (dense patterns: STEPS is the frame's width in cells); 0: the level-RL
+// subtrees that hold the cells next to the tile, which cover STEPS steps
+// (their side, one less for the triangles).
 struct LaneTriangle : PatTriangle {
-    static constexpr int J = 2, MMAX = 8, LANES = 832, STEPS = 15, FRAME = 0;
+    static constexpr int J = 2, MMAX = 8, LANES = 832, RL = 4, STEPS = 15, FRAME = 0;
 };
 struct LaneTrianglePaper : PatTrianglePaper {
-    static constexpr int J = 2, MMAX = 8, LANES = 832, STEPS = 15, FRAME = 0;
+    static constexpr int J = 2, MMAX = 8, LANES = 832, RL = 4, STEPS = 15, FRAME = 0;
 };
 struct LaneVicsek : PatVicsek {
-    static constexpr int J = 2, MMAX = 6, LANES = 704, STEPS = 27, FRAME = 0;
+    static constexpr int J = 2, MMAX = 6, LANES = 704, RL = 3, STEPS = 27, FRAME = 0;
 };
 struct LaneCarpet : PatCarpet {
-    static constexpr int J = 2, MMAX = 5, LANES = 768, STEPS = 18, FRAME = 2;
+    static constexpr int J = 2, MMAX = 5, LANES = 768, RL = 0, STEPS = 18, FRAME = 2;
 };
 struct LaneCarpetSmall : PatCarpet {
-    static constexpr int J = 2, MMAX = 4, LANES = 192, STEPS = 18, FRAME = 2;
+    static constexpr int J = 2, MMAX = 4, LANES = 192, RL = 0, STEPS = 18, FRAME = 2;
 };
 
 // Storage types: G in memory, binary32 in registers.

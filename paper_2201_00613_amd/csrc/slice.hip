@@ -94,6 +94,7 @@ SliceSpec slice_spec(int M)
     S.B = P::B;
     S.J = J;
     S.RL = P::RL;
+    S.steps = P::STEPS;
     S.nc = PL.nc;
     S.box = PL.box;
     S.nh = PL.nh;
@@ -259,7 +260,7 @@ sqz_status slice_batch_config(const FractalHost &F, SliceConfig **out, bool *own
 void slice_prepare_resident(FractalHost &F)
 {
     SliceConfig *S = F.slice;
-    if (!S || !tile_resident(F)) return;
+    if (!S || !tile_few(F)) return;
     const unsigned nt = slice_threads(*S);
     int per_cu = 0, cus = 0;
     int nc = 0;

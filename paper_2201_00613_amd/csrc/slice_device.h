@@ -44,11 +44,15 @@
 namespace sqz {
 
 // Bit level B (k^B subtiles per tile), ring level RL, block level J and largest
-// subtile level LMAX of a kernel.  *Small: subtiles of at most 243 (625) words,
+// subtile level LMAX of a kernel.  STEPS: steps the ring subtrees cover, that
+// is, the distance (along member cells outside the tile) up to which every cell
+// lies in the level-RL subtrees that hold the cells next to the tile: one step
+// less than their side for the triangles, whose next subtrees touch at a
+// corner, their side for the Vicsek cross.  *Small: subtiles of at most 243 (625) words,
 // always loaded four cells a lane (fewer registers and less LDS, so more
 // workgroups per CU: batches).
 struct SliceTri : PatTriangle {
-    static constexpr int B = 3, RL = 5, J = 2, LMAX = 8;
+    static constexpr int B = 3, RL = 5, STEPS = 31, J = 2, LMAX = 8;
     static constexpr bool SMALL = false;
 };
 struct SliceTriSmall : SliceTri {
@@ -59,7 +63,7 @@ struct SliceTriWide : SliceTri {
     static constexpr int J = 3;
 };
 struct SlicePaper : PatTrianglePaper {
-    static constexpr int B = 3, RL = 5, J = 2, LMAX = 8;
+    static constexpr int B = 3, RL = 5, STEPS = 31, J = 2, LMAX = 8;
     static constexpr bool SMALL = false;
 };
 struct SlicePaperSmall : SlicePaper {
@@ -70,7 +74,7 @@ struct SlicePaperWide : SlicePaper {
     static constexpr int J = 3;
 };
 struct SliceVicsek : PatVicsek {
-    static constexpr int B = 2, RL = 3, J = 1, LMAX = 5;
+    static constexpr int B = 2, RL = 3, STEPS = 27, J = 1, LMAX = 5;
     static constexpr bool SMALL = false;
 };
 struct SliceVicsekSmall : SliceVicsek {

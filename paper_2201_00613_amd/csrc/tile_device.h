@@ -44,23 +44,10 @@ namespace sqz {
 #ifndef SQZ_TRI_TILE_BIG_FROM  // fractal level from which triangle tiles use SQZ_TRI_TILE_LEVEL (else 8)
 #define SQZ_TRI_TILE_BIG_FROM 16
 #endif
-#ifndef SQZ_SPLIT_EXCHANGE  // 1: the resident run updates interior blocks while its exchange barrier completes
-#define SQZ_SPLIT_EXCHANGE 1
-#endif
-#ifndef SQZ_NT_LOAD
-#define SQZ_NT_LOAD 0
-#endif
-#ifndef SQZ_NT_STORE  // 1: nontemporal stores in every tiled kernel, 0: in the multi-step kernels only
-#define SQZ_NT_STORE 0
-#endif
-
 // Tile level M: MMAX for fractals of level >= MBIG, else MSMALL (more,
-// smaller tiles keep a smaller fractal's launch balanced; from level 16 the
-// larger triangle tile is faster with several steps per launch).  Large
-// triangles are their own pattern type, with level-10 tiles and 512-lane
-// workgroups (all of a level-16 triangle's 729 tiles resident at once), so
-// that the kernels for smaller triangles (and the batch) keep LDS sized for
-// level-8 tiles.
+// smaller tiles keep a smaller fractal's launch balanced).  Large triangles
+// are their own pattern type, with level-10 tiles and 512-lane workgroups, so
+// that the kernel for smaller triangles keeps LDS sized for level-8 tiles.
 struct PatTriangle {  // Sierpinski triangle, member iff x & y == 0
     static constexpr int S = 2, K = 3, J = 3, MMAX = 8, MSMALL = 8, MBIG = 0;
     static constexpr int OX[3] = {0, 1, 0};
@@ -90,10 +77,8 @@ constexpr int cpow(int b, int e)
 }
 
 constexpr int kMaxHalo = 16;      // halo cells per block
-constexpr int kMaxSteps = 10;     // Life steps per launch of the multi-step tiled kernel
+constexpr int kMaxSteps = 10;     // Life steps per launch reported for bit-sliced tiles (runs take more: slice_device.h)
 constexpr int kMaxTileHalo = 32;  // halo cells per tile (one LDS word of bits)
-constexpr int kMaxRing = 256;     // ring cells of all rings (one lane each)
-constexpr int kRingTab = kMaxRing * 9;  // LDS words of a tile's ring tables: 8 sources per cell, then homes
 constexpr int kBlock = 256;
 
 // ---------------------------------------------------------------------------
@@ -341,33 +326,20 @@ struct TileConfig {
     uint32_t tile;         // K^M cells per tile
     uint32_t nblocks;      // K^(M-J)
     uint32_t nthalo;       // tile halo slots (ring 1: cells of other tiles adjacent to the tile)
-    uint32_t ksteps;       // Life steps one launch of the multi-step kernel can take (1: none)
-    uint32_t ring_start[kMaxSteps + 1];  // slots of ring d are [ring_start[d-1], ring_start[d])
-    uint32_t nsrc;         // ring cells whose next states are computed: ring_start[ksteps - 1]
-    uint32_t tstride;      // per-tile entries of d_tile_halo: ring_start[ksteps]
     uint32_t nbstride;     // u32 entries per block in d_nbtab (multiple of 4)
     uint64_t ntiles;       // K^(r-M)
     uint32_t *d_nbtab;     // [nblocks][nbstride] LDS byte offsets (16-bit pairs) of each block's adjacent-block words
-    uint64_t *d_tile_halo; // [ntiles][tstride] global indices of the ring cells
-    uint32_t *d_ringsrc;   // [nsrc][8] LDS sources of each advanced ring cell's neighbours
-    uint32_t *d_ringhome;  // [tstride] LDS word and bit of each ring cell
+    uint64_t *d_tile_halo; // [ntiles][nthalo] global indices of the ring cells
+    uint32_t *d_ringhome;  // [nthalo] LDS word and bit of each ring cell
     MapParams Pc;          // maps at the coarse level r-M
     void *d_coarse_tables;
-    // resident run (all tiles on the chip at once), null / 0 when unavailable
-    uint32_t nbound;       // boundary cells per tile (exported at every exchange)
-    uint32_t lds_pad;      // LDS bytes reserved per workgroup so that at most ceil(tiles / CUs) share a CU
-    uint32_t *d_bound;     // [nbound] their tile-local indices
-    uint32_t *d_bar;       // {arrivals, timed out} of the grid barrier
-    uint32_t *h_flag;      // pinned host word: a barrier wait of an earlier run timed out
 };
 
 struct TileArgs {
     uint64_t ntiles, N;
-    uint32_t tile, nblocks, nthalo, tstride, nsrc, nbstride;
-    uint32_t ring_start[kMaxSteps + 1];
+    uint32_t tile, nblocks, nthalo, nbstride;
     const uint32_t *nbtab;
     const uint64_t *tile_halo;
-    const uint32_t *ringsrc;
     const uint32_t *ringhome;
 };
 
@@ -380,13 +352,9 @@ inline TileArgs tile_args(const FractalHost &F)
     A.tile = T->tile;
     A.nblocks = T->nblocks;
     A.nthalo = T->nthalo;
-    A.tstride = T->tstride;
-    A.nsrc = T->nsrc;
     A.nbstride = T->nbstride;
-    for (int d = 0; d <= kMaxSteps; ++d) A.ring_start[d] = T->ring_start[d];
     A.nbtab = T->d_nbtab;
     A.tile_halo = T->d_tile_halo;
-    A.ringsrc = T->d_ringsrc;
     A.ringhome = T->d_ringhome;
     return A;
 }
@@ -394,12 +362,9 @@ inline TileArgs tile_args(const FractalHost &F)
 // LDS words of one tile's state, one word per level-J block (bit i = cell i
 // of the block, bits from K^J up zero): blocks [0, NBMAX), two words that
 // stay zero (absent neighbours), one word per adjacent block of another tile
-// that holds ring-1 cells (each at its bit within that block), then the bits
-// of rings 2..kMaxSteps, packed in ring order.  Ring d holds the cells of other
-// tiles at graph distance d from the tile (each neighbour of a ring-d cell is
-// in ring d-1, d or d+1, or in the tile for d = 1).  The layout does not
-// depend on where the tile starts within a 32-byte word, so every table that
-// addresses it is the same for all tiles.  The tile's bytes are first packed
+// that holds ring cells (each at its bit within that block).  The layout does
+// not depend on where the tile starts within a 32-byte word, so every table
+// that addresses it is the same for all tiles.  The tile's bytes are first packed
 // to bits at their 32-byte alignment in the low words of another buffer
 // (STAGE words) and then cut into block words.
 template <class Pat>
@@ -409,8 +374,7 @@ struct TileLds {
     static constexpr int NBMAX = TMAX / NC;
     static constexpr int ZERO = NBMAX;
     static constexpr int VIRT = ZERO + 2;
-    static constexpr int RING2 = VIRT + kMaxTileHalo;
-    static constexpr int WORDS = RING2 + (kMaxRing + 31) / 32;
+    static constexpr int WORDS = VIRT + kMaxTileHalo;
     static constexpr int STAGE = (TMAX + 31 + 31) / 32 + 1;
     static constexpr int NGRP = PlanOf<Pat>::value.ngrp > 0 ? PlanOf<Pat>::value.ngrp : 1;
     static_assert(STAGE <= NBMAX, "packed tile overlaps the special words");
@@ -418,11 +382,6 @@ struct TileLds {
 };
 
 // LDS entry: byte offset of a word within a buffer << 16 | bit.
-__device__ __forceinline__ uint32_t lds_bit(const uint32_t *base, uint32_t e)
-{
-    return __builtin_amdgcn_ubfe(*reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(base) + (e >> 16)),
-                                 e, 1);
-}
 __device__ __forceinline__ uint32_t *lds_word(uint32_t *base, uint32_t e)
 {
     return reinterpret_cast<uint32_t *>(reinterpret_cast<char *>(base) + (e >> 16));
@@ -434,28 +393,6 @@ __device__ __forceinline__ uint32_t pack8(uint32_t d0, uint32_t d1)
     return __builtin_amdgcn_udot4(d1, 0x80402010u, __builtin_amdgcn_udot4(d0, 0x08040201u, 0u, false), false);
 }
 __device__ __forceinline__ uint32_t spread4(uint32_t v) { return __umul24(v, 0x204081u) & 0x01010101u; }
-
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ uint4 load16(const uint8_t *p)
-{
-#if SQZ_NT_LOAD
-    const u32x4 v = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(p));
-    return make_uint4(v.x, v.y, v.z, v.w);
-#else
-    return *reinterpret_cast<const uint4 *>(p);
-#endif
-}
-template <bool NTS>
-__device__ __forceinline__ void store16(uint8_t *p, uint4 v)
-{
-    if constexpr (NTS || SQZ_NT_STORE) {
-        u32x4 w = {v.x, v.y, v.z, v.w};
-        __builtin_nontemporal_store(w, reinterpret_cast<u32x4 *>(p));
-    } else {
-        *reinterpret_cast<uint4 *>(p) = v;
-    }
-}
 
 // (a << S) | c as one instruction.  Written out because the compiler
 // rewrites ((a & m) << s) | c into a shift, an AND with the shifted mask and
@@ -570,42 +507,6 @@ struct NbRegs {
     }
 };
 
-#ifndef SQZ_RES_STATIC  // 1: resident rounds read LDS at fixed buffer addresses through unpacked offsets
-#define SQZ_RES_STATIC 1
-#endif
-#ifndef SQZ_RES_UNPACK  // slots whose offsets the resident rounds hold unpacked (the rest stay packed)
-#define SQZ_RES_UNPACK 3
-#endif
-// The same offsets, those of the first SQZ_RES_UNPACK slots one per register
-// (the rest packed as in NbRegs): with the state buffer at a fixed LDS
-// address, a neighbour word of an unpacked slot is read with its offset
-// register as the address and the buffer in the instruction's offset field,
-// without the add that unpacks and rebases a packed offset.
-template <class Pat, int NT>
-struct NbOffs {
-    static constexpr int NSLOT = NbRegs<Pat, NT>::NSLOT;
-    static constexpr int NU = SQZ_RES_UNPACK < NSLOT ? SQZ_RES_UNPACK : NSLOT;  // slots held unpacked
-    static constexpr int NP = NbRegs<Pat, NT>::NP;
-    uint32_t o[NU > 0 ? NU : 1][TileLds<Pat>::NGRP];
-    uint32_t p[NSLOT - NU > 0 ? NSLOT - NU : 1][NP];
-    __device__ __forceinline__ uint32_t at(int s, int g) const
-    {
-        if (s < NU) return o[s][g];
-        return g & 1 ? p[s - NU][g >> 1] >> 16 : p[s - NU][g >> 1] & 0xFFFFu;
-    }
-    __device__ __forceinline__ void keep_packed()
-    {
-#pragma unroll
-        for (int s = 0; s < NU; ++s)
-#pragma unroll
-            for (int g = 0; g < TileLds<Pat>::NGRP; ++g) asm volatile("" : "+v"(o[s][g]));
-#pragma unroll
-        for (int s = 0; s < NSLOT - NU; ++s)
-#pragma unroll
-            for (int q = 0; q < NP; ++q) asm volatile("" : "+v"(p[s][q]));
-    }
-};
-
 template <class Pat, int NT>
 __device__ __forceinline__ void load_nb(const TileArgs &A, NbRegs<Pat, NT> &R)
 {
@@ -626,14 +527,8 @@ __device__ __forceinline__ void load_nb(const TileArgs &A, NbRegs<Pat, NT> &R)
 
 // Phase C: one lane per level-J block.  Reads the block's word and the words
 // of its adjacent blocks from `src`, writes the block's new word to `dst`.
-// Full: the tile has all TileLds<Pat>::NBMAX blocks (its level is the pattern's
-// largest), so every slot but the last is whole and runs without a branch,
-// which lets the compiler overlap one slot's LDS reads with another's logic.
-// sel (not Full): bit s set = update the blocks of slot s (the same for every
-// lane of a wave).
-template <class Pat, int NT, bool Full = false, class Regs = NbRegs<Pat, NT>>
-__device__ __forceinline__ void tile_blocks(const TileArgs &A, Regs &R, const uint32_t *src, uint32_t *dst,
-                                            uint32_t sel = ~0u)
+template <class Pat, int NT>
+__device__ __forceinline__ void tile_blocks(const TileArgs &A, NbRegs<Pat, NT> &R, const uint32_t *src, uint32_t *dst)
 {
     R.keep_packed();
     using LDS = TileLds<Pat>;
@@ -651,47 +546,16 @@ __device__ __forceinline__ void tile_blocks(const TileArgs &A, Regs &R, const ui
         apply_halo<Pat, NL, NG>(w, L, std::make_index_sequence<PL.nhterm>{});
         return life_rule<NL>(x, L) & CELLS;
     };
-    if constexpr (Full) {
-        // software pipeline: the words of slot s + 1 are read before slot s is
-        // updated and stored (lanes past the last block read block 0's words)
-        uint32_t xc, wc[NG];
-        {
-            const uint32_t b = (NT <= LDS::NBMAX || threadIdx.x < A.nblocks) ? threadIdx.x : 0u;
-            xc = src[b];
 #pragma unroll
-            for (int g = 0; g < NG; ++g)
-                wc[g] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(src) + R.at(0, g));
-        }
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const uint32_t b = threadIdx.x + s * NT;
-            const uint32_t x = xc;
+    for (int s = 0; s < NS; ++s) {
+        const uint32_t b = threadIdx.x + s * NT;
+        if (b < A.nblocks) {
+            const uint32_t x = src[b];
             uint32_t w[NG];
 #pragma unroll
-            for (int g = 0; g < NG; ++g) w[g] = wc[g];
-            if (s + 1 < NS) {
-                const uint32_t bn = threadIdx.x + (s + 1) * NT;
-                xc = src[((s + 2) * NT <= LDS::NBMAX || bn < A.nblocks) ? bn : 0u];
-#pragma unroll
-                for (int g = 0; g < NG; ++g)
-                    wc[g] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(src) +
-                                                                R.at(s + 1 < NS ? s + 1 : s, g));
-            }
-            const uint32_t v = update(x, w);
-            if ((s + 1) * NT <= LDS::NBMAX || b < A.nblocks) dst[b] = v;
-        }
-    } else {
-#pragma unroll
-        for (int s = 0; s < NS; ++s) {
-            const uint32_t b = threadIdx.x + s * NT;
-            if (((sel >> s) & 1u) && b < A.nblocks) {  // sel: the slots to update (uniform per wave)
-                const uint32_t x = src[b];
-                uint32_t w[NG];
-#pragma unroll
-                for (int g = 0; g < NG; ++g)
-                    w[g] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(src) + R.at(s, g));
-                dst[b] = update(x, w);
-            }
+            for (int g = 0; g < NG; ++g)
+                w[g] = *reinterpret_cast<const uint32_t *>(reinterpret_cast<const char *>(src) + R.at(s, g));
+            dst[b] = update(x, w);
         }
     }
 }
@@ -707,8 +571,8 @@ __device__ __forceinline__ void tile_pack(const TileArgs &A, const uint8_t *__re
         const uint64_t g = A0 + 32ull * w;
         uint32_t bits = 0;
         if (g + 32 <= A.N) {
-            const uint4 a = load16(in + g);
-            const uint4 b = load16(in + g + 16);
+            const uint4 a = *reinterpret_cast<const uint4 *>(in + g);
+            const uint4 b = *reinterpret_cast<const uint4 *>(in + g + 16);
             bits = pack8(a.x, a.y) | pack8(a.z, a.w) << 8 | pack8(b.x, b.y) << 16 | pack8(b.z, b.w) << 24;
         } else {
             for (uint32_t i = 0; i < 32; ++i)
@@ -733,10 +597,10 @@ __device__ __forceinline__ void tile_convert(const TileArgs &A, uint32_t o, cons
 }
 
 // Phase D: join block words back into 32-cell words, unpack and store whole
-// 32-byte words (NTS: nontemporal); the (at most two) edge words of the tile
+// 32-byte words; the (at most two) edge words of the tile
 // go out byte by byte, one byte per lane of wave 0.  A whole word reads at most the blocks
 // b0 .. b0+2 <= nblocks + 1; bits of blocks past the tile fall beyond bit 31.
-template <class Pat, int NT, bool NTS = false>
+template <class Pat, int NT>
 __device__ __forceinline__ void tile_store(const TileArgs &A, uint8_t *__restrict__ out, uint64_t A0, uint32_t o,
                                            uint32_t W, const uint32_t *blk)
 {
@@ -759,8 +623,8 @@ __device__ __forceinline__ void tile_store(const TileArgs &A, uint8_t *__restric
             b.y = spread4((v >> 20) & 15);
             b.z = spread4((v >> 24) & 15);
             b.w = spread4(v >> 28);
-            store16<NTS>(out + g, a);
-            store16<NTS>(out + g + 16, b);
+            *reinterpret_cast<uint4 *>(out + g) = a;
+            *reinterpret_cast<uint4 *>(out + g + 16) = b;
         }
     }
     if (tid < 64) {
@@ -791,7 +655,7 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, const uint8_t *__re
     uint64_t gi = kHole64;
     uint32_t home = 0;
     if (tid < A.nthalo) {
-        gi = A.tile_halo[t * A.tstride + tid];
+        gi = A.tile_halo[t * A.nthalo + tid];
         home = A.ringhome[tid];
     }
     NbRegs<Pat, NT> R;
@@ -811,384 +675,9 @@ __device__ __forceinline__ void tile_body(const TileArgs &A, const uint8_t *__re
     __syncthreads();  // LDS is reused by the next tile
 }
 
-// One tile, K steps (temporal blocking).  The states of the ring cells are
-// loaded with the tile, one lane per ring cell; in round j (computing t+j)
-// the tile's blocks and the cells of rings 1..K-j are advanced together, ring
-// cell c by lane c, which reads its eight neighbours at t+j-1 (tile bits or
-// ring bits, through the tile-invariant source table, copied to LDS with the
-// tile).  A ring cell whose tile does not exist stays zero.  Three LDS
-// buffers rotate: round j reads buf[(j-1)%3], writes buf[j%3] and clears the
-// ring words of buf[(j+1)%3]; buf[2] first holds the packed bytes.  s_ring:
-// kRingTab words, 16-byte aligned.
-template <class Pat, int K, int NT = kBlock, bool Full = false>
-__device__ __forceinline__ void tile_bodyK(const TileArgs &A, const uint8_t *__restrict__ in,
-                                           uint8_t *__restrict__ out, uint64_t t, uint32_t *const buf[3],
-                                           uint32_t *s_ring)
-{
-    using LDS = TileLds<Pat>;
-    static_assert(kMaxRing <= NT, "one lane per ring cell");
-    const uint32_t tid = threadIdx.x;
-    const uint64_t S0 = t * A.tile;
-    const uint64_t A0 = S0 & ~31ull;
-    const uint32_t o = (uint32_t)(S0 - A0);
-    const uint32_t W = (o + A.tile + 31) / 32;
-
-    uint64_t gi = kHole64;
-    uint32_t home = 0;
-    if (tid < A.tstride) {
-        gi = A.tile_halo[t * A.tstride + tid];
-        home = A.ringhome[tid];
-    }
-    NbRegs<Pat, NT> R;
-    load_nb<Pat, NT>(A, R);
-    for (uint32_t i = tid; i < A.nsrc * 8; i += NT) s_ring[i] = A.ringsrc[i];
-    tile_pack<NT>(A, in, A0, W, buf[2]);
-    if (tid < LDS::WORDS - LDS::ZERO) {
-        buf[0][LDS::ZERO + tid] = 0;
-        buf[1][LDS::ZERO + tid] = 0;
-        buf[2][LDS::ZERO + tid] = 0;
-    }
-    const bool here = gi != kHole64;  // ring cell tid exists
-    uint32_t v = 0;
-    if (tid < kMaxRing) {
-        v = here ? (in[gi] & 1u) : 0u;
-        s_ring[kMaxRing * 8 + tid] = home;
-    }
-    __syncthreads();
-    tile_convert<Pat, NT>(A, o, buf[2], buf[0]);
-    if (v) atomicOr(lds_word(buf[0], home), 1u << (home & 31));
-    __syncthreads();
-#pragma unroll
-    for (int j = 1; j <= K; ++j) {
-        const uint32_t *src = buf[(j - 1) % 3];
-        uint32_t *dst = buf[j % 3];
-        tile_blocks<Pat, NT, Full>(A, R, src, dst);
-        if (j < K) {
-            uint32_t *clr = buf[(j + 1) % 3];
-            if (tid < LDS::WORDS - LDS::VIRT) clr[LDS::VIRT + tid] = 0;
-            if (tid < A.ring_start[K - j]) {
-                const uint4 e0 = *reinterpret_cast<const uint4 *>(s_ring + tid * 8);
-                const uint4 e1 = *reinterpret_cast<const uint4 *>(s_ring + tid * 8 + 4);
-                const uint32_t cnt = lds_bit(src, e0.x) + lds_bit(src, e0.y) + lds_bit(src, e0.z) +
-                                     lds_bit(src, e0.w) + lds_bit(src, e1.x) + lds_bit(src, e1.y) +
-                                     lds_bit(src, e1.z) + lds_bit(src, e1.w);
-                const uint32_t h = s_ring[kMaxRing * 8 + tid];
-                const uint32_t self = lds_bit(src, h);
-                if (here & ((cnt == 3) | (self & (cnt == 2)))) atomicOr(lds_word(dst, h), 1u << (h & 31));
-            }
-        }
-        __syncthreads();
-    }
-    tile_store<Pat, NT, true>(A, out, A0, o, W, buf[K % 3]);  // streaming: read next by another launch
-    __syncthreads();
-}
-
-
-// ---------------------------------------------------------------------------
-// Resident run: the tiles stay in LDS for the whole run.
-//
-// When every tile of the fractal fits on the chip at once (one workgroup per
-// tile, all co-resident), the tile's state is loaded
-// from HBM once, advanced for all steps in LDS, and stored once.  Every
-// kstep steps the workgroups exchange only the cells other tiles hold as
-// ring cells: each tile writes the current states of its boundary cells
-// (`bound`, tile-local indices; the same for every tile) to their compact
-// positions in one of the two caller buffers, the grid meets at a barrier,
-// and each tile reads its ring cells from there, then advances kstep more
-// steps exactly as the multi-step launch does (tile_bodyK).  Exchange
-// buffers alternate between b and a, so a tile writing the exports of one
-// exchange never meets a tile still reading the previous one; the final
-// state goes to a (steps even) or b (odd), after one more barrier only when
-// the last exchange went through that buffer.
-// ---------------------------------------------------------------------------
-struct ResidentArgs {
-    uint8_t *a, *b;        // caller buffers; a holds the start
-    int32_t steps;         // Life steps of the run (>= 1)
-    int32_t kstep;         // steps between exchanges (2 .. ring depth)
-    uint32_t nbound;       // boundary cells per tile
-    const uint32_t *bound; // their tile-local indices
-    uint32_t *bar;         // device words of the grid barrier (bar_words(grid)); counts carry over between runs
-    uint32_t *flag;        // host-visible word: set to 1 when a barrier wait timed out
-};
-
-// Polls of a barrier wait before it gives up (each poll is a device-scope load
-// and a short sleep, about a microsecond: seconds in all, far above any
-// legitimate wait of a co-resident grid).
+// Polls of a wait on other workgroups before it gives up (each poll is a
+// device-scope load and a short sleep, about a microsecond: seconds in all, far
+// above any legitimate wait between workgroups that are on the chip at once).
 constexpr uint32_t kSpinLimit = 1u << 22;
-
-// Grid barrier of a launch whose workgroups are all on the chip at once.  The
-// cells the tiles exchange are written and read only with device-scope atomic
-// byte accesses (stores and loads that the eight XCDs' separate L2 caches pass
-// through to device-coherent memory), so no cache write-back or invalidation
-// is needed: each wave waits until its exchange stores have completed, the
-// workgroup meets, and one lane counts the arrival.  Counting is two-level, so
-// that no counter takes more than kBarGroup atomic additions per barrier: the
-// workgroups of a group of kBarGroup consecutive block indices add to their
-// group's counter (own 128-byte line), the last of a group to arrive adds to
-// the global counter, and every workgroup polls the global counter until all
-// groups have arrived.  Counts accumulate over runs, modulo 2^32 (barrier i
-// since the counters were cleared waits for i arrivals per member, compared
-// wrap-safe); word 2 holds the barriers completed by earlier runs, read by
-// every workgroup at its start and advanced by workgroup 0 after the run's
-// last barrier, so that no run has to clear the counters (clearing them
-// costs a launch of its own) and replays of a captured run stay in step.
-// The workgroup meets again before any lane reads what others wrote.  The wait is bounded: after kSpinLimit polls, or as soon
-// as another workgroup has given up, the workgroup marks the run as timed out
-// (device word and host-visible flag) and goes on, so every wave reaches the
-// end of the kernel; such a run's results are invalid and the host reports it.
-constexpr uint32_t kBarGroup = 27;
-constexpr uint32_t kBarStride = 32;  // words between counters (128 bytes)
-
-__host__ __device__ constexpr uint32_t bar_words(uint64_t grid)
-{
-    return (uint32_t)((1 + (grid + kBarGroup - 1) / kBarGroup) * kBarStride);
-}
-
-// Arrival of this workgroup at barrier n (one lane, after the workgroup has
-// met with every wave's exchange stores complete).
-__device__ __forceinline__ void barrier_arrive(uint32_t *bar, uint32_t n)
-{
-    const uint32_t G = gridDim.x, g = blockIdx.x / kBarGroup;
-    const uint32_t gs = G - g * kBarGroup < kBarGroup ? G - g * kBarGroup : kBarGroup;
-    const uint32_t old = __hip_atomic_fetch_add(bar + kBarStride * (1 + g), 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    if (old + 1 == n * gs) __hip_atomic_fetch_add(bar, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-// Wait of one lane until every workgroup has arrived at barrier n (bounded).
-__device__ __forceinline__ void barrier_poll(uint32_t *bar, uint32_t n, uint32_t *flag)
-{
-    const uint32_t ng = (gridDim.x + kBarGroup - 1) / kBarGroup, target = n * ng;
-    for (uint32_t spin = 0;; ++spin) {
-        const uint64_t v = __hip_atomic_load(reinterpret_cast<uint64_t *>(bar), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if ((int32_t)((uint32_t)v - target) >= 0) break;
-        if ((v >> 32) != 0 || spin == kSpinLimit) {
-            __hip_atomic_store(bar + 1, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(flag, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
-            break;
-        }
-        __builtin_amdgcn_s_sleep(2);
-    }
-}
-
-__device__ __forceinline__ void grid_barrier(uint32_t *bar, uint32_t nbar, uint32_t *flag)
-{
-    __builtin_amdgcn_s_waitcnt(0);  // this wave's exchange stores are complete
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        barrier_arrive(bar, nbar);
-        barrier_poll(bar, nbar, flag);
-    }
-    __syncthreads();
-}
-
-// One tile for the whole run.  s_buf: three LDS buffers of TileLds<Pat>::WORDS
-// words, one after another; s_ring: kRingTab words (16-byte aligned); s_rs:
-// kMaxSteps + 1 words.  grid = number of tiles, all resident.
-template <class Pat, int NT>
-__device__ __forceinline__ void tile_bodyR(const TileArgs &A, const ResidentArgs &P, uint64_t t, uint32_t *s_buf,
-                                           uint32_t *s_ring, uint32_t *s_rs)
-{
-    using LDS = TileLds<Pat>;
-    constexpr uint32_t NC = PlanOf<Pat>::value.nc;
-    constexpr uint32_t WORDS = LDS::WORDS;
-    static_assert(kMaxRing <= NT, "one lane per ring cell");
-    const uint32_t tid = threadIdx.x;
-    const uint64_t S0 = t * A.tile;
-    const uint64_t A0 = S0 & ~31ull;
-    const uint32_t o = (uint32_t)(S0 - A0);
-    const uint32_t W = (o + A.tile + 31) / 32;
-
-    uint64_t gi = kHole64;
-    uint32_t home = 0;
-    if (tid < A.tstride) {
-        gi = A.tile_halo[t * A.tstride + tid];
-        home = A.ringhome[tid];
-    }
-    NbRegs<Pat, NT> R;
-    load_nb<Pat, NT>(A, R);
-    for (uint32_t i = tid; i < A.nsrc * 8; i += NT) s_ring[i] = A.ringsrc[i];
-    if (tid <= (uint32_t)kMaxSteps) s_rs[tid] = A.ring_start[tid];
-    tile_pack<NT>(A, P.a, A0, W, s_buf + 2 * WORDS);
-    if (tid < WORDS - LDS::ZERO) {
-        s_buf[LDS::ZERO + tid] = 0;
-        s_buf[WORDS + LDS::ZERO + tid] = 0;
-        s_buf[2 * WORDS + LDS::ZERO + tid] = 0;
-    }
-    const bool here = gi != kHole64;  // ring cell tid exists
-    uint32_t v = 0;
-    if (tid < kMaxRing) {
-        v = here ? (P.a[gi] & 1u) : 0u;
-        s_ring[kMaxRing * 8 + tid] = home;
-    }
-    __syncthreads();
-    tile_convert<Pat, NT>(A, o, s_buf + 2 * WORDS, s_buf);
-    if (v) atomicOr(lds_word(s_buf, home), 1u << (home & 31));
-    __syncthreads();
-
-    uint32_t cur = 0, nbar = 0;  // buffer holding the state; barriers passed in this run
-    // barriers completed by earlier runs (used by the counting lane only)
-    const uint32_t base = tid == 0 ? __hip_atomic_load(P.bar + 2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
-    // Slots of this wave with a block that reads ring words (word VIRT and up,
-    // cleared at an exchange and then filled from the other tiles): the first
-    // round after an exchange updates the other slots while the barrier
-    // completes, these after the ring cells have arrived.  The neighbour table
-    // is the same for every tile, so this is too.
-    uint32_t defer = 0;
-#pragma unroll
-    for (int sl = 0; sl < NbRegs<Pat, NT>::NSLOT; ++sl) {
-        bool ring = false;
-        if (tid + sl * NT < A.nblocks)
-#pragma unroll
-            for (int g = 0; g < LDS::NGRP; ++g) ring |= R.at(sl, g) >= 4u * LDS::VIRT;
-        if (__ballot(ring)) defer |= 1u << sl;
-    }
-    // 512-lane workgroups (six waves per SIMD) have the registers for offsets held
-    // unpacked; the 256-lane ones (eight) keep the packed form
-    constexpr bool STATIC = SQZ_RES_STATIC && NT >= 512;
-    NbOffs<Pat, NT> U;
-    if constexpr (STATIC) {
-#pragma unroll
-        for (int sl = 0; sl < NbOffs<Pat, NT>::NU; ++sl)
-#pragma unroll
-            for (int g = 0; g < LDS::NGRP; ++g) U.o[sl][g] = R.at(sl, g);
-#pragma unroll
-        for (int sl = NbOffs<Pat, NT>::NU; sl < NbOffs<Pat, NT>::NSLOT; ++sl)
-#pragma unroll
-            for (int q = 0; q < NbOffs<Pat, NT>::NP; ++q) U.p[sl - NbOffs<Pat, NT>::NU][q] = R.a[sl][q];
-    }
-    const uint8_t *imp = nullptr;  // exchange buffer whose barrier this workgroup has arrived at, not yet passed
-    int32_t done = 0;
-    for (;;) {
-        const int32_t ks = P.steps - done < P.kstep ? P.steps - done : P.kstep;
-        if constexpr (STATIC) {
-        for (int32_t j = 1; j <= ks; ++j) {
-            // one round from buffer C (a compile-time choice, so every LDS
-            // address below is a register plus a constant)
-            auto round = [&](auto Cc) {
-                constexpr uint32_t C = decltype(Cc)::value, NX = C == 2 ? 0 : C + 1, CL = NX == 2 ? 0 : NX + 1;
-                const uint32_t *src = s_buf + C * WORDS;
-                uint32_t *dst = s_buf + NX * WORDS;
-                if (imp) {
-                    tile_blocks<Pat, NT>(A, U, src, dst, ~defer);
-                    if (tid == 0) barrier_poll(P.bar, base + nbar, P.flag);
-                    __syncthreads();
-                    v = 0;
-                    if (tid < kMaxRing)
-                        v = here ? (__hip_atomic_load(imp + gi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u) : 0u;
-                    if (v) atomicOr(lds_word(s_buf + C * WORDS, home), 1u << (home & 31));
-                    __syncthreads();
-                    tile_blocks<Pat, NT>(A, U, src, dst, defer);
-                    imp = nullptr;
-                } else {
-                    tile_blocks<Pat, NT>(A, U, src, dst);
-                }
-                if (j < ks) {
-                    uint32_t *clr = s_buf + CL * WORDS;
-                    if (tid < WORDS - LDS::VIRT) clr[LDS::VIRT + tid] = 0;
-                    if (tid < s_rs[ks - j]) {
-                        const uint4 e0 = *reinterpret_cast<const uint4 *>(s_ring + tid * 8);
-                        const uint4 e1 = *reinterpret_cast<const uint4 *>(s_ring + tid * 8 + 4);
-                        const uint32_t cnt = lds_bit(src, e0.x) + lds_bit(src, e0.y) + lds_bit(src, e0.z) +
-                                             lds_bit(src, e0.w) + lds_bit(src, e1.x) + lds_bit(src, e1.y) +
-                                             lds_bit(src, e1.z) + lds_bit(src, e1.w);
-                        const uint32_t h = s_ring[kMaxRing * 8 + tid];
-                        const uint32_t self = lds_bit(src, h);
-                        if (here & ((cnt == 3) | (self & (cnt == 2)))) atomicOr(lds_word(dst, h), 1u << (h & 31));
-                    }
-                }
-            };
-            if (cur == 0)
-                round(std::integral_constant<uint32_t, 0>{});
-            else if (cur == 1)
-                round(std::integral_constant<uint32_t, 1>{});
-            else
-                round(std::integral_constant<uint32_t, 2>{});
-            __syncthreads();
-            cur = cur == 2 ? 0 : cur + 1;
-        }
-        } else {
-        for (int32_t j = 1; j <= ks; ++j) {
-            const uint32_t nx = cur == 2 ? 0 : cur + 1, cl = nx == 2 ? 0 : nx + 1;
-            const uint32_t *src = s_buf + cur * WORDS;
-            uint32_t *dst = s_buf + nx * WORDS;
-            if (imp) {
-                tile_blocks<Pat, NT>(A, R, src, dst, ~defer);
-                if (tid == 0) barrier_poll(P.bar, base + nbar, P.flag);
-                __syncthreads();
-                v = 0;
-                if (tid < kMaxRing)
-                    v = here ? (__hip_atomic_load(imp + gi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u) : 0u;
-                if (v) atomicOr(lds_word(s_buf + cur * WORDS, home), 1u << (home & 31));
-                __syncthreads();
-                tile_blocks<Pat, NT>(A, R, src, dst, defer);
-                imp = nullptr;
-            } else if (A.nblocks == LDS::NBMAX) {
-                tile_blocks<Pat, NT, true>(A, R, src, dst);
-            } else {
-                tile_blocks<Pat, NT>(A, R, src, dst);
-            }
-            if (j < ks) {
-                uint32_t *clr = s_buf + cl * WORDS;
-                if (tid < WORDS - LDS::VIRT) clr[LDS::VIRT + tid] = 0;
-                if (tid < s_rs[ks - j]) {
-                    const uint4 e0 = *reinterpret_cast<const uint4 *>(s_ring + tid * 8);
-                    const uint4 e1 = *reinterpret_cast<const uint4 *>(s_ring + tid * 8 + 4);
-                    const uint32_t cnt = lds_bit(src, e0.x) + lds_bit(src, e0.y) + lds_bit(src, e0.z) +
-                                         lds_bit(src, e0.w) + lds_bit(src, e1.x) + lds_bit(src, e1.y) +
-                                         lds_bit(src, e1.z) + lds_bit(src, e1.w);
-                    const uint32_t h = s_ring[kMaxRing * 8 + tid];
-                    const uint32_t self = lds_bit(src, h);
-                    if (here & ((cnt == 3) | (self & (cnt == 2)))) atomicOr(lds_word(dst, h), 1u << (h & 31));
-                }
-            }
-            __syncthreads();
-            cur = nx;
-        }
-        }
-        done += ks;
-        if (done >= P.steps) break;
-        // exchange: boundary cells out, ring cells in
-        uint8_t *xb = (nbar & 1) ? P.a : P.b;
-        const uint32_t *st = s_buf + cur * WORDS;
-        for (uint32_t i = tid; i < P.nbound; i += NT) {
-            const uint32_t z = P.bound[i];
-            __hip_atomic_store(xb + S0 + z, (uint8_t)((st[z / NC] >> (z % NC)) & 1u), __ATOMIC_RELAXED,
-                               __HIP_MEMORY_SCOPE_AGENT);
-        }
-        if (tid < WORDS - LDS::VIRT) {
-            s_buf[LDS::VIRT + tid] = 0;
-            s_buf[WORDS + LDS::VIRT + tid] = 0;
-            s_buf[2 * WORDS + LDS::VIRT + tid] = 0;
-        }
-        ++nbar;
-        if (SQZ_SPLIT_EXCHANGE) {
-            __builtin_amdgcn_s_waitcnt(0);  // this wave's exchange stores are complete
-            __syncthreads();
-            if (tid == 0) barrier_arrive(P.bar, base + nbar);
-            imp = xb;  // the next round waits for the barrier after updating the other slots
-        } else {
-            grid_barrier(P.bar, base + nbar, P.flag);
-            v = 0;
-            if (tid < kMaxRing)
-                v = here ? (__hip_atomic_load(xb + gi, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & 1u) : 0u;
-            if (v) atomicOr(lds_word(s_buf + cur * WORDS, home), 1u << (home & 31));
-            __syncthreads();
-        }
-    }
-    // The state goes to the buffer of the step count's parity.  A tile reads an
-    // exchange buffer only between the barrier that closes that exchange and its
-    // own arrival at the next barrier, and reads the start buffer `a` only before
-    // its first one; so only the last exchange's buffer (exchange j goes through
-    // b for odd j, a for even j; `a` counts as exchange 0) may still be in use,
-    // and only a store into it must wait for every tile.
-    if ((uint32_t)(P.steps & 1) == (nbar & 1)) {
-        ++nbar;
-        grid_barrier(P.bar, base + nbar, P.flag);
-    }
-    // every workgroup has passed a barrier of this run, so has read the base
-    if (nbar && blockIdx.x == 0 && tid == 0)
-        __hip_atomic_store(P.bar + 2, base + nbar, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    tile_store<Pat, NT, true>(A, (P.steps & 1) ? P.b : P.a, A0, o, W, s_buf + cur * WORDS);
-}
 
 }  // namespace sqz
