@@ -178,9 +178,8 @@ sqz_status sqz_fractal_info(const sqz_fractal *f, sqz_info *out)
     out->xtile_level = xtile_level_of(f->h);
     out->bits_level = bitbox_level_of(f->h);
     {
-        const int kt = tile_steps_per_launch(f->h), kb = bitbox_steps_per_launch(f->h),
-                  kx = xtile_steps_per_launch(f->h);
-        const int k = f->h.tile_kind ? kt : (f->h.bitbox ? kb : kx);
+        const int kt = tile_steps_per_launch(f->h), kx = xtile_steps_per_launch(f->h);
+        const int k = f->h.tile_kind ? kt : (f->h.bitbox ? kMaxSteps : kx);
         out->run_steps_per_launch = k > 1 ? k : 1;
         out->resident_run = resident(f->h) ? 1 : 0;
     }
@@ -388,7 +387,7 @@ sqz_status sqz_compact_run_form(const sqz_fractal *f, sqz_run_form form, uint8_t
     const bool aligned8 = !(((uintptr_t)d_a | (uintptr_t)d_b) & 7);
     const bool bits = f->h.bitbox && aligned8;
     const int K = bits ? bitbox_steps_per_launch(f->h) : (f->h.tile_kind && aligned ? 1 : xtile_steps_per_launch(f->h));
-    if (K >= 2) {
+    if (bits || K >= 2) {
         const std::vector<int> plan = plan_launches(steps, K);
         const hipStream_t s = (hipStream_t)stream;
         for (size_t i = 0; i < plan.size() && st == SQZ_OK; ++i) {

@@ -218,18 +218,16 @@ k_batch_slice(GroupArgs G, const uint8_t *in, uint8_t *out, int32_t steps)
     slice_tile<P, false>(A, in + base, out + base, b - G.tstart[i], SliceRing{in + base, false}, steps, SliceRes{}, sm);
 }
 
-template <class Pat, int K>
-__global__ void __launch_bounds__(kBxThreads) __attribute__((amdgpu_waves_per_eu(6)))
-k_batch_bitbox(GroupArgs G, const uint8_t *__restrict__ in, uint8_t *__restrict__ out)
+template <class Pat>
+__global__ void __launch_bounds__(kBxThreads) __attribute__((amdgpu_waves_per_eu(8)))
+k_batch_bitbox(GroupArgs G, const uint8_t *__restrict__ in, uint8_t *__restrict__ out, int32_t steps)
 {
-    __shared__ uint32_t s_buf[2][kBxBuf];
-    __shared__ uint64_t s_nb[9];
-    __shared__ uint32_t s_ex;
+    __shared__ __align__(16) uint32_t sm[kBxLds];
     const uint64_t b = blockIdx.x;
     const uint32_t i = group_instance(G, b);
     const BitboxArgs &A = reinterpret_cast<const BitboxArgs *>(G.args)[i];
     const uint64_t base = G.base[i];
-    bitbox_tile<Pat, K>(A, in + base, out + base, b - G.tstart[i], s_buf, s_nb, &s_ex);
+    bitbox_tile<Pat>(A, in + base, out + base, b - G.tstart[i], steps, sm);
 }
 
 // Instance of the persistent tiled launch (patterns with a tiled kernel).
@@ -253,10 +251,6 @@ struct TiledArgs {
     uint64_t total_cost;
 };
 
-// LDS of a tile body: the bit-sliced tiles' words or the bit-row layout (two
-// row buffers, nine bases, one flag word), whichever the kind uses; bytes.
-constexpr size_t kBitsLds = 2 * (size_t)kBxBuf * 4 + 9 * 8 + 16;
-
 template <class P>
 __device__ __forceinline__ void tiled_unit(const SliceArgs &A, const uint8_t *in, uint8_t *out, uint64_t t, int32_t steps,
                                            unsigned char *smem)
@@ -265,41 +259,32 @@ __device__ __forceinline__ void tiled_unit(const SliceArgs &A, const uint8_t *in
     __syncthreads();  // LDS is free for the next tile
 }
 
-template <int K>
-__device__ __forceinline__ void bits_unit(const BitboxArgs &A, const uint8_t *in, uint8_t *out, uint64_t t,
-                                          unsigned char *smem)
-{
-    if constexpr (K <= kBxMaxSteps) {
-        uint32_t(*s_buf)[kBxBuf] = reinterpret_cast<uint32_t(*)[kBxBuf]>(smem);
-        uint64_t *s_nb = reinterpret_cast<uint64_t *>(smem + ((2 * (size_t)kBxBuf * 4 + 7) & ~(size_t)7));
-        bitbox_tile<PatCarpet, K>(A, in, out, t, s_buf, s_nb, reinterpret_cast<uint32_t *>(s_nb + 9));
-    }
-}
-
-template <int K>
-__device__ __forceinline__ void tiled_run(const TiledInst &I, const uint8_t *in, uint8_t *out, uint64_t j,
+__device__ __forceinline__ void tiled_run(const TiledInst &I, const uint8_t *in, uint8_t *out, uint64_t j, int32_t steps,
                                           unsigned char *smem)
 {
     const uint8_t *ii = in + I.base;
     uint8_t *oo = out + I.base;
     switch (I.kind) {
-    case kBTri: tiled_unit<SliceTriSmall>(I.t, ii, oo, j, K, smem); break;
-    case kBTriPaper: tiled_unit<SlicePaperSmall>(I.t, ii, oo, j, K, smem); break;
-    case kBVicsek: tiled_unit<SliceVicsekSmall>(I.t, ii, oo, j, K, smem); break;
-    default: bits_unit<K>(I.x, ii, oo, j, smem); break;
+    case kBTri: tiled_unit<SliceTriSmall>(I.t, ii, oo, j, steps, smem); break;
+    case kBTriPaper: tiled_unit<SlicePaperSmall>(I.t, ii, oo, j, steps, smem); break;
+    case kBVicsek: tiled_unit<SliceVicsekSmall>(I.t, ii, oo, j, steps, smem); break;
+    default:
+        bitbox_tile<PatCarpet>(I.x, ii, oo, j, steps, reinterpret_cast<uint32_t *>(smem));
+        __syncthreads();
+        break;
     }
 }
 
-// K Life steps of every instance with a tiled kernel in one launch: the tiles
+// `steps` Life steps of every instance with a tiled kernel in one launch: the tiles
 // of all such instances form one sequence, each run with its pattern's tile
 // body (bit-sliced tiles of the triangle, its mirror image and the Vicsek
 // cross; bit rows of the carpet).  Persistent (PerTile false): the sequence
 // is weighted by cells and workgroup b takes the tiles whose first cell falls
 // in the b-th equal share.  PerTile: one workgroup per tile, dealt to the
 // XCDs in contiguous runs.
-template <int K, bool PerTile>
+template <bool PerTile>
 __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
-k_batch_tiles(TiledArgs B, const uint8_t *in, uint8_t *out)
+k_batch_tiles(TiledArgs B, const uint8_t *in, uint8_t *out, int32_t steps)
 {
     extern __shared__ __align__(16) unsigned char smem[];
     if constexpr (PerTile) {
@@ -323,7 +308,7 @@ k_batch_tiles(TiledArgs B, const uint8_t *in, uint8_t *out)
             }
             j = b - B.tile_start[a];
         }
-        tiled_run<K>(B.inst[a], in, out, j, smem);
+        tiled_run(B.inst[a], in, out, j, steps, smem);
         return;
     }
     const uint64_t lo = B.total_cost * blockIdx.x / gridDim.x;
@@ -350,7 +335,7 @@ k_batch_tiles(TiledArgs B, const uint8_t *in, uint8_t *out)
             continue;
         }
         if (I.cost_start + j * I.unit_cells >= hi) break;
-        tiled_run<K>(I, in, out, j, smem);
+        tiled_run(I, in, out, j, steps, smem);
         ++j;  // every tile body ends with a barrier: LDS is free for the next tile
     }
 }
@@ -498,8 +483,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                 T.x = bitbox_args(F);
                 T.units = T.x.ntiles;
                 T.unit_cells = T.x.tile;
-                H->Kt_max = std::min(H->Kt_max, bitbox_steps_per_launch(F));
-                H->tlds = std::max(H->tlds, kBitsLds);
+                                H->tlds = std::max<size_t>(H->tlds, kBxLds * 4);
             } else {
                 SliceConfig *&C = slice_of[&F];
                 if (!C) {
@@ -529,14 +513,15 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                 G = &H->groups.back();
             }
             if (I.kind == kBBits) {
-                G->K_full = kMaxSteps;
+                const int K = bitbox_steps_per_launch(F);
+                if (K) G->K_full = K;
             } else {
                 const SliceConfig *C = slice_of[&F];
                 if (C->K) G->K_full = (int)C->K;  // the same for every fractal of more than one tile
                 G->threads = std::max(G->threads, (C->A.lanes + 63) / 64 * 64);
             }
             G->members.push_back((uint32_t)i);
-            G->K_max = std::min(G->K_max, I.kind == kBBits ? bitbox_steps_per_launch(F) : tile_steps_per_launch(F));
+            G->K_max = std::min(G->K_max, I.kind == kBBits ? kMaxSteps : tile_steps_per_launch(F));
             G->K = G->K_max;
             I.units = 0;  // not in the expanded-tile / thread-level launch
             I.unit_cells = 1;
@@ -671,7 +656,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
         H->Kt = H->Kt_max;
         int per_cu = 0;
         if (e == hipSuccess)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch_tiles<2, false>, 256, H->tlds);
+            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch_tiles<false>, 256, H->tlds);
         H->twg_max = per_cu < 1 ? 1u : (unsigned)per_cu;
         H->twg = H->twg_max;
     }
@@ -787,26 +772,7 @@ static sqz_status launch_batch(const BatchHost *H, unsigned wg_per_cu, const uin
     return e == hipSuccess ? SQZ_OK : hip_error(e, "batch launch");
 }
 
-static void launch_bits_group(const GroupArgs &A, unsigned grid, const uint8_t *in, uint8_t *out, int steps,
-                              hipStream_t st)
-{
-    const dim3 g(grid), b(kBxThreads);
-    switch (steps) {
-    case 1: hipLaunchKernelGGL((k_batch_bitbox<PatCarpet, 1>), g, b, 0, st, A, in, out); break;
-    case 2: hipLaunchKernelGGL((k_batch_bitbox<PatCarpet, 2>), g, b, 0, st, A, in, out); break;
-    case 3: hipLaunchKernelGGL((k_batch_bitbox<PatCarpet, 3>), g, b, 0, st, A, in, out); break;
-    case 4: hipLaunchKernelGGL((k_batch_bitbox<PatCarpet, 4>), g, b, 0, st, A, in, out); break;
-    case 5: hipLaunchKernelGGL((k_batch_bitbox<PatCarpet, 5>), g, b, 0, st, A, in, out); break;
-    case 6: hipLaunchKernelGGL((k_batch_bitbox<PatCarpet, 6>), g, b, 0, st, A, in, out); break;
-    case 7: hipLaunchKernelGGL((k_batch_bitbox<PatCarpet, 7>), g, b, 0, st, A, in, out); break;
-    case 8: hipLaunchKernelGGL((k_batch_bitbox<PatCarpet, 8>), g, b, 0, st, A, in, out); break;
-    case 9: hipLaunchKernelGGL((k_batch_bitbox<PatCarpet, 9>), g, b, 0, st, A, in, out); break;
-    default: hipLaunchKernelGGL((k_batch_bitbox<PatCarpet, 10>), g, b, 0, st, A, in, out); break;
-    }
-}
-
-// One launch of `steps` steps (bit rows: at most kMaxSteps, bit-sliced tiles:
-// at most K_full) for every instance of group G.
+// One launch of `steps` steps (at most K_full) for every instance of group G.
 static sqz_status launch_group(const BatchGroup &G, const uint8_t *in, uint8_t *out, int steps, hipStream_t st)
 {
     const GroupArgs A{G.d_args, G.d_base, G.d_tstart, (uint32_t)G.members.size()};
@@ -821,7 +787,9 @@ static sqz_status launch_group(const BatchGroup &G, const uint8_t *in, uint8_t *
     case kBVicsek:
         hipLaunchKernelGGL(k_batch_slice<SliceVicsekSmall>, dim3(grid), dim3(G.threads), 0, st, A, in, out, steps);
         break;
-    default: launch_bits_group(A, grid, in, out, steps, st); break;
+    default:
+        hipLaunchKernelGGL(k_batch_bitbox<PatCarpet>, dim3(grid), dim3(kBxThreads), 0, st, A, in, out, steps);
+        break;
     }
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? SQZ_OK : hip_error(e, "batch group launch");
@@ -831,18 +799,7 @@ template <bool PerTile>
 static void launch_tiles_k(int steps, dim3 g, dim3 b, size_t L, hipStream_t st, const TiledArgs &A, const uint8_t *in,
                            uint8_t *out)
 {
-    switch (steps) {
-    case 1: hipLaunchKernelGGL((k_batch_tiles<1, PerTile>), g, b, L, st, A, in, out); break;
-    case 2: hipLaunchKernelGGL((k_batch_tiles<2, PerTile>), g, b, L, st, A, in, out); break;
-    case 3: hipLaunchKernelGGL((k_batch_tiles<3, PerTile>), g, b, L, st, A, in, out); break;
-    case 4: hipLaunchKernelGGL((k_batch_tiles<4, PerTile>), g, b, L, st, A, in, out); break;
-    case 5: hipLaunchKernelGGL((k_batch_tiles<5, PerTile>), g, b, L, st, A, in, out); break;
-    case 6: hipLaunchKernelGGL((k_batch_tiles<6, PerTile>), g, b, L, st, A, in, out); break;
-    case 7: hipLaunchKernelGGL((k_batch_tiles<7, PerTile>), g, b, L, st, A, in, out); break;
-    case 8: hipLaunchKernelGGL((k_batch_tiles<8, PerTile>), g, b, L, st, A, in, out); break;
-    case 9: hipLaunchKernelGGL((k_batch_tiles<9, PerTile>), g, b, L, st, A, in, out); break;
-    default: hipLaunchKernelGGL((k_batch_tiles<10, PerTile>), g, b, L, st, A, in, out); break;
-    }
+    hipLaunchKernelGGL(k_batch_tiles<PerTile>, g, b, L, st, A, in, out, steps);
 }
 
 // One launch of `steps` (1..H->Kt_max) steps for every tiled instance: form 1

@@ -128,6 +128,11 @@ inline std::vector<int> plan_launches(int32_t steps, int K)
     return plan;
 }
 
+// Life steps per launch that are reported for bit-sliced tiles and bit rows,
+// and the most a caller can choose in a batch (runs of the library's own choice
+// take more: slice_device.h, bitbox_device.h).
+constexpr int kMaxSteps = 10;
+
 // Host helpers (api.hip; the HIP-free ones are in host_tables.h)
 sqz_status hip_error(hipError_t e, const char *what);
 // map tables of `level` (map_tables) uploaded to new device memory *d_mem; P's table pointers set
@@ -189,7 +194,7 @@ int mass_grid();
 // Bit-row expanded tiles (bitbox.hip)
 sqz_status bitbox_prepare(FractalHost &F);
 void bitbox_release(FractalHost &F);
-int bitbox_steps_per_launch(const FractalHost &F);  // 0: none
+int bitbox_steps_per_launch(const FractalHost &F);  // 0: any number (one tile); -1: no bit rows
 int32_t bitbox_level_of(const FractalHost &F);
 sqz_status launch_life_bitbox(const FractalHost &F, const uint8_t *in, uint8_t *out, int steps, hipStream_t st);
 

@@ -77,7 +77,6 @@ constexpr int cpow(int b, int e)
 }
 
 constexpr int kMaxHalo = 16;      // halo cells per block
-constexpr int kMaxSteps = 10;     // Life steps per launch reported for bit-sliced tiles (runs take more: slice_device.h)
 constexpr int kMaxTileHalo = 32;  // halo cells per tile (one LDS word of bits)
 constexpr int kBlock = 256;
 
