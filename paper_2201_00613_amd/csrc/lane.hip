@@ -44,7 +44,11 @@ auto lane_dispatch(int kind, F &&f)
     case 2: return f(LaneTrianglePaper{});
     case 3: return f(LaneVicsek{});
     case 4: return f(LaneCarpet{});
-    default: return f(LaneCarpetSmall{});
+    case 5: return f(LaneCarpetSmall{});
+    case 6: return f(LaneTriangleFine{});
+    case 7: return f(LaneTrianglePaperFine{});
+    case 8: return f(LaneVicsekFine{});
+    default: return f(LaneCarpetFine{});
     }
 }
 
@@ -57,18 +61,40 @@ bool lane_matches(const FractalHost &F)
     return true;
 }
 
+// Kernel.  Level-1 blocks where a fractal does not fill the chip and a step
+// takes the latency of one lane's work (30 steps, binary32 / bfloat16 with
+// stochastic rounding: level-9 triangle 16.8 / 21.5 -> 12.1 / 13.6 us, level 12
+// 18.9 / 28.0 -> 18.5 / 22.3; Vicsek level 6 22.6 / 39.0 -> 14.5 / 16.5; carpet
+// level 6 50 / 75 -> 27 / 40), level-2 blocks above, where the wider frames and
+// the halo reads per cell cost more (triangle level 13 24.4 against 36.1, Vicsek
+// level 9 36 against 40, carpet level 7 58 against 127).
+int lane_kind(const FractalHost &F)
+{
+    if (lane_matches<LaneTriangleFine>(F)) return F.r >= 13 ? 1 : 6;
+    if (lane_matches<LaneTrianglePaperFine>(F)) return F.r >= 13 ? 2 : 7;
+    if (lane_matches<LaneVicsekFine>(F)) return F.r >= 9 ? 3 : 8;
+    if (lane_matches<LaneCarpetFine>(F)) return F.r >= 8 ? 4 : (F.r == 7 ? 5 : 9);
+    return 0;
+}
+
 // Tile level.  A fractal of at most one full workgroup is one tile (no ring,
-// any number of steps per launch); above, the largest tiles that still leave
+// any number of steps per launch), except where several small ones have the
+// shorter step (triangle level 7: 13.9 us as one tile of 729 lanes, 11.6 as
+// nine; level 6: 10.0 and 10.5).  Above, the largest tiles that still leave
 // tens to hundreds of them: until the chip is full a step takes as long as one
-// tile of any size (level-5 and level-6 carpets, 8 and 64 tiles of level 4: 30
-// steps in 49 and 50 us).
+// tile of any size.
 int lane_level(int kind, int r)
 {
     switch (kind) {
-    case 3: return r <= 5 ? r : (r <= 7 ? 4 : std::min(r - 3, 6));
+    case 1:
+    case 2: return r <= 13 ? 7 : 8;
+    case 3: return 6;
     case 4: return 5;
-    case 5: return std::min(r, 4);
-    default: return r <= 8 ? r : (r <= 10 ? 6 : (r <= 13 ? 7 : 8));
+    case 5: return 4;
+    case 6:
+    case 7: return r <= 6 ? r : (r <= 9 ? 5 : (r <= 11 ? 6 : 7));
+    case 8: return std::min(r, 4);
+    default: return r <= 4 ? r : 3;
     }
 }
 
@@ -85,11 +111,7 @@ void lane_release(FractalHost &F)
 sqz_status lane_prepare(FractalHost &F)
 {
     F.lane = nullptr;
-    int kind = 0;
-    if (lane_matches<LaneTriangle>(F)) kind = 1;
-    else if (lane_matches<LaneTrianglePaper>(F)) kind = 2;
-    else if (lane_matches<LaneVicsek>(F)) kind = 3;
-    else if (lane_matches<LaneCarpet>(F)) kind = F.r >= 8 ? 4 : 5;
+    const int kind = lane_kind(F);
     if (!kind) return SQZ_OK;
     LaneSpec S{};
     S.M = lane_level(kind, F.r);
@@ -154,7 +176,8 @@ bool lane_available(const FractalHost &F) { return F.lane != nullptr; }
 // it for the carpet (level 9: 263 against 238), whose box it fills densely.
 bool lane_one_step(const FractalHost &F)
 {
-    return F.lane && (F.lane->kind <= 2 || (F.lane->kind == 3 && F.r >= 9));
+    const int kind = F.lane ? F.lane->kind : 0;
+    return kind == 1 || kind == 2 || kind == 3 || kind == 6 || kind == 7;
 }
 
 // `steps` steps ping-ponging from a: launches of nearly equal step counts, at

@@ -3,8 +3,8 @@
 // Thread-level to Block-level").
 //
 //   tile  = a level-M subtree, one workgroup; block = a level-J subtree (the
-//           carpet's 64 cells, 9 of the triangle, 25 of the Vicsek cross), one
-//           lane.  In-block neighbours are registers; the cells of adjacent
+//           carpet's 64 cells, 9 of the triangle, 25 of the Vicsek cross; 8, 3
+//           and 5 where the fractal does not fill the chip), one lane.  In-block neighbours are registers; the cells of adjacent
 //           blocks a block touches are values those lanes publish in LDS each
 //           step.  Where every cell read eight neighbours from LDS (nine reads
 //           a cell and step), a carpet block reads 40 values and publishes 32
@@ -170,26 +170,40 @@ struct LanePlanOf {
     static_assert(value.ok, "block does not fit the lane kernel");
 };
 
-// Patterns: block level J, largest tile level MMAX, lanes (a multiple of 64,
+// Patterns: block level J, lanes (a multiple of 64,
 // more than tile and ring need: the last lane's LDS column stays zero).
 // FRAME blocks: the ring is the frame of that many blocks around the tile
 // (dense patterns: STEPS is the frame's width in cells); 0: the level-RL
 // subtrees that hold the cells next to the tile, which cover STEPS steps
 // (their side, one less for the triangles).
 struct LaneTriangle : PatTriangle {
-    static constexpr int J = 2, MMAX = 8, LANES = 832, RL = 4, STEPS = 15, FRAME = 0;
+    static constexpr int J = 2, LANES = 832, RL = 4, STEPS = 15, FRAME = 0;
 };
 struct LaneTrianglePaper : PatTrianglePaper {
-    static constexpr int J = 2, MMAX = 8, LANES = 832, RL = 4, STEPS = 15, FRAME = 0;
+    static constexpr int J = 2, LANES = 832, RL = 4, STEPS = 15, FRAME = 0;
 };
 struct LaneVicsek : PatVicsek {
-    static constexpr int J = 2, MMAX = 6, LANES = 704, RL = 3, STEPS = 27, FRAME = 0;
+    static constexpr int J = 2, LANES = 704, RL = 3, STEPS = 27, FRAME = 0;
 };
 struct LaneCarpet : PatCarpet {
-    static constexpr int J = 2, MMAX = 5, LANES = 768, RL = 0, STEPS = 18, FRAME = 2;
+    static constexpr int J = 2, LANES = 768, RL = 0, STEPS = 18, FRAME = 2;
 };
 struct LaneCarpetSmall : PatCarpet {
-    static constexpr int J = 2, MMAX = 4, LANES = 192, RL = 0, STEPS = 18, FRAME = 2;
+    static constexpr int J = 2, LANES = 192, RL = 0, STEPS = 18, FRAME = 2;
+};
+// Fractals that do not fill the chip, where a step's own latency counts: fewer
+// cells per lane.
+struct LaneTriangleFine : PatTriangle {
+    static constexpr int J = 1, LANES = 960, RL = 4, STEPS = 15, FRAME = 0;
+};
+struct LaneTrianglePaperFine : PatTrianglePaper {
+    static constexpr int J = 1, LANES = 960, RL = 4, STEPS = 15, FRAME = 0;
+};
+struct LaneVicsekFine : PatVicsek {
+    static constexpr int J = 1, LANES = 768, RL = 3, STEPS = 27, FRAME = 0;
+};
+struct LaneCarpetFine : PatCarpet {
+    static constexpr int J = 1, LANES = 576, RL = 0, STEPS = 15, FRAME = 5;
 };
 
 // Storage types: G in memory, binary32 in registers.
