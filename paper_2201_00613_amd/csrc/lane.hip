@@ -8,8 +8,8 @@
 namespace sqz {
 
 template <class P, class Op>
-__global__ void __launch_bounds__(P::LANES) __attribute__((amdgpu_waves_per_eu(P::FRAME ? 3 : 1))) k_lane(LaneArgs A, const typename Op::G *__restrict__ in,
-                                                   typename Op::G *__restrict__ out, XOp op, int32_t steps)
+__global__ void __launch_bounds__(P::LANES) __attribute__((amdgpu_waves_per_eu(P::FRAME ? 3 : 1)))
+k_lane(LaneArgs A, const typename Op::G *__restrict__ in, typename Op::G *__restrict__ out, XOp op, int32_t steps)
 {
     __shared__ __align__(16) uint32_t sm[LaneCfg<P, Op>::LDSW];
     lane_tile<P, Op>(A, in, out, xcd_remap(blockIdx.x, gridDim.x), op, steps, sm);
@@ -209,14 +209,19 @@ sqz_status lane_diffuse_run(const FractalHost &F, int dtype, float coef, int rou
             using P = decltype(p);
             const dim3 block((L.A.lanes + 63) / 64 * 64);
             const dim3 grid(L.A.ntiles);
+            auto launch = [&](auto o) {
+                using Op = decltype(o);
+                using G = typename Op::G;
+                hipLaunchKernelGGL((k_lane<P, Op>), grid, block, 0, st, L.A, (const G *)in, (G *)out, op, k);
+            };
             if (dtype == SQZ_F32)
-                hipLaunchKernelGGL((k_lane<P, LaneF32>), grid, block, 0, st, L.A, (const float *)in, (float *)out, op, k);
-            else if (rounding == SQZ_ROUND_STOCHASTIC)
-                hipLaunchKernelGGL((k_lane<P, LaneBF16<SQZ_ROUND_STOCHASTIC>>), grid, block, 0, st, L.A,
-                                   (const uint16_t *)in, (uint16_t *)out, op, k);
-            else
-                hipLaunchKernelGGL((k_lane<P, LaneBF16<SQZ_ROUND_NEAREST_EVEN>>), grid, block, 0, st, L.A,
-                                   (const uint16_t *)in, (uint16_t *)out, op, k);
+                launch(LaneF32{});
+            else if (rounding != SQZ_ROUND_STOCHASTIC)
+                launch(LaneBF16<SQZ_ROUND_NEAREST_EVEN>{});
+            else if (F.N <= 0x100000000ull)
+                launch(LaneBF16<SQZ_ROUND_STOCHASTIC>{});
+            else if constexpr (P::LARGE)
+                launch(LaneBF16<SQZ_ROUND_STOCHASTIC, true>{});
             return 0;
         });
         const hipError_t e = hipGetLastError();

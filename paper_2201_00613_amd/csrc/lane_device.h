@@ -175,35 +175,45 @@ struct LanePlanOf {
 // FRAME blocks: the ring is the frame of that many blocks around the tile
 // (dense patterns: STEPS is the frame's width in cells); 0: the level-RL
 // subtrees that hold the cells next to the tile, which cover STEPS steps
-// (their side, one less for the triangles).
+// (their side, one less for the triangles).  LARGE: fractals of more than 2^32
+// cells run on it too.
 struct LaneTriangle : PatTriangle {
     static constexpr int J = 2, LANES = 832, RL = 4, STEPS = 15, FRAME = 0;
+    static constexpr bool LARGE = true;
 };
 struct LaneTrianglePaper : PatTrianglePaper {
     static constexpr int J = 2, LANES = 832, RL = 4, STEPS = 15, FRAME = 0;
+    static constexpr bool LARGE = true;
 };
 struct LaneVicsek : PatVicsek {
     static constexpr int J = 2, LANES = 704, RL = 3, STEPS = 27, FRAME = 0;
+    static constexpr bool LARGE = true;
 };
 struct LaneCarpet : PatCarpet {
     static constexpr int J = 2, LANES = 768, RL = 0, STEPS = 18, FRAME = 2;
+    static constexpr bool LARGE = true;
 };
 struct LaneCarpetSmall : PatCarpet {
     static constexpr int J = 2, LANES = 192, RL = 0, STEPS = 18, FRAME = 2;
+    static constexpr bool LARGE = false;
 };
 // Fractals that do not fill the chip, where a step's own latency counts: fewer
 // cells per lane.
 struct LaneTriangleFine : PatTriangle {
     static constexpr int J = 1, LANES = 960, RL = 4, STEPS = 15, FRAME = 0;
+    static constexpr bool LARGE = false;
 };
 struct LaneTrianglePaperFine : PatTrianglePaper {
     static constexpr int J = 1, LANES = 960, RL = 4, STEPS = 15, FRAME = 0;
+    static constexpr bool LARGE = false;
 };
 struct LaneVicsekFine : PatVicsek {
     static constexpr int J = 1, LANES = 768, RL = 3, STEPS = 27, FRAME = 0;
+    static constexpr bool LARGE = false;
 };
 struct LaneCarpetFine : PatCarpet {
     static constexpr int J = 1, LANES = 576, RL = 0, STEPS = 15, FRAME = 5;
+    static constexpr bool LARGE = false;
 };
 
 // Storage types: G in memory, binary32 in registers.
@@ -211,10 +221,11 @@ struct LaneF32 {
     using G = float;
     static constexpr int RND = -1;
 };
-template <int R>  // sqz_rounding
+template <int R, bool WIDE = false>  // sqz_rounding; WIDE: cell indices of more than 32 bits
 struct LaneBF16 {
     using G = uint16_t;
     static constexpr int RND = R;
+    static constexpr bool WIDX = WIDE;
 };
 
 // Memory layout of a workgroup.  Published values: column = lane, row =
@@ -248,12 +259,11 @@ struct LaneArgs {
 
 typedef uint32_t lane_u32x4 __attribute__((ext_vector_type(4), aligned(2)));
 
-// rand16 of a cell (cx: the cell's low 32 bits xor the term of its high bits;
-// sx: the terms of the seed and the step).  The finaliser's last x ^= x >> 16
+// rand16 of a cell (x: the cell's low 32 bits xor the term of its high bits,
+// plus sx, the terms of the seed and the step).  The finaliser's last x ^= x >> 16
 // leaves the upper 16 bits, all that is used, as they are.
-__device__ __forceinline__ uint32_t lane_rand16(uint32_t cx, uint32_t sx)
+__device__ __forceinline__ uint32_t lane_rand16(uint32_t x)
 {
-    uint32_t x = cx + sx;
     x ^= x >> 16;
     x *= 0x7FEB352Du;
     x ^= x >> 15;
@@ -261,8 +271,12 @@ __device__ __forceinline__ uint32_t lane_rand16(uint32_t cx, uint32_t sx)
     return x >> 16;
 }
 
+// base: lo + sx, of which cell I's argument is base + I where no cell index has
+// high bits (30 steps: level-12 triangle 22.3 -> 20.7 us, level 9 13.6 -> 12.9;
+// level-9 carpet, 100 steps 9.23 -> 9.17 ms); with high bits two to five
+// operations a cell take its place.
 struct LaneRand {
-    uint32_t lo, hx, hx1, sx;  // hx1: the term once lo + i has carried
+    uint32_t lo, hx, hx1, sx, base;  // hx1: the term once lo + i has carried
 };
 
 template <class P, class Op, int I, int NC, int NH, int ND>
@@ -284,11 +298,13 @@ __device__ __forceinline__ float lane_cell(const float (&x)[NC], const float (&h
     } else {
         uint32_t b = __float_as_uint(u);
         if constexpr (Op::RND == SQZ_ROUND_STOCHASTIC) {
-            if constexpr ((NC & (NC - 1)) == 0) {  // lo is a multiple of NC: lo + I = lo ^ I
-                b += lane_rand16((R.lo ^ R.hx) ^ (uint32_t)I, R.sx);
+            if constexpr (!Op::WIDX) {
+                b += lane_rand16(R.base + (uint32_t)I);
+            } else if constexpr ((NC & (NC - 1)) == 0) {  // lo is a multiple of NC: lo + I = lo ^ I
+                b += lane_rand16(((R.lo ^ R.hx) ^ (uint32_t)I) + R.sx);
             } else {
                 const uint32_t lo = R.lo + I;
-                b += lane_rand16(lo ^ (lo < (uint32_t)I ? R.hx1 : R.hx), R.sx);
+                b += lane_rand16((lo ^ (lo < (uint32_t)I ? R.hx1 : R.hx)) + R.sx);
             }
         } else {
             b += 0x7FFFu + ((b >> 16) & 1u);
@@ -457,6 +473,7 @@ __device__ __forceinline__ void lane_tile(const LaneArgs &A, const typename Op::
         if constexpr (Op::RND == SQZ_ROUND_STOCHASTIC) {
             asm volatile("" : "+v"(R.lo));  // or the per-cell terms are hoisted into a register each
             R.sx = (uint32_t)op.seed * 0x9E3779B9u + (uint32_t)(op.seed >> 32) + (uint32_t)(op.step + s) * 0x7FEB352Du;
+            R.base = R.lo + R.sx;
         }
         lane_cells<P, Op, 0>(x, h, nd, op.coef, R, y, std::make_index_sequence<N0>{});
         if constexpr (C::DB == 1) __syncthreads();  // every lane has read this step's halo

@@ -70,3 +70,18 @@ def test_infinities_and_nan(name, r):
     got = F.diffuse_run(u.clone(), torch.empty_like(u), 4, 0.1)
     assert torch.equal(torch.isnan(got), torch.isnan(x))
     assert torch.equal(torch.nan_to_num(got, 0.0), torch.nan_to_num(x, 0.0))
+
+
+def test_cells_beyond_32_bits():
+    """10.46e9 cells: the rounding hash of cells on both sides of index 2^32."""
+    torch = torch_or_skip()
+    F = gpu_fractal("triangle", 21)
+    a = torch.empty(F.cells, dtype=torch.uint16, device="cuda")
+    a.view(torch.bfloat16).uniform_(-0.5, 0.5, generator=torch.Generator("cuda").manual_seed(5))
+    x, y, b = a.clone(), torch.empty_like(a), torch.empty_like(a)
+    for s in range(3):
+        F.diffuse_step(x, y, 0.1, dtype="bf16", step=7 + s, rounding="stochastic", impl="xtile", seed=9)
+        x, y = y, x
+    res = F.diffuse_run(a, b, 3, 0.1, dtype="bf16", first_step=7, rounding="stochastic", seed=9)
+    for at in range(0, F.cells, 1 << 30):  # in pieces: comparison needs a copy
+        assert torch.equal(res[at:at + (1 << 30)].view(torch.int16), x[at:at + (1 << 30)].view(torch.int16)), at
