@@ -375,7 +375,7 @@ sqz_status sqz_compact_run_form(const sqz_fractal *f, sqz_run_form form, uint8_t
     if (aligned && slice_available(f->h) && steps >= 2)
         return slice_run_launches(f->h, d_a, d_b, steps, (hipStream_t)stream);
     if (f->h.gbox && steps >= 2) {
-        const std::vector<int> plan = plan_launches(steps, gbox_steps_per_launch(f->h));
+        const std::vector<int> plan = plan_launches(steps, gbox_steps_per_launch(f->h, steps));
         for (size_t i = 0; i < plan.size() && st == SQZ_OK; ++i) {
             const uint8_t *in = (i & 1) ? d_b : d_a;
             uint8_t *out = (i & 1) ? d_a : d_b;

@@ -220,7 +220,8 @@ sqz_status lane_diffuse_run(const FractalHost &F, int dtype, float coef, int rou
 sqz_status gbox_prepare(FractalHost &F);  // after the other Life kernels
 void gbox_release(FractalHost &F);
 bool gbox_one_step(const FractalHost &F);  // a single step is faster with it too
-int gbox_steps_per_launch(const FractalHost &F);  // 0: any number (one tile); -1: no bit box
+// most steps per launch of a run of `steps`: 0: any number (one tile); -1: no bit box
+int gbox_steps_per_launch(const FractalHost &F, int32_t steps);
 sqz_status launch_life_gbox(const FractalHost &F, const uint8_t *in, uint8_t *out, int steps, hipStream_t st);
 
 // Batched Life (batch.hip)

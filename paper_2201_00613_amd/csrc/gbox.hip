@@ -14,8 +14,10 @@
 //
 // The expanded-tile kernel that ran these patterns before (xtile_device.h)
 // holds a byte per position and takes at most three steps per launch.
-// Measured (s = 4, k = 10): 21 steps of 1e6 cells 79.8 -> 28.2 us (three
-// launches of seven, bound by their latency), of 1e8 cells 3.50 -> 0.89 ms.
+// Measured (s = 4, k = 10): 21 steps of 1e6 cells 79.8 -> 19.6 us (one launch,
+// bound by the latency of its steps), of 1e8 cells 3.50 -> 0.89 ms.  Rows that
+// the remaining steps no longer reach are computed all the same: leaving them
+// out costs an index division a step (16 steps of 1e6 cells 18.3 -> 19.2 us).
 #include <algorithm>
 #include <vector>
 
@@ -24,7 +26,9 @@
 
 namespace sqz {
 
-constexpr int kGbMaxBorder = 16;
+constexpr int kGbBorder = 16, kGbMaxBorder = 32;
+constexpr uint64_t kGbFewTiles = 2048;  // at most two tiles per SIMD: a tile's own time counts
+constexpr int kGbFewNT = 256, kGbFewStrip = 2;
 
 struct GboxArgs {
     uint32_t ntiles, KM;       // tiles, cells per tile
@@ -37,8 +41,9 @@ struct GboxArgs {
 };
 
 struct GboxConfig {
-    int K;  // steps per launch (0: one tile, any number)
-    GboxArgs A;
+    int K;          // steps per launch (0: one tile, any number)
+    int K2;         // of the tables with the wider border (0: none)
+    GboxArgs A, A2;
     void *d_tab, *d_coarse;
 };
 
@@ -178,52 +183,69 @@ sqz_status gbox_prepare(FractalHost &F)
     // cost more in border cells than it saves in launches); around a single
     // tile one cell, always empty (a column between the row's ends).
     const bool one = F.r == M;
-    const int D = one ? 1 : std::min<int>({kGbMaxBorder, (int)B, std::max(4, (int)B / 4)});
+    const int D = one ? 1 : std::min<int>({kGbBorder, (int)B, std::max(4, (int)B / 4)});
     GboxConfig *C = new GboxConfig();
-    GboxArgs &A = C->A;
     C->K = one ? 0 : D;
-    A.ntiles = (uint32_t)nt;
-    A.KM = (uint32_t)KM;
-    A.B = (uint32_t)B;
-    A.D = (uint32_t)D;
-    A.W = (A.B + 2 * A.D + 31) / 32;
-    A.rows = A.B + 2 * A.D;
-    std::vector<XRingSlot> ring;
-    std::vector<uint32_t> start;
-    std::vector<uint16_t> lam;
-    std::vector<uint8_t> own;
-    const uint32_t P = 32 * A.W;
-    xtile_layer_tables(F, M, D, P, A.rows, ring, start, lam, own);
-    for (int d = 0; d <= D; ++d) A.ring[d] = start[d];
-    std::vector<uint32_t> slot(ring.size()), member((size_t)A.rows * A.W, 0);
-    for (size_t i = 0; i < own.size(); ++i)
-        if (own[i]) member[i / 32] |= 1u << (i % 32);
-    for (size_t i = 0; i < ring.size(); ++i) {
-        slot[i] = ring[i].pos | (ring[i].info >> 16) << 16 | (ring[i].info & 0xFFFFu) << 19;
-        member[ring[i].pos / 32] |= 1u << (ring[i].pos % 32);
-    }
-    lam.resize((lam.size() + 3) / 4 * 4, 0);  // read four at a time
-    const size_t o_slot = lam.size() * 2, o_mem = o_slot + slot.size() * 4, total = o_mem + member.size() * 4;
-    std::vector<uint8_t> blob(total);
-    std::copy(lam.begin(), lam.end(), reinterpret_cast<uint16_t *>(blob.data()));
-    std::copy(slot.begin(), slot.end(), reinterpret_cast<uint32_t *>(blob.data() + o_slot));
-    std::copy(member.begin(), member.end(), reinterpret_cast<uint32_t *>(blob.data() + o_mem));
-    sqz_status st = build_map_params(F, F.r - M, A.Pc, &C->d_coarse);
+    // Few tiles: a second set of tables with the widest border (of more than
+    // D cells) whose box the lanes still update in one turn.
+    if (!one && nt <= kGbFewTiles)
+        for (int d = D + 1; d <= std::min<int>(kGbMaxBorder, (int)B); ++d)
+            if (((int)B + 2 * d + 31) / 32 * gb_rows((uint32_t)B + 2 * d, kGbFewStrip) / kGbFewStrip <= kGbFewNT) C->K2 = d;
+    std::vector<uint8_t> blob;
+    size_t at[2][3];  // offsets of pos, slot, member
+    auto build = [&](GboxArgs &A, int border, size_t (&o)[3]) {
+        A.ntiles = (uint32_t)nt;
+        A.KM = (uint32_t)KM;
+        A.B = (uint32_t)B;
+        A.D = (uint32_t)border;
+        A.W = (A.B + 2 * A.D + 31) / 32;
+        A.rows = A.B + 2 * A.D;
+        std::vector<XRingSlot> ring;
+        std::vector<uint32_t> start;
+        std::vector<uint16_t> lam;
+        std::vector<uint8_t> own;
+        const uint32_t P = 32 * A.W;
+        xtile_layer_tables(F, M, border, P, A.rows, ring, start, lam, own);
+        for (int d = 0; d <= border; ++d) A.ring[d] = start[d];
+        std::vector<uint32_t> slot(ring.size()), member((size_t)A.rows * A.W, 0);
+        for (size_t i = 0; i < own.size(); ++i)
+            if (own[i]) member[i / 32] |= 1u << (i % 32);
+        for (size_t i = 0; i < ring.size(); ++i) {
+            slot[i] = ring[i].pos | (ring[i].info >> 16) << 16 | (ring[i].info & 0xFFFFu) << 19;
+            member[ring[i].pos / 32] |= 1u << (ring[i].pos % 32);
+        }
+        lam.resize((lam.size() + 7) / 8 * 8, 0);  // read four at a time
+        o[0] = (blob.size() + 15) / 16 * 16;
+        o[1] = o[0] + lam.size() * 2;
+        o[2] = o[1] + slot.size() * 4;
+        blob.resize(o[2] + member.size() * 4);
+        std::copy(lam.begin(), lam.end(), reinterpret_cast<uint16_t *>(blob.data() + o[0]));
+        std::copy(slot.begin(), slot.end(), reinterpret_cast<uint32_t *>(blob.data() + o[1]));
+        std::copy(member.begin(), member.end(), reinterpret_cast<uint32_t *>(blob.data() + o[2]));
+    };
+    build(C->A, D, at[0]);
+    if (C->K2) build(C->A2, C->K2, at[1]);
+    sqz_status st = build_map_params(F, F.r - M, C->A.Pc, &C->d_coarse);
     if (st != SQZ_OK) {
         delete C;
         return st;
     }
-    hipError_t e = hipMalloc(&C->d_tab, total);
-    if (e == hipSuccess) e = hipMemcpy(C->d_tab, blob.data(), total, hipMemcpyHostToDevice);
+    hipError_t e = hipMalloc(&C->d_tab, blob.size());
+    if (e == hipSuccess) e = hipMemcpy(C->d_tab, blob.data(), blob.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) {
         if (C->d_tab) (void)hipFree(C->d_tab);
         (void)hipFree(C->d_coarse);
         delete C;
         return hip_error(e, "bit box tables");
     }
-    A.pos = (const uint16_t *)C->d_tab;
-    A.slot = (const uint32_t *)((const uint8_t *)C->d_tab + o_slot);
-    A.member = (const uint32_t *)((const uint8_t *)C->d_tab + o_mem);
+    C->A2.Pc = C->A.Pc;
+    for (int i = 0; i < (C->K2 ? 2 : 1); ++i) {
+        GboxArgs &A = i ? C->A2 : C->A;
+        const uint8_t *t = (const uint8_t *)C->d_tab;
+        A.pos = (const uint16_t *)(t + at[i][0]);
+        A.slot = (const uint32_t *)(t + at[i][1]);
+        A.member = (const uint32_t *)(t + at[i][2]);
+    }
     F.gbox = C;
     return SQZ_OK;
 }
@@ -237,19 +259,32 @@ bool gbox_one_step(const FractalHost &F)
     return F.gbox && 2ull * F.gbox->A.KM <= (uint64_t)F.gbox->A.B * F.gbox->A.B;
 }
 
-int gbox_steps_per_launch(const FractalHost &F) { return F.gbox ? F.gbox->K : -1; }
+// Most steps per launch of a run: those of the wider border where that takes
+// fewer launches. A step on its larger box is slower, a launch costs more than
+// that (s = 4, k = 10, 1e6 cells, the usual border and the wider one throughout:
+// 16 steps, two launches with either, 18.3 and 21.7 us; 21 steps, three and one,
+// 25.5 and 19.6; 50 steps, four and two, 46.6 and 45.8).
+int gbox_steps_per_launch(const FractalHost &F, int32_t steps)
+{
+    if (!F.gbox) return -1;
+    const GboxConfig &C = *F.gbox;
+    return C.K2 && plan_launches(steps, C.K2).size() < plan_launches(steps, C.K).size() ? C.K2 : C.K;
+}
 
 sqz_status launch_life_gbox(const FractalHost &F, const uint8_t *in, uint8_t *out, int steps, hipStream_t st)
 {
     const GboxConfig &C = *F.gbox;
-    if (steps < 1 || (C.K && steps > C.K))
-        return set_error(SQZ_ERR_UNSUPPORTED, "%d steps per launch exceed the border of %d cells", steps, C.K);
-    if (C.A.ntiles <= 2048) {  // at most two tiles per SIMD
-        const size_t lds = (gb_lds(C.A.W, gb_rows(C.A.rows, 2)) + 1) * sizeof(uint32_t);
-        hipLaunchKernelGGL((k_life_gbox<2, 256>), dim3(C.A.ntiles), dim3(256), lds, st, C.A, in, out, steps);
+    if (steps < 1 || (C.K && steps > std::max(C.K, C.K2)))
+        return set_error(SQZ_ERR_UNSUPPORTED, "%d steps per launch exceed the border of %d cells", steps,
+                         std::max(C.K, C.K2));
+    const GboxArgs &A = C.K && steps > C.K ? C.A2 : C.A;
+    if (A.ntiles <= kGbFewTiles) {
+        const size_t lds = (gb_lds(A.W, gb_rows(A.rows, kGbFewStrip)) + 1) * sizeof(uint32_t);
+        hipLaunchKernelGGL((k_life_gbox<kGbFewStrip, kGbFewNT>), dim3(A.ntiles), dim3(kGbFewNT), lds, st, A, in, out,
+                           steps);
     } else {
-        const size_t lds = (gb_lds(C.A.W, gb_rows(C.A.rows, 5)) + 1) * sizeof(uint32_t);
-        hipLaunchKernelGGL((k_life_gbox<5, 64>), dim3(C.A.ntiles), dim3(64), lds, st, C.A, in, out, steps);
+        const size_t lds = (gb_lds(A.W, gb_rows(A.rows, 5)) + 1) * sizeof(uint32_t);
+        hipLaunchKernelGGL((k_life_gbox<5, 64>), dim3(A.ntiles), dim3(64), lds, st, A, in, out, steps);
     }
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? SQZ_OK : hip_error(e, "compact run (bit box) launch");
