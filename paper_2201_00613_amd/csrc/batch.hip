@@ -356,12 +356,6 @@ struct BatchGroup {
     uint64_t *d_base, *d_tstart;
 };
 
-// A branch of a captured run.
-struct BatchBranch {
-    hipStream_t stream;
-    hipEvent_t done;
-};
-
 struct BatchHost {
     // instances with a tiled kernel run as one launch per pattern group
     // (tiled_form 0), one persistent launch over all of them (1) or one launch
@@ -393,8 +387,6 @@ struct BatchHost {
     unsigned wg_per_cu, max_wg_per_cu;
     std::string key;
     hipStream_t cap;
-    hipEvent_t fork;
-    std::vector<BatchBranch> branches;
     hipGraphExec_t gexec;
     const void *g_a, *g_b;
     int32_t g_steps;
@@ -491,7 +483,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                 T.x = bitbox_args(F);
                 T.units = T.x.ntiles;
                 T.unit_cells = T.x.tile;
-                H->tlds = std::max<size_t>(H->tlds, kBxLds * 4);
+                                H->tlds = std::max<size_t>(H->tlds, kBxLds * 4);
             } else {
                 SliceConfig *&C = slice_of[&F];
                 if (!C) {
@@ -614,7 +606,6 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
     H->d_inst = nullptr;
     H->d_cost_start = nullptr;
     H->cap = nullptr;
-    H->fork = nullptr;
     H->gexec = nullptr;
     e = hipMalloc(&H->d_inst, sizeof(BatchInst) * count);
     if (e == hipSuccess) e = hipMalloc(&H->d_cost_start, sizeof(uint64_t) * (count + 1));
@@ -718,13 +709,6 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
     }
     if (e == hipSuccess) e = upload_costs(H);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&H->cap, hipStreamNonBlocking);
-    if (e == hipSuccess) e = hipEventCreateWithFlags(&H->fork, hipEventDisableTiming);
-    // launches fork into at most a branch per group and one for the rest, the first on `cap`
-    H->branches.resize(H->groups.size(), BatchBranch{nullptr, nullptr});
-    for (BatchBranch &b : H->branches) {
-        if (e == hipSuccess) e = hipStreamCreateWithFlags(&b.stream, hipStreamNonBlocking);
-        if (e == hipSuccess) e = hipEventCreateWithFlags(&b.done, hipEventDisableTiming);
-    }
     int per_cu = 0;
     if (e == hipSuccess) {
         switch (H->K) {
@@ -753,11 +737,6 @@ void batch_destroy(BatchHost *H)
     if (!H) return;
     if (H->gexec) (void)hipGraphExecDestroy(H->gexec);
     if (H->cap) (void)hipStreamDestroy(H->cap);
-    if (H->fork) (void)hipEventDestroy(H->fork);
-    for (const BatchBranch &b : H->branches) {
-        if (b.stream) (void)hipStreamDestroy(b.stream);
-        if (b.done) (void)hipEventDestroy(b.done);
-    }
     for (SliceConfig *S : H->slices) slice_free(S);
     (void)hipFree(H->d_inst);
     (void)hipFree(H->d_cost_start);
@@ -848,67 +827,37 @@ static sqz_status launch_tiled(const BatchHost *H, int form, unsigned wg_per_cu,
     return e == hipSuccess ? SQZ_OK : hip_error(e, "batch tiled launch");
 }
 
-// All launches of `steps` steps, in chains that touch different instances: each
-// pattern group (or the launch over all tiled instances) and the expanded-tile
-// / thread-level launch follow their own plans (each with the parity of
-// `steps`, so every result lands in the same buffer).  Forked (a capture of
-// st), each chain is a branch of the graph, so that one group's loads run
-// under another's steps and a group too small to fill the chip leaves no idle
-// CUs (50 steps, one chain -> branches: 512 mixed fractals 1234 -> 1171 us, 64
-// 252 -> 197, 8 152 -> 118).
-static sqz_status launch_all(const BatchHost *H, const uint8_t *a, const uint8_t *b, int32_t steps, hipStream_t st,
-                             bool forked)
+// All launches of `steps` steps: the tiled launch and the expanded-tile /
+// thread-level launch follow their own plans (each with the parity of
+// `steps`, so every result lands in the same buffer).
+static sqz_status launch_all(const BatchHost *H, const uint8_t *a, const uint8_t *b, int32_t steps, hipStream_t st)
 {
+    sqz_status s2 = SQZ_OK;
     uint8_t *const A = const_cast<uint8_t *>(a), *const B = const_cast<uint8_t *>(b);
-    size_t used = 0;  // branches in use
-    hipError_t e = forked ? hipEventRecord(H->fork, st) : hipSuccess;
-    // launch(in, out, steps, stream): one launch of a chain that takes at most K steps each
-    auto chain = [&](int K, bool first, auto &&launch) {
-        if (e != hipSuccess) return hip_error(e, "batch capture");
-        hipStream_t s = st;
-        if (forked && !first) {
-            s = H->branches[used++].stream;
-            e = hipStreamWaitEvent(s, H->fork, 0);
-            if (e != hipSuccess) return hip_error(e, "batch capture");
-        }
-        const std::vector<int> plan = plan_launches(steps, K);
-        for (size_t i = 0; i < plan.size(); ++i) {
-            const sqz_status r = launch((i & 1) ? B : A, (i & 1) ? A : B, plan[i], s);
-            if (r != SQZ_OK) return r;
-        }
-        return SQZ_OK;
-    };
-    sqz_status r = SQZ_OK;
-    bool first = true;
     if (!H->tiled.empty() && H->tiled_form != 0) {
-        r = chain(H->Kt, true, [&](const uint8_t *in, uint8_t *out, int k, hipStream_t s) {
-            return launch_tiled(H, H->tiled_form, H->twg, in, out, k, s);
-        });
-        first = false;
+        const std::vector<int> plan = plan_launches(steps, H->Kt);
+        for (size_t i = 0; i < plan.size() && s2 == SQZ_OK; ++i)
+            s2 = launch_tiled(H, H->tiled_form, H->twg, (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
     } else {
-        for (const BatchGroup &G : H->groups) {
-            if (r != SQZ_OK) break;
+        for (size_t g = 0; g < H->groups.size() && s2 == SQZ_OK; ++g) {
             // the most the tiles can take, unless fewer were chosen
-            r = chain(G.K < G.K_max ? G.K : G.K_full, first,
-                      [&](const uint8_t *in, uint8_t *out, int k, hipStream_t s) { return launch_group(G, in, out, k, s); });
-            first = false;
+            const BatchGroup &G = H->groups[g];
+            const std::vector<int> plan = plan_launches(steps, G.K < G.K_max ? G.K : G.K_full);
+            for (size_t i = 0; i < plan.size() && s2 == SQZ_OK; ++i)
+                s2 = launch_group(H->groups[g], (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
         }
     }
-    if (H->has_rest && r == SQZ_OK)
-        r = chain(H->K, first, [&](const uint8_t *in, uint8_t *out, int k, hipStream_t s) {
-            return launch_batch(H, H->wg_per_cu, in, out, k, s);
-        });
-    for (size_t i = 0; i < used && e == hipSuccess; ++i) {
-        e = hipEventRecord(H->branches[i].done, H->branches[i].stream);
-        if (e == hipSuccess) e = hipStreamWaitEvent(st, H->branches[i].done, 0);
+    if (H->has_rest) {
+        const std::vector<int> plan = plan_launches(steps, H->K);
+        for (size_t i = 0; i < plan.size() && s2 == SQZ_OK; ++i)
+            s2 = launch_batch(H, H->wg_per_cu, (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
     }
-    if (r == SQZ_OK && e != hipSuccess) r = hip_error(e, "batch capture");
-    return r;
+    return s2;
 }
 
 sqz_status batch_step(const BatchHost *H, const uint8_t *in, uint8_t *out, hipStream_t st)
 {
-    return launch_all(H, in, out, 1, st, false);
+    return launch_all(H, in, out, 1, st);
 }
 
 sqz_status batch_run(BatchHost *H, uint8_t *a, uint8_t *b, int32_t steps, hipStream_t st)
@@ -922,7 +871,7 @@ sqz_status batch_run(BatchHost *H, uint8_t *a, uint8_t *b, int32_t steps, hipStr
         }
         hipError_t e = hipStreamBeginCapture(H->cap, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return hip_error(e, "hipStreamBeginCapture");
-        const sqz_status s2 = launch_all(H, a, b, steps, H->cap, true);
+        const sqz_status s2 = launch_all(H, a, b, steps, H->cap);
         hipGraph_t g = nullptr;
         e = hipStreamEndCapture(H->cap, &g);
         if (s2 != SQZ_OK) {
