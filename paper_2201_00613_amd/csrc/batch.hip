@@ -483,7 +483,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                 T.x = bitbox_args(F);
                 T.units = T.x.ntiles;
                 T.unit_cells = T.x.tile;
-                                H->tlds = std::max<size_t>(H->tlds, kBxLds * 4);
+                H->tlds = std::max<size_t>(H->tlds, kBxLds * 4);
             } else {
                 SliceConfig *&C = slice_of[&F];
                 if (!C) {

@@ -30,9 +30,9 @@
 // them moving bits.  Here the triangle needs 45 per 9 words (J = 2) or 121 per
 // 27 words (J = 3), each word 27 cells: 0.17-0.19 instructions per cell.
 // Measured against those blocks: level-16 triangle, 100 steps, all tiles
-// resident: 333 -> 70 us; level 20, 20 steps: two launches of ten (4.68 ms,
+// resident: 333 -> 67 us; level 20, 20 steps: two launches of ten (4.68 ms,
 // bound by vector issue) -> one in place (1.51 ms, 4.6 TB/s of loads and
-// stores, the rate of a large copy); level 13, 25 steps: 23.5 -> 14.3 us;
+// stores, the rate of a large copy); level 13, 25 steps: 23.5 -> 14.1 us;
 // level-9 Vicsek cross, 37 steps: 43.4 -> 17.5 us.
 #pragma once
 
@@ -50,10 +50,10 @@ namespace sqz {
 // less than their side for the triangles, whose next subtrees touch at a
 // corner, their side for the Vicsek cross.  *Small: subtiles of at most 243 (625) words,
 // always loaded four cells a lane (fewer registers and less LDS, so more
-// workgroups per CU: batches).
+// workgroups per CU: batches).  PARTS: see publish() in slice_tile.
 struct SliceTri : PatTriangle {
     static constexpr int B = 3, RL = 5, STEPS = 31, J = 2, LMAX = 8;
-    static constexpr bool SMALL = false;
+    static constexpr bool SMALL = false, PARTS = true;
 };
 struct SliceTriSmall : SliceTri {
     static constexpr int LMAX = 5;
@@ -61,10 +61,11 @@ struct SliceTriSmall : SliceTri {
 };
 struct SliceTriWide : SliceTri {
     static constexpr int J = 3;
+    static constexpr bool PARTS = false;
 };
 struct SlicePaper : PatTrianglePaper {
     static constexpr int B = 3, RL = 5, STEPS = 31, J = 2, LMAX = 8;
-    static constexpr bool SMALL = false;
+    static constexpr bool SMALL = false, PARTS = true;
 };
 struct SlicePaperSmall : SlicePaper {
     static constexpr int LMAX = 5;
@@ -72,14 +73,15 @@ struct SlicePaperSmall : SlicePaper {
 };
 struct SlicePaperWide : SlicePaper {
     static constexpr int J = 3;
+    static constexpr bool PARTS = false;
 };
 struct SliceVicsek : PatVicsek {
     static constexpr int B = 2, RL = 3, STEPS = 27, J = 1, LMAX = 5;
-    static constexpr bool SMALL = false;
+    static constexpr bool SMALL = false, PARTS = false;
 };
 struct SliceVicsekSmall : SliceVicsek {
     static constexpr int LMAX = 4;
-    static constexpr bool SMALL = true;
+    static constexpr bool SMALL = true, PARTS = true;
 };
 struct SliceVicsekWide : SliceVicsek {
     static constexpr int J = 2;
@@ -232,23 +234,32 @@ __device__ __forceinline__ uint32_t bop3(uint32_t a, uint32_t b, uint32_t c)
 __device__ __forceinline__ uint32_t xor3(uint32_t a, uint32_t b, uint32_t c) { return bop3<0x96>(a, b, c); }
 __device__ __forceinline__ uint32_t maj3(uint32_t a, uint32_t b, uint32_t c) { return bop3<0xE8>(a, b, c); }
 
+// Sums of a cell's first neighbour words, which lie in its block.
+struct SlicePart {
+    uint32_t a, b, c;
+};
+
+// Of D neighbours the first IN in the block: how many the part covers (all of
+// them: the part is the new state).
+constexpr int slice_known(int D, int IN) { return IN == D ? D : (IN >= 5 ? 5 : (IN >= 3 ? 3 : 0)); }
+
 // B3/S23 of a word x with D neighbour words n: alive' = (count == 3) | (x & count == 2), that is exactly
-// one weight-2 carry and (odd rest or alive).
-template <int D>
-__device__ __forceinline__ uint32_t slice_rule(uint32_t x, const uint32_t *n)
+// one weight-2 carry and (odd rest or alive).  KNOWN = 3 or 5: the sums of that many neighbours are in `part`.
+template <int D, int KNOWN = 0>
+__device__ __forceinline__ uint32_t slice_rule(uint32_t x, const uint32_t *n, const SlicePart &part = SlicePart{})
 {
     if constexpr (D < 2) {
         return 0u;
     } else if constexpr (D == 2) {
         return bop3<0x80>(n[0], n[1], x);
     } else {
-        const uint32_t s1 = xor3(n[0], n[1], n[2]), c1 = maj3(n[0], n[1], n[2]);
+        const uint32_t s1 = KNOWN >= 3 ? part.a : xor3(n[0], n[1], n[2]), c1 = KNOWN >= 3 ? part.b : maj3(n[0], n[1], n[2]);
         if constexpr (D == 3) {
             return bop3<0xE0>(c1, s1, x);  // c1 & (s1 | x)
         } else if constexpr (D == 4) {
             return bop3<0x78>(c1, s1, n[3]) & bop3<0xBE>(s1, n[3], x);  // (c1 ^ s1 n3) & ((s1 ^ n3) | x)
         } else {
-            const uint32_t s2 = xor3(s1, n[3], n[4]), c2 = maj3(s1, n[3], n[4]);
+            const uint32_t s2 = KNOWN == 5 ? part.a : xor3(s1, n[3], n[4]), c2 = KNOWN == 5 ? part.c : maj3(s1, n[3], n[4]);
             if constexpr (D == 5) {
                 return bop3<0x28>(c1, c2, s2 | x);  // (c1 ^ c2) & (s2 | x)
             } else if constexpr (D == 6) {
@@ -262,24 +273,71 @@ __device__ __forceinline__ uint32_t slice_rule(uint32_t x, const uint32_t *n)
     }
 }
 
-template <class P, int J, int I, int NC, int NH>
-__device__ __forceinline__ uint32_t slice_cell(const uint32_t (&x)[NC], const uint32_t (&h)[NH])
+template <class P, int J, int I>
+constexpr int slice_in_block()
 {
     using PO = SlicePlanOf<P, J>;
-    constexpr int D = PO::value.deg[I];
-    uint32_t n[8];
-#pragma unroll
-    for (int d = 0; d < D; ++d) {
-        const int q = PO::value.nb[I][d];
-        n[d] = q < NC ? x[q < NC ? q : 0] : h[q < NC ? 0 : q - NC];
-    }
-    return slice_rule<D>(x[I], n);
+    int in = 0;
+    for (int d = 0; d < PO::value.deg[I]; ++d) in += PO::value.nb[I][d] < PO::value.nc;
+    return in;
 }
 
-template <class P, int J, int NC, int NH, size_t... I>
-__device__ __forceinline__ void slice_step(uint32_t (&x)[NC], const uint32_t (&h)[NH], std::index_sequence<I...>)
+// The part of cell I from its own block's words.
+template <class P, int J, int I, int NC>
+__device__ __forceinline__ SlicePart slice_part(const uint32_t (&x)[NC])
 {
-    const uint32_t y[] = {slice_cell<P, J, (int)I>(x, h)...};
+    using PO = SlicePlanOf<P, J>;
+    constexpr int D = PO::value.deg[I], KNOWN = slice_known(D, slice_in_block<P, J, I>());
+    uint32_t n[8];
+#pragma unroll
+    for (int d = 0; d < KNOWN; ++d) n[d] = x[PO::value.nb[I][d]];
+    SlicePart p{};
+    if constexpr (KNOWN == D) {
+        p.a = slice_rule<D>(x[I], n);
+    } else if constexpr (KNOWN >= 3) {
+        p.a = xor3(n[0], n[1], n[2]);
+        p.b = maj3(n[0], n[1], n[2]);
+        if constexpr (KNOWN == 5) {
+            p.c = maj3(p.a, n[3], n[4]);
+            p.a = xor3(p.a, n[3], n[4]);
+        }
+    }
+    // computed here, not where it is used
+    if constexpr (KNOWN > 0) asm volatile("" : "+v"(p.a));
+    if constexpr (KNOWN > 0 && KNOWN != D) asm volatile("" : "+v"(p.b));
+    if constexpr (KNOWN == 5 && KNOWN != D) asm volatile("" : "+v"(p.c));
+    return p;
+}
+
+template <class P, int J, int I, bool PARTS, int NC, int NH>
+__device__ __forceinline__ uint32_t slice_cell(const uint32_t (&x)[NC], const uint32_t (&h)[NH], const SlicePart &part)
+{
+    using PO = SlicePlanOf<P, J>;
+    constexpr int D = PO::value.deg[I], KNOWN = PARTS ? slice_known(D, slice_in_block<P, J, I>()) : 0;
+    if constexpr (PARTS && KNOWN == D) {
+        return part.a;
+    } else {
+        uint32_t n[8];
+#pragma unroll
+        for (int d = 0; d < D; ++d) {
+            const int q = PO::value.nb[I][d];
+            n[d] = q < NC ? x[q < NC ? q : 0] : h[q < NC ? 0 : q - NC];
+        }
+        return slice_rule<D, KNOWN>(x[I], n, part);
+    }
+}
+
+template <class P, int J, int NC, size_t... I>
+__device__ __forceinline__ void slice_parts(const uint32_t (&x)[NC], SlicePart (&part)[NC], std::index_sequence<I...>)
+{
+    ((part[I] = slice_part<P, J, (int)I>(x)), ...);
+}
+
+template <class P, int J, bool PARTS, int NC, int NH, size_t... I>
+__device__ __forceinline__ void slice_step(uint32_t (&x)[NC], const uint32_t (&h)[NH], const SlicePart (&part)[NC],
+                                           std::index_sequence<I...>)
+{
+    const uint32_t y[] = {slice_cell<P, J, (int)I, PARTS>(x, h, part[I])...};
     ((x[I] = y[I]), ...);
 }
 
@@ -506,8 +564,17 @@ __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in
 
     char *const lds = reinterpret_cast<char *>(sm);
     char *const ex = lds + C::EX0 + blk * C::PITCH;
+    SlicePart part[NC];
     // Publish into buffer p: the block's cells that other blocks read, then
     // (first wave, whose lanes hold every source) the subtile and ring halos.
+    // The other waves wait for that chain of LDS accesses and ballots: with
+    // PARTS they meanwhile add up each cell's neighbours in its own block, and
+    // a step's second half is the halo words alone (100 steps: level-16
+    // triangle 69.7 -> 66.3 us, level 8 34.8 -> 33.5, level-6 Vicsek 28.6 -> 27.2).
+    // Not where the sums cost more registers than they save time (27-cell
+    // blocks; level-10 Vicsek 45.5 -> 47.6).  In the first wave they come after
+    // the chain: between its reads and ballots they lengthen it (level 8 36.0),
+    // and so does raised priority for that wave (level 16 69.8).
     auto publish = [&](auto pp) {
         constexpr uint32_t O = decltype(pp)::value * C::BUF;
         if (active) {
@@ -530,13 +597,14 @@ __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in
             if (tid >= (uint32_t)NH) w = (uint32_t)(b[NPT] >> ((tid - NH) * kSliceMaxRing & 63u)) & 0xFFu;
             if (tid < 2u * NH) *reinterpret_cast<uint32_t *>(lds + O + C::HALO + 4 * tid) = w;
         }
+        if constexpr (P::PARTS) slice_parts<P, J>(x, part, std::make_index_sequence<NC>{});
     };
     auto advance = [&](auto pp) {
         constexpr uint32_t O = decltype(pp)::value * C::BUF;
         uint32_t h[NH];
 #pragma unroll
         for (int q = 0; q < NH; ++q) h[q] = *reinterpret_cast<const uint32_t *>(lds + O + ha[q]);
-        slice_step<P, J>(x, h, std::make_index_sequence<NC>{});
+        slice_step<P, J, P::PARTS>(x, h, part, std::make_index_sequence<NC>{});
     };
     uint32_t nx = 0;  // exchanges done
     auto exchange = [&]() {
