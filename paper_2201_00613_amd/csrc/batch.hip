@@ -204,8 +204,8 @@ __device__ __forceinline__ uint32_t group_instance(const GroupArgs &G, uint64_t 
 // their ring) and level-6 Vicsek crosses, about 2.5 and 6 KB of LDS and 80
 // registers, six waves per SIMD of independent workgroups; up to 31 (27) steps
 // a launch.  512 mixed fractals, 50 steps: 3.86 ms with the 27-cell blocks
-// (five launches of ten, bound by vector issue) -> 1.41 ms, of which the
-// carpets' bit rows take 0.55.
+// (five launches of ten, bound by vector issue) -> 1.22 ms, of which the
+// carpets' bit rows take 0.40.
 template <class P>
 __global__ void __launch_bounds__(SliceCfg<P>::LANES)
 k_batch_slice(GroupArgs G, const uint8_t *in, uint8_t *out, int32_t steps)
@@ -216,6 +216,23 @@ k_batch_slice(GroupArgs G, const uint8_t *in, uint8_t *out, int32_t steps)
     const SliceArgs A = reinterpret_cast<const SliceArgs *>(G.args)[i];
     const uint64_t base = G.base[i];
     slice_tile<P, false>(A, in + base, out + base, b - G.tstart[i], SliceRing{in + base, false}, steps, SliceRes{}, sm);
+}
+
+// A launch of one step: the bit-sliced blocks, whose loads and stores are 16
+// bytes wide, where the small tiles above move four a lane (mixed fractals, one
+// step: those tiles 230 / 137 / 62 us for 256 / 128 / 64 of them,
+// this 196 / 120 / 60).
+template <class Pat>
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(8)))
+k_batch_tile(GroupArgs G, const uint8_t *__restrict__ in, uint8_t *__restrict__ out)
+{
+    using LDS = TileLds<Pat>;
+    __shared__ uint32_t s_buf[2][LDS::WORDS];
+    const uint64_t b = xcd_remap(blockIdx.x, gridDim.x);
+    const uint32_t i = group_instance(G, b);
+    const TileArgs &A = reinterpret_cast<const TileArgs *>(G.args)[i];
+    const uint64_t base = G.base[i];
+    tile_body<Pat>(A, in + base, out + base, b - G.tstart[i], s_buf[0], s_buf[1]);
 }
 
 template <class Pat>
@@ -351,9 +368,9 @@ struct BatchGroup {
     int K_full;     // steps a launch can take at most (bit-sliced tiles: more than K_max; 0: any number)
     unsigned threads;
     std::vector<uint32_t> members;
-    uint64_t ntiles;
-    void *d_args;
-    uint64_t *d_base, *d_tstart;
+    uint64_t ntiles, ntiles1;  // tiles; of launches of one step (but kBBits)
+    void *d_args, *d_args1;
+    uint64_t *d_base, *d_tstart, *d_tstart1;
 };
 
 struct BatchHost {
@@ -509,7 +526,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
             for (BatchGroup &g : H->groups)
                 if (g.kind == I.kind) G = &g;
             if (!G) {
-                H->groups.push_back(BatchGroup{I.kind, kMaxSteps, kMaxSteps, 0, 0, {}, 0, nullptr, nullptr, nullptr});
+                H->groups.push_back(BatchGroup{I.kind, kMaxSteps, kMaxSteps, 0, 0, {}, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr});
                 G = &H->groups.back();
             }
             if (I.kind == kBBits) {
@@ -667,8 +684,9 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
         const bool bits = G.kind == kBBits;
         std::vector<SliceArgs> ta(bits ? 0 : m);
         std::vector<BitboxArgs> ba(bits ? m : 0);
-        std::vector<uint64_t> base(m), ts(m + 1);
-        uint64_t tiles = 0;
+        std::vector<TileArgs> ta1(bits ? 0 : m);
+        std::vector<uint64_t> base(m), ts(m + 1), ts1(bits ? 0 : m + 1);
+        uint64_t tiles = 0, tiles1 = 0;
         for (size_t q = 0; q < m; ++q) {
             const FractalHost &F = fractal_host_of(fr[G.members[q]]);
             ts[q] = tiles;
@@ -679,10 +697,22 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
             } else {
                 ta[q] = slice_of[&F]->A;
                 tiles += ta[q].ntiles;
+                ta1[q] = tile_args(F);
+                ts1[q] = tiles1;
+                tiles1 += ta1[q].ntiles;
             }
         }
         ts[m] = tiles;
         G.ntiles = tiles;
+        G.ntiles1 = tiles1;
+        if (!bits) {
+            ts1[m] = tiles1;
+            e = hipMalloc(&G.d_args1, sizeof(TileArgs) * m);
+            if (e == hipSuccess) e = hipMemcpy(G.d_args1, ta1.data(), sizeof(TileArgs) * m, hipMemcpyHostToDevice);
+            if (e == hipSuccess) e = hipMalloc(&G.d_tstart1, sizeof(uint64_t) * (m + 1));
+            if (e == hipSuccess) e = hipMemcpy(G.d_tstart1, ts1.data(), sizeof(uint64_t) * (m + 1), hipMemcpyHostToDevice);
+            if (e != hipSuccess) break;
+        }
         const size_t asz = bits ? sizeof(BitboxArgs) * m : sizeof(SliceArgs) * m;
         e = hipMalloc(&G.d_args, asz);
         if (e == hipSuccess) e = hipMemcpy(G.d_args, bits ? (const void *)ba.data() : (const void *)ta.data(), asz,
@@ -748,6 +778,8 @@ void batch_destroy(BatchHost *H)
         (void)hipFree(G.d_args);
         (void)hipFree(G.d_base);
         (void)hipFree(G.d_tstart);
+        (void)hipFree(G.d_args1);
+        (void)hipFree(G.d_tstart1);
     }
     delete H;
 }
@@ -777,6 +809,14 @@ static sqz_status launch_group(const BatchGroup &G, const uint8_t *in, uint8_t *
 {
     const GroupArgs A{G.d_args, G.d_base, G.d_tstart, (uint32_t)G.members.size()};
     const unsigned grid = (unsigned)G.ntiles;
+    if (steps == 1 && G.kind != kBBits) {
+        const GroupArgs A1{G.d_args1, G.d_base, G.d_tstart1, (uint32_t)G.members.size()};
+        const auto kernel = G.kind == kBTri ? k_batch_tile<PatTriangle>
+                                            : (G.kind == kBTriPaper ? k_batch_tile<PatTrianglePaper> : k_batch_tile<PatVicsek>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)G.ntiles1), dim3(kBlock), 0, st, A1, in, out);
+        const hipError_t e = hipGetLastError();
+        return e == hipSuccess ? SQZ_OK : hip_error(e, "batch group launch");
+    }
     switch (G.kind) {
     case kBTri:
         hipLaunchKernelGGL(k_batch_slice<SliceTriSmall>, dim3(grid), dim3(G.threads), 0, st, A, in, out, steps);
@@ -842,7 +882,14 @@ static sqz_status launch_all(const BatchHost *H, const uint8_t *a, const uint8_t
         for (size_t g = 0; g < H->groups.size() && s2 == SQZ_OK; ++g) {
             // the most the tiles can take, unless fewer were chosen
             const BatchGroup &G = H->groups[g];
-            const std::vector<int> plan = plan_launches(steps, G.K < G.K_max ? G.K : G.K_full);
+            const int K = G.K < G.K_max ? G.K : G.K_full;
+            std::vector<int> plan = plan_launches(steps, K);
+            // a launch that only sets the parity takes one step where that has a faster kernel
+            // (256 fractals, 4 steps: 2 + 2 458 us, 3 + 1 430)
+            if (G.kind != kBBits && steps > 1 && K != 1 && (int)plan.size() > (K < 1 ? 1 : (steps + K - 1) / K)) {
+                plan = plan_launches(steps - 1, K);
+                plan.push_back(1);
+            }
             for (size_t i = 0; i < plan.size() && s2 == SQZ_OK; ++i)
                 s2 = launch_group(H->groups[g], (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
         }

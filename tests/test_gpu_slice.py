@@ -82,3 +82,27 @@ def test_batch_equals_single_runs(steps):
     for i, F in enumerate(fr):
         x = F.fill_bernoulli(11 * i, 0.5)
         assert torch.equal(B.instance(res, i), F.compact_run(x, torch.empty_like(x), steps)), (i, steps)
+
+
+@pytest.mark.parametrize("steps", [1, 2, 3, 4, 31, 32, 33, 62, 63, 64])
+def test_batch_plans_against_single_runs(steps):
+    """A batch's launches, among them those of one step that set the parity, around the
+    most steps of a launch (27 for the Vicsek cross, 31 for the triangles)."""
+    torch = torch_or_skip()
+    import paper_2201_00613_amd as sqz
+
+    fr = [gpu_fractal(*n) for n in (("triangle", 9), ("triangle", 5), ("vicsek", 7), ("triangle_paper", 10), ("vicsek", 4),
+                                    ("triangle", 12), ("carpet", 5))]
+    B = sqz.Batch(fr)
+    a, b = B.empty_state(), B.empty_state()
+    starts = []
+    for i, F in enumerate(fr):
+        starts.append(F.fill_bernoulli(40 + i, 0.5))
+        B.instance(a, i).copy_(starts[i])
+    res = B.run(a, b, steps) if steps > 1 else B.step(a, b)
+    for i, F in enumerate(fr):
+        x, y = starts[i], torch.empty_like(starts[i])
+        for _ in range(steps):
+            F.compact_step(x, y, impl="cell")
+            x, y = y, x
+        assert torch.equal(B.instance(res, i), x), i
