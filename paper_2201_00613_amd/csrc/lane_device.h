@@ -4,9 +4,10 @@
 //
 //   tile  = a level-M subtree, one workgroup; block = a level-J subtree (the
 //           carpet's 64 cells, 9 of the triangle, 25 of the Vicsek cross; 8, 3
-//           and 5 where the fractal does not fill the chip), one lane.  In-block neighbours are registers; the cells of adjacent
-//           blocks a block touches are values those lanes publish in LDS each
-//           step.  Where every cell read eight neighbours from LDS (nine reads
+//           and 5 where the fractal does not fill the chip), one lane.
+//           In-block neighbours are registers; the cells of adjacent blocks a
+//           block touches are values those lanes publish in LDS each step.
+//           Where every cell read eight neighbours from LDS (nine reads
 //           a cell and step), a carpet block reads 40 values and publishes 32
 //           per 64 cells.
 //   ring  = the blocks of adjacent tiles that hold every cell within K steps
@@ -19,9 +20,9 @@
 // bfloat16 storage every step rounded as a one-step launch stores it.  Results
 // are equal bit for bit.
 //
-// Measured against one launch per step (level-9 carpet, 100 steps; 6 launches
-// of 16 or 17): binary32 23.19 -> 5.10 ms, bfloat16 with stochastic rounding
-// 20.88 -> 9.75 ms, and 61 steps on the level-12 triangle 413 -> 49 us.  What
+// Measured against one launch per step (level-9 carpet, 100 steps and their mass; 6 launches
+// of 16 or 17): binary32 23.19 -> 4.98 ms, bfloat16 with stochastic rounding
+// 20.88 -> 9.38 ms, and 61 steps on the level-12 triangle 413 -> 46 us.  What
 // bounds the carpet now: a launch moves its 1.2 GB (frames included) in about
 // 245 us with nothing to overlap it (one workgroup of eleven waves per CU, 160
 // registers a lane), and a step takes 35 us in binary32 (530 vector
