@@ -319,6 +319,10 @@ sqz_status slice_run_resident(const FractalHost &F, uint8_t *a, uint8_t *b, int 
         return set_error(SQZ_ERR_HIP, "a wait of an earlier resident run timed out: its result is invalid");
     }
     if (steps < 1) return SQZ_OK;
+    // Without an exchange and with the result in the other buffer the launch
+    // needs no state: the plain kernel, whose tiles wait for nothing (25 steps:
+    // level-13 triangle 13.2 -> 11.6 us, level-9 Vicsek 11.0 -> 10.2).
+    if (!S.K || (steps <= (int)S.K && (steps & 1))) return slice_run_launches(F, a, b, steps, st);
     slice_dispatch(S.kind, S.var, [&](auto p) {
         using P = decltype(p);
         if constexpr (P::J < (P::B == 2 ? 2 : 3))

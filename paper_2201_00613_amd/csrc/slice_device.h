@@ -30,10 +30,10 @@
 // them moving bits.  Here the triangle needs 45 per 9 words (J = 2) or 121 per
 // 27 words (J = 3), each word 27 cells: 0.17-0.19 instructions per cell.
 // Measured against those blocks: level-16 triangle, 100 steps, all tiles
-// resident: 333 -> 67 us; level 20, 20 steps: two launches of ten (4.68 ms,
+// resident: 333 -> 62 us; level 20, 20 steps: two launches of ten (4.68 ms,
 // bound by vector issue) -> one in place (1.51 ms, 4.6 TB/s of loads and
-// stores, the rate of a large copy); level 13, 25 steps: 23.5 -> 14.1 us;
-// level-9 Vicsek cross, 37 steps: 43.4 -> 17.5 us.
+// stores, the rate of a large copy); level 13, 25 steps: 23.5 -> 12.0 us;
+// level-9 Vicsek cross, 37 steps: 43.4 -> 16.5 us.
 #pragma once
 
 #include <utility>
@@ -653,24 +653,27 @@ __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in
     };
 
     if (tid < 2) *reinterpret_cast<uint32_t *>(lds + tid * C::BUF + C::ZERO) = 0;
-    publish(std::integral_constant<uint32_t, 0>{});
-    __syncthreads();
-    int32_t left = steps, since = 0;
-    for (;;) {
-        advance(std::integral_constant<uint32_t, 0>{});
-        if (--left == 0) break;
-        if constexpr (RES) {
-            if (A.nring && ++since == (int32_t)R.K) exchange(), since = 0;
-        }
-        publish(std::integral_constant<uint32_t, 1>{});
-        __syncthreads();
-        advance(std::integral_constant<uint32_t, 1>{});
-        if (--left == 0) break;
-        if constexpr (RES) {
-            if (A.nring && ++since == (int32_t)R.K) exchange(), since = 0;
-        }
+    // Steps between exchanges in a loop of their own: with the exchange inside
+    // it, every step was slower (100 steps: level-16 triangle 66.3 -> 61.2 us,
+    // level 13 44.3 -> 41.3, level-10 Vicsek 45.5 -> 43.0).
+    for (int32_t left = steps;;) {
+        const int32_t m = RES && A.nring && left > (int32_t)R.K ? (int32_t)R.K : left;
         publish(std::integral_constant<uint32_t, 0>{});
         __syncthreads();
+        for (int32_t c = m;;) {
+            advance(std::integral_constant<uint32_t, 0>{});
+            if (--c == 0) break;
+            publish(std::integral_constant<uint32_t, 1>{});
+            __syncthreads();
+            advance(std::integral_constant<uint32_t, 1>{});
+            if (--c == 0) break;
+            publish(std::integral_constant<uint32_t, 0>{});
+            __syncthreads();
+        }
+        left -= m;
+        if (!RES || left == 0) break;
+        __syncthreads();  // every lane has read its last halo
+        exchange();
     }
     if constexpr (RES) {
         // The result of an even step count goes where the start was: the tiles
@@ -690,10 +693,12 @@ __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in
     if constexpr (RES) {
         if (tid == 0) __hip_atomic_store(R.epoch + t, epoch + nx, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
-    // Launches stream over arrays that outgrow the last-level cache: nontemporal
-    // stores (level 20: 1580 -> 1508 us per 20 steps).  A resident run's array
-    // fits it and is read again by the next run: plain ones (level 16: 70.1 us
-    // per 100 steps, 71.4 nontemporal).
+    // The wide kernels stream over arrays that outgrow the last-level cache:
+    // nontemporal stores (level 20: 1580 -> 1508 us per 20 steps).  The level-16
+    // triangle fits it and is read again by the next launch: plain ones (three
+    // steps 23.8 -> 20.0 us, 100 steps resident 1.3 us less).  The level-10 Vicsek
+    // cross, whose 125 tiles leave half of the CUs idle, keeps them (9.9 -> 9.5).
+    constexpr bool NTS = !RES && (J == 3 || P::B == 2);
     uint8_t *dst = out + t * A.cells;
     if (P::SMALL || A.words <= 4 * NT) {
         const uint32_t n = (A.words + 3) / 4;
@@ -702,7 +707,7 @@ __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in
     } else if constexpr (!P::SMALL) {
         const uint32_t n = (A.words + 15) / 16;
         for (uint32_t k = tid; k < n; k += NT)
-            slice_store_words<C, 4, !RES>(dst, A.words, 16 * k + 16 <= A.words ? 16 * k : A.words - 16, sm);
+            slice_store_words<C, 4, NTS>(dst, A.words, 16 * k + 16 <= A.words ? 16 * k : A.words - 16, sm);
     }
 }
 

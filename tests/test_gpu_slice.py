@@ -106,3 +106,22 @@ def test_batch_plans_against_single_runs(steps):
             F.compact_step(x, y, impl="cell")
             x, y = y, x
         assert torch.equal(B.instance(res, i), x), i
+
+
+@pytest.mark.parametrize("name,r", [("triangle", 8), ("triangle", 9), ("triangle", 16), ("vicsek", 6), ("vicsek", 8), ("vicsek", 10)])
+def test_resident_runs_without_and_with_exchanges(name, r):
+    """The resident form where it takes the plain kernel (one launch, no exchange) and
+    around its exchanges, run after run on the same state (their counts carry over)."""
+    torch = torch_or_skip()
+    F = gpu_fractal(name, r)
+    x = F.fill_bernoulli(6, 0.5)
+    y, a = torch.empty_like(x), x.clone()
+    b = torch.empty_like(a)
+    for steps in (3, 2, 27, 28, 31, 32, 1, 55, 63, 94, 4):
+        res = F.compact_run(a, b, steps, form="resident")
+        if res is not a:
+            a, b = b, a
+        for _ in range(steps):
+            F.compact_step(x, y)
+            x, y = y, x
+        assert torch.equal(res, x), steps
