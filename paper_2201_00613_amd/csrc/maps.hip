@@ -47,6 +47,7 @@ constexpr int kMapUnroll = SQZ_MAP_UNROLL;
 // 6.8 us without, 6.0 with; 7-digit carpet 5.6 and 6.0; 3e4: 5.7 and 6.0).
 typedef uint64_t map_u64x2 __attribute__((ext_vector_type(2), aligned(8)));
 typedef int32_t map_i32x4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef int32_t map_i32x2 __attribute__((ext_vector_type(2), aligned(4)));
 static_assert(kMapUnroll % 2 == 0, "pairs");
 constexpr int64_t kMapLarge = 1 << 20;
 
@@ -88,7 +89,7 @@ __global__ void __launch_bounds__(kBlock) k_lambda(MapParams P, const uint64_t *
     };
     const int64_t stride = (int64_t)gridDim.x * kBlock * kMapUnroll;
     for (int64_t i0 = (int64_t)blockIdx.x * kBlock * kMapUnroll + 2 * threadIdx.x; i0 < count; i0 += stride) {
-        if (i0 + (kMapUnroll - 2) * kBlock + 1 < count) {
+        if (i0 - 2 * threadIdx.x + kMapUnroll * kBlock <= count) {  // a whole pass (the same for every lane)
             map_u64x2 c[kMapUnroll / 2];
 #pragma unroll
             for (int u = 0; u < kMapUnroll / 2; ++u)
@@ -100,12 +101,20 @@ __global__ void __launch_bounds__(kBlock) k_lambda(MapParams P, const uint64_t *
                 map_store<LARGE>(o, reinterpret_cast<map_i32x4 *>(xy + 2 * (i0 + 2 * u * kBlock)));
             }
         } else {
+            uint64_t c[kMapUnroll];
+#pragma unroll
             for (int u = 0; u < kMapUnroll; ++u) {
                 const int64_t i = i0 + (u / 2) * 2 * kBlock + (u & 1);
-                if (i >= count) break;
-                const int2 p = map(idx[i]);
-                xy[2 * i] = p.x;
-                xy[2 * i + 1] = p.y;
+                c[u] = i < count ? idx[i] : ~0ull;
+            }
+#pragma unroll
+            for (int u = 0; u < kMapUnroll; ++u) {
+                const int64_t i = i0 + (u / 2) * 2 * kBlock + (u & 1);
+                if (i < count) {
+                    const int2 p = map(c[u]);
+                    const map_i32x2 o = {p.x, p.y};
+                    *reinterpret_cast<map_i32x2 *>(xy + 2 * i) = o;
+                }
             }
         }
     }
@@ -126,7 +135,7 @@ __global__ void __launch_bounds__(kBlock) k_nu(MapParams P, const int32_t *__res
     L.nu_top = s_nu + (P.nu_top - P.nu_lo);
     const int64_t stride = (int64_t)gridDim.x * kBlock * kMapUnroll;
     for (int64_t i0 = (int64_t)blockIdx.x * kBlock * kMapUnroll + 2 * threadIdx.x; i0 < count; i0 += stride) {
-        if (i0 + (kMapUnroll - 2) * kBlock + 1 < count) {
+        if (i0 - 2 * threadIdx.x + kMapUnroll * kBlock <= count) {  // a whole pass (the same for every lane)
             map_i32x4 p[kMapUnroll / 2];
 #pragma unroll
             for (int u = 0; u < kMapUnroll / 2; ++u)
@@ -137,10 +146,17 @@ __global__ void __launch_bounds__(kBlock) k_nu(MapParams P, const int32_t *__res
                 map_store<LARGE>(o, reinterpret_cast<map_u64x2 *>(idx + i0 + 2 * u * kBlock));
             }
         } else {
+            map_i32x2 p[kMapUnroll];
+#pragma unroll
             for (int u = 0; u < kMapUnroll; ++u) {
                 const int64_t i = i0 + (u / 2) * 2 * kBlock + (u & 1);
-                if (i >= count) break;
-                idx[i] = nu_map(L, xy[2 * i], xy[2 * i + 1]);
+                p[u] = (map_i32x2)0;
+                if (i < count) p[u] = *reinterpret_cast<const map_i32x2 *>(xy + 2 * i);
+            }
+#pragma unroll
+            for (int u = 0; u < kMapUnroll; ++u) {
+                const int64_t i = i0 + (u / 2) * 2 * kBlock + (u & 1);
+                if (i < count) idx[i] = nu_map(L, p[u].x, p[u].y);
             }
         }
     }
