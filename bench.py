@@ -6,9 +6,9 @@ Workload (N=1): level-16 Sierpinski triangle, replicas (0,0),(1,0),(0,1),
 "step" is one B3/S23 update of every cell.  The K timed steps are one
 sqz_compact_run call, in the run form the library picks for K steps: from 10
 steps (and where launches would need an extra one-step launch) one launch
-that holds all 729 tiles in LDS for all K steps, exchanging ring cells every
-ten steps; otherwise launches of ten steps.  The other form is timed beside
-it.  The
+that holds all 243 tiles on the chip for all K steps, exchanging ring subtrees
+every 31 steps; otherwise launches of up to 31 steps.  The other form is timed
+beside it.  The
 same steps on the 65536 x 65536 bounding-box grid give the speedup (these
 comparison runs go first, so the headline is not the process's first GPU
 work); the
@@ -60,15 +60,19 @@ def time_steps(torch, step, steps: int, warmup: int):
     return start.elapsed_time(end) / 1e3
 
 
+# Most Life steps a launch of a run takes here: tiles sliced across subtrees (the
+# triangle) and bit rows (the carpet)
+STEPS_PER_LAUNCH = {3: 31, 8: 15}
+
+
 def run_launches(F, steps: int) -> int:
-    """Launches sqz_compact_run makes for `steps` steps: K = F.run_steps_per_launch
-    steps per launch plus one launch of the remainder, and one more launch when the
-    count's parity differs from that of `steps` (a launch is split in two)."""
-    K = F.run_steps_per_launch
-    if K < 2:
+    """Launches over all cells that sqz_compact_run makes for `steps` steps: of nearly
+    equal step counts, at most STEPS_PER_LAUNCH each; where their number has not the
+    parity of `steps`, the triangle's last one updates in place, the carpet takes one more."""
+    if F.run_steps_per_launch < 2:
         return steps
-    n = steps // K + (1 if steps % K else 0)
-    return n + (1 if n % 2 != steps % 2 else 0)
+    n = -(-steps // STEPS_PER_LAUNCH[F.k])
+    return n + (1 if F.k == 8 and n % 2 != steps % 2 else 0)
 
 
 def compact_run(torch, F, seed, p, steps, warmup, impl="auto", form="auto"):
@@ -349,8 +353,8 @@ def repeat_stats(torch, F, seed, p, steps: int, reps: int, form: str = "auto") -
 
 
 def carpet_life_leg(torch, sqz, steps: int) -> dict:
-    """Life on the level-9 Sierpinski carpet (134,217,728 cells; bit-row tiles, up to ten
-    steps per launch), Bernoulli(0.5), `steps` steps as one sqz_compact_run call, after
+    """Life on the level-9 Sierpinski carpet (134,217,728 cells; bit-row tiles, up to
+    fifteen steps per launch), Bernoulli(0.5), `steps` steps as one sqz_compact_run call, after
     an untimed run of the same steps (a first run in the process is measurably slower)."""
     from paper_2201_00613_amd import workloads as W
 
@@ -358,7 +362,7 @@ def carpet_life_leg(torch, sqz, steps: int) -> dict:
     sec = compact_run(torch, F, 2201, 0.5, steps, steps)
     launches = run_launches(F, steps)
     res = {"fractal": "sierpinski carpet s=3 k=8", "level": 9, "cells": F.cells, "steps": steps,
-           "steps_per_launch": F.run_steps_per_launch, "launches": launches, "ms_per_step": sec * 1e3 / steps,
+           "steps_per_launch": steps / launches, "launches": launches, "ms_per_step": sec * 1e3 / steps,
            "cell_updates_per_s": F.cells * steps / sec,
            "algorithmic_gbs_per_launch": BYTES_PER_UPDATE * F.cells * launches / sec / 1e9}
     del F
@@ -456,7 +460,7 @@ def main() -> int:
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=100)
     ap.add_argument("--warmup", type=int, default=20,
-                    help="untimed steps first (20: two launches of the ten-step kernel the timed run uses)")
+                    help="untimed steps first, in the timed run's form")
     ap.add_argument("--level", type=int, default=16)
     ap.add_argument("--impl", default="auto", choices=["auto", "tile", "cell"])
     ap.add_argument("--form", default="auto", choices=["auto", "launches", "resident"],
@@ -554,7 +558,7 @@ def main() -> int:
                    "level": r, "cells": F.cells, "bernoulli_p": p, "seed": seed, "impl": args.impl,
                    "run_form": used, "tile_level": F.tile_level, "launches": launches,
                    "steps_between_exchanges" if used == "resident" else "steps_per_launch":
-                       F.run_steps_per_launch if used == "resident" else args.steps / launches,
+                       STEPS_PER_LAUNCH[F.k] if used == "resident" else args.steps / launches,
                    "note": "2 x 43 MB working set is Infinity-Cache resident" if r == 16 else ""},
     }
     hbm = {"algorithmic_gbs_per_launch": gbs, "frac_of_hbm_peak": gbs / HBM_PEAK_GBS,
@@ -575,7 +579,7 @@ def main() -> int:
         alu = alu_roofline(rl, args.steps, sl, nl, F.cells, "k_life_tileK_triangle_r16.md")
         if alu:
             out["launches_form"]["roofline"] = alu
-        log(f"[bench] launches of {F.run_steps_per_launch} steps: {sl * 1e3 / args.steps:.4f} ms/step")
+        log(f"[bench] {nl} launches: {sl * 1e3 / args.steps:.4f} ms/step")
     elif other and other[0] == "resident":
         sr = other[1]
         out["resident_form"] = {"ms_per_step": sr * 1e3 / args.steps, "cell_updates_per_s": F.cells * args.steps / sr,
