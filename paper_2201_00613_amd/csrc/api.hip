@@ -320,10 +320,11 @@ sqz_status sqz_compact_run(const sqz_fractal *f, uint8_t *d_a, uint8_t *d_b, int
 }
 
 // SQZ_RUN_AUTO's choice on aligned buffers: the resident run when it is offered
-// and either the run is long enough for its fixed cost (loading and storing
-// every tile once: at level 16 it is ahead of launches of ten steps from 10
-// steps on) or the launches would need a one-step launch of their own to land
-// the result in the buffer of the step count's parity.
+// and either there are at least ten steps or their number is even, so that one
+// launch would leave the result in the wrong buffer (launches / resident: 2 steps,
+// level-9 triangle 7.5 / 7.1 us, level 16 21.9 / 21.1, level-9 Vicsek 7.7 / 6.2; 10
+// steps, level 16 24.6 / 23.8; 32 steps 48.6 / 33.5).  One launch of odd steps is the
+// same kernel in both forms (slice_run_resident).
 constexpr int32_t kAutoResidentSteps = 10;
 
 static bool auto_resident(const FractalHost &h, int32_t steps)
