@@ -179,9 +179,65 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(4))) k
     }
 }
 
+// A whole fractal too small for a subtile to hold a block (SliceArgs::words 0,
+// its neighbour table in place of the halo sources): the states in LDS, any
+// number of steps, at most two cells a lane.  It shares its pattern's launches,
+// because a launch of its own costs more than its steps do (50 steps: 64 level-4
+// triangles 135 us on expanded tiles, 27 here; 16 mixed fractals, four of them
+// as small, 177 and 120).
+constexpr uint32_t kTinyCells = 96;
+
+__device__ __forceinline__ void tiny_tile(const SliceArgs &A, const uint8_t *in, uint8_t *out, int32_t steps,
+                                          uint32_t *sm)
+{
+    uint8_t *const v = reinterpret_cast<uint8_t *>(sm);
+    const uint32_t N = A.cells;
+    uint32_t c[2], q[2][8];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+        c[t] = threadIdx.x + t * blockDim.x;
+        if (c[t] < N) {
+            const uint2 e = reinterpret_cast<const uint2 *>(A.perm)[c[t]];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) q[t][j] = ((j < 4 ? e.x : e.y) >> (8 * (j & 3))) & 0xFFu;
+            v[c[t]] = in[c[t]] & 1u;
+        }
+    }
+    if (threadIdx.x < 2) v[threadIdx.x * kTinyCells + N] = 0;
+    __syncthreads();
+    for (int32_t s = 0; s < steps; ++s) {
+        const uint8_t *src = v + (s & 1) * kTinyCells;
+        uint8_t *dst = v + (~s & 1) * kTinyCells;
+#pragma unroll
+        for (int t = 0; t < 2; ++t)
+            if (c[t] < N) {
+                uint32_t cnt = 0;
+#pragma unroll
+                for (int j = 0; j < 8; ++j) cnt += src[q[t][j]];
+                dst[c[t]] = (uint8_t)(cnt == 3 || (src[c[t]] && cnt == 2));
+            }
+        __syncthreads();
+    }
+#pragma unroll
+    for (int t = 0; t < 2; ++t)
+        if (c[t] < N) out[c[t]] = v[(steps & 1) * kTinyCells + c[t]];
+}
+
+// One tile of an instance.
+template <class P>
+__device__ __forceinline__ void slice_unit(const SliceArgs &A, const uint8_t *in, uint8_t *out, uint64_t t,
+                                           int32_t steps, uint32_t *sm)
+{
+    static_assert(SliceCfg<P>::LDS >= 2 * kTinyCells, "LDS of a small fractal");
+    if (A.words == 0)
+        tiny_tile(A, in, out, steps, sm);
+    else
+        slice_tile<P, false>(A, in, out, t, SliceRing{in, false}, steps, SliceRes{}, sm);
+}
+
 // One group: instances of one tiled pattern, one workgroup per tile.
 struct GroupArgs {
-    const void *args;        // per instance: TileArgs or BitboxArgs
+    const void *args;        // per instance: TileArgs, SliceArgs or BitboxArgs
     const uint64_t *base;    // byte offset of each instance
     const uint64_t *tstart;  // ninst + 1 prefix sums of tile counts
     uint32_t ninst;
@@ -215,7 +271,7 @@ k_batch_slice(GroupArgs G, const uint8_t *in, uint8_t *out, int32_t steps)
     const uint32_t i = group_instance(G, b);
     const SliceArgs A = reinterpret_cast<const SliceArgs *>(G.args)[i];
     const uint64_t base = G.base[i];
-    slice_tile<P, false>(A, in + base, out + base, b - G.tstart[i], SliceRing{in + base, false}, steps, SliceRes{}, sm);
+    slice_unit<P>(A, in + base, out + base, b - G.tstart[i], steps, sm);
 }
 
 // A launch of one step: the bit-sliced blocks, whose loads and stores are 16
@@ -269,10 +325,10 @@ struct TiledArgs {
 };
 
 template <class P>
-__device__ __forceinline__ void tiled_unit(const SliceArgs &A, const uint8_t *in, uint8_t *out, uint64_t t, int32_t steps,
+__device__ __forceinline__ void tiled_unit(const TiledInst &I, const uint8_t *in, uint8_t *out, uint64_t t, int32_t steps,
                                            unsigned char *smem)
 {
-    slice_tile<P, false>(A, in, out, t, SliceRing{in, false}, steps, SliceRes{}, reinterpret_cast<uint32_t *>(smem));
+    slice_unit<P>(I.t, in, out, t, steps, reinterpret_cast<uint32_t *>(smem));
     __syncthreads();  // LDS is free for the next tile
 }
 
@@ -282,9 +338,9 @@ __device__ __forceinline__ void tiled_run(const TiledInst &I, const uint8_t *in,
     const uint8_t *ii = in + I.base;
     uint8_t *oo = out + I.base;
     switch (I.kind) {
-    case kBTri: tiled_unit<SliceTriSmall>(I.t, ii, oo, j, steps, smem); break;
-    case kBTriPaper: tiled_unit<SlicePaperSmall>(I.t, ii, oo, j, steps, smem); break;
-    case kBVicsek: tiled_unit<SliceVicsekSmall>(I.t, ii, oo, j, steps, smem); break;
+    case kBTri: tiled_unit<SliceTriSmall>(I, ii, oo, j, steps, smem); break;
+    case kBTriPaper: tiled_unit<SlicePaperSmall>(I, ii, oo, j, steps, smem); break;
+    case kBVicsek: tiled_unit<SliceVicsekSmall>(I, ii, oo, j, steps, smem); break;
     default:
         bitbox_tile<PatCarpet>(I.x, ii, oo, j, steps, reinterpret_cast<uint32_t *>(smem));
         __syncthreads();
@@ -378,6 +434,7 @@ struct BatchHost {
     // (tiled_form 0), one persistent launch over all of them (1) or one launch
     // over all of them with a workgroup per tile (2); the autotuner picks
     std::vector<BatchGroup> groups;
+    uint32_t *d_tiny;  // neighbour tables of the fractals too small to tile (null: none)
     std::vector<SliceConfig *> slices;  // tile configurations that are not a fractal's own
     int tiled_form;
     std::vector<TiledInst> tiled;
@@ -424,11 +481,40 @@ const FractalHost &fractal_host_of(const sqz_fractal *f);  // api.hip
 static uint32_t kind_of(const FractalHost &F)
 {
     if (F.bitbox) return kBBits;
-    if (F.slice && F.tile_kind == 1) return kBTri;
-    if (F.slice && F.tile_kind == 2) return kBTriPaper;
-    if (F.slice && F.tile_kind == 3) return kBVicsek;
+    if (F.slice || F.N < kTinyCells) {
+        if (F.tile_kind == 1) return kBTri;
+        if (F.tile_kind == 2) return kBTriPaper;
+        if (F.tile_kind == 3) return kBVicsek;
+    }
     if (F.xtile) return F.xtile->P == 84 ? kBX84 : (F.xtile->P == 68 ? kBX68 : kBXAny);
     return kBCell;
+}
+
+// A fractal too small to tile: one unit, with the 8 neighbours of each cell as
+// bytes (N: none) at `nb`.
+static SliceArgs tiny_args(const FractalHost &F, const uint32_t *nb)
+{
+    SliceArgs A;
+    memset(&A, 0, sizeof A);
+    A.ntiles = 1;
+    A.cells = (uint32_t)F.N;
+    A.perm = nb;
+    return A;
+}
+
+static void tiny_neighbours(const FractalHost &F, std::vector<uint32_t> &t)
+{
+    for (uint64_t c = 0; c < F.N; ++c) {
+        int64_t x, y;
+        host_lambda(F, F.r, c, x, y);
+        uint32_t w[2] = {0, 0};
+        for (int j = 0; j < 8; ++j) {
+            const int d = j < 4 ? j : j + 1;
+            const int64_t q = host_nu(F, F.r, x + d % 3 - 1, y + d / 3 - 1);
+            w[j / 4] |= (uint32_t)(q < 0 ? (int64_t)F.N : q) << (8 * (j & 3));
+        }
+        t.insert(t.end(), {w[0], w[1]});
+    }
 }
 
 static bool grouped(uint32_t kind) { return kind == kBTri || kind == kBTriPaper || kind == kBVicsek || kind == kBBits; }
@@ -474,6 +560,21 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
     std::map<std::string, uint32_t> xcfg_ids;
     std::map<const FractalHost *, SliceConfig *> slice_of;  // a fractal may occur many times
     std::vector<uint64_t> cell_start(count + 1);
+    std::map<const FractalHost *, size_t> tiny_of;  // offset of a small fractal's neighbour table
+    std::vector<uint32_t> tiny;
+    for (int32_t i = 0; i < count; ++i) {
+        const FractalHost &F = fractal_host_of(fr[i]);
+        const uint32_t k = kind_of(F);
+        if (grouped(k) && k != kBBits && !F.slice && tiny_of.emplace(&F, tiny.size()).second) tiny_neighbours(F, tiny);
+    }
+    if (!tiny.empty()) {
+        e = hipMalloc(&H->d_tiny, tiny.size() * sizeof(uint32_t));
+        if (e == hipSuccess) e = hipMemcpy(H->d_tiny, tiny.data(), tiny.size() * sizeof(uint32_t), hipMemcpyHostToDevice);
+        if (e != hipSuccess) {
+            batch_destroy(H);
+            return hip_error(e, "batch tables");
+        }
+    }
     uint64_t off = 0, cstart = 0;
     size_t lds = 0, ldsk = 0;
     int kmin = kMaxSteps;
@@ -481,7 +582,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
     for (int32_t i = 0; i < count; ++i) {
         const FractalHost &F = fractal_host_of(fr[i]);
         if (F.device != H->device) {
-            delete H;
+            batch_destroy(H);
             return set_error(SQZ_ERR_INVALID, "instance %d lives on device %d, not %d", i, F.device, H->device);
         }
         BatchInst &I = H->inst[i];
@@ -503,7 +604,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                 H->tlds = std::max<size_t>(H->tlds, kBxLds * 4);
             } else {
                 SliceConfig *&C = slice_of[&F];
-                if (!C) {
+                if (!C && F.slice) {
                     bool own = true;
                     const sqz_status st = slice_batch_config(F, &C, &own);
                     if (st == SQZ_OK && !own) H->slices.push_back(C);
@@ -512,7 +613,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                         return st;
                     }
                 }
-                T.t = C->A;
+                T.t = C ? C->A : tiny_args(F, H->d_tiny + tiny_of[&F]);
                 T.units = T.t.ntiles;
                 T.unit_cells = T.t.cells;
                 H->Kt_max = std::min(H->Kt_max, tile_steps_per_launch(F));
@@ -526,7 +627,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
             for (BatchGroup &g : H->groups)
                 if (g.kind == I.kind) G = &g;
             if (!G) {
-                H->groups.push_back(BatchGroup{I.kind, kMaxSteps, kMaxSteps, 0, 0, {}, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr});
+                H->groups.push_back(BatchGroup{I.kind, kMaxSteps, kMaxSteps, 0, 64, {}, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr});
                 G = &H->groups.back();
             }
             if (I.kind == kBBits) {
@@ -534,8 +635,8 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                 if (K) G->K_full = K;
             } else {
                 const SliceConfig *C = slice_of[&F];
-                if (C->K) G->K_full = (int)C->K;  // the same for every fractal of more than one tile
-                G->threads = std::max(G->threads, (C->A.lanes + 63) / 64 * 64);
+                if (C && C->K) G->K_full = (int)C->K;  // the same for every fractal of more than one tile
+                if (C) G->threads = std::max(G->threads, (C->A.lanes + 63) / 64 * 64);
             }
             G->members.push_back((uint32_t)i);
             G->K_max = std::min(G->K_max, I.kind == kBBits ? kMaxSteps : tile_steps_per_launch(F));
@@ -695,7 +796,8 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                 ba[q] = bitbox_args(F);
                 tiles += ba[q].ntiles;
             } else {
-                ta[q] = slice_of[&F]->A;
+                const SliceConfig *C = slice_of[&F];
+                ta[q] = C ? C->A : tiny_args(F, H->d_tiny + tiny_of[&F]);
                 tiles += ta[q].ntiles;
                 ta1[q] = tile_args(F);
                 ts1[q] = tiles1;
@@ -768,6 +870,7 @@ void batch_destroy(BatchHost *H)
     if (H->gexec) (void)hipGraphExecDestroy(H->gexec);
     if (H->cap) (void)hipStreamDestroy(H->cap);
     for (SliceConfig *S : H->slices) slice_free(S);
+    if (H->d_tiny) (void)hipFree(H->d_tiny);
     (void)hipFree(H->d_inst);
     (void)hipFree(H->d_cost_start);
     (void)hipFree(H->d_tiled);
