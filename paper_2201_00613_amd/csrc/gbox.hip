@@ -178,7 +178,10 @@ sqz_status gbox_prepare(FractalHost &F)
     uint64_t B = 1, KM = 1, nt = 1;
     for (int i = 0; i < M; ++i) B *= F.s, KM *= F.k;
     for (int i = M; i < F.r; ++i) nt *= F.k;
-    if (KM > 8192 || B > 128 || nt >= 0x7FFFFFFFull) return SQZ_OK;
+    // a launch holds fewer than 2^32 lanes, and there are at least 64 a tile: more
+    // tiles (17 GB of sparse cells) are left to the expanded-tile kernel, whose grid
+    // does not grow with them
+    if (KM > 8192 || B > 128 || nt * 64 > 0xFFFFFFFFull) return SQZ_OK;
     // Border: up to 16 cells, at most a quarter of the box (a wider one would
     // cost more in border cells than it saves in launches); around a single
     // tile one cell, always empty (a column between the row's ends).
