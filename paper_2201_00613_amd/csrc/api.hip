@@ -389,7 +389,7 @@ sqz_status sqz_compact_run_form(const sqz_fractal *f, sqz_run_form form, uint8_t
     const bool bits = f->h.bitbox && aligned8;
     const int K = bits ? bitbox_steps_per_launch(f->h) : (f->h.tile_kind && aligned ? 1 : xtile_steps_per_launch(f->h));
     if (bits || K >= 2) {
-        const std::vector<int> plan = plan_launches(steps, K);
+        const std::vector<int> plan = bits ? plan_launches(steps, K) : plan_full_launches(steps, K);
         const hipStream_t s = (hipStream_t)stream;
         for (size_t i = 0; i < plan.size() && st == SQZ_OK; ++i) {
             const uint8_t *in = (i & 1) ? d_b : d_a;
@@ -530,7 +530,7 @@ sqz_status sqz_diffuse_run(const sqz_fractal *f, const sqz_diffusion *d, uint64_
     if (overlap(d_a, d_b, f->h.N * dtype_size(d->dtype))) return set_error(SQZ_ERR_INVALID, "d_a and d_b overlap");
     const int K = d->steps_per_launch;
     if (K >= 2) {
-        const std::vector<int> plan = plan_launches(steps, K);
+        const std::vector<int> plan = plan_full_launches(steps, K);
         uint64_t done = 0;
         for (size_t i = 0; i < plan.size() && st == SQZ_OK; ++i) {
             st = launch_diffuse_xtile_steps(f->h, d->dtype, d->coef, d->rounding, d->seed, first_step + done,

@@ -998,7 +998,7 @@ static sqz_status launch_all(const BatchHost *H, const uint8_t *a, const uint8_t
         }
     }
     if (H->has_rest) {
-        const std::vector<int> plan = plan_launches(steps, H->K);
+        const std::vector<int> plan = plan_full_launches(steps, H->K);
         for (size_t i = 0; i < plan.size() && s2 == SQZ_OK; ++i)
             s2 = launch_batch(H, H->wg_per_cu, (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
     }

@@ -113,21 +113,6 @@ __device__ __forceinline__ uint64_t splitmix64_at(uint64_t seed, uint64_t i)
     return z ^ (z >> 31);
 }
 
-// Launch sizes for `steps` steps with at most K per launch (temporal
-// blocking; K < 1: any number): launches of nearly equal size.  Every launch
-// swaps the two buffers, so the launch count must have the parity of `steps`
-// for the result to land where one-step launches would leave it; if it does
-// not, there is one launch more.
-inline std::vector<int> plan_launches(int32_t steps, int K)
-{
-    if (steps < 1) return {};
-    int n = K < 1 ? 1 : (int)(((int64_t)steps + K - 1) / K);
-    if ((n ^ steps) & 1) ++n;
-    std::vector<int> plan;
-    for (int i = 0; i < n; ++i) plan.push_back((int)((int64_t)steps * (i + 1) / n - (int64_t)steps * i / n));
-    return plan;
-}
-
 // Life steps per launch that are reported for bit-sliced tiles and bit rows,
 // and the most a caller can choose in a batch (runs of the library's own choice
 // take more: slice_device.h, bitbox_device.h).

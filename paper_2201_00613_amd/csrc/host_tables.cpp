@@ -299,6 +299,34 @@ static std::vector<Pos> ring_subtrees(const FractalHost &F, int level, int64_t r
 }
 
 // ---------------------------------------------------------------------------
+// Launch sizes
+// ---------------------------------------------------------------------------
+std::vector<int> plan_launches(int32_t steps, int K)
+{
+    if (steps < 1) return {};
+    int n = K < 1 ? 1 : (int)(((int64_t)steps + K - 1) / K);
+    if ((n ^ steps) & 1) ++n;
+    std::vector<int> plan;
+    for (int i = 0; i < n; ++i) plan.push_back((int)((int64_t)steps * (i + 1) / n - (int64_t)steps * i / n));
+    return plan;
+}
+
+std::vector<int> plan_full_launches(int32_t steps, int K)
+{
+    if (steps < 1) return {};
+    std::vector<int> plan((size_t)(steps / K), K);
+    if (steps % K) plan.push_back(steps % K);
+    if ((plan.size() & 1) != (size_t)(steps & 1))
+        for (size_t i = plan.size(); i-- > 0;)
+            if (plan[i] >= 2) {
+                plan[i] -= 1;
+                plan.push_back(1);
+                break;
+            }
+    return plan;
+}
+
+// ---------------------------------------------------------------------------
 // Bit-sliced tiles
 // ---------------------------------------------------------------------------
 sqz_status tile_tables(const FractalHost &F, const TileSpec &S, TileTables &T)

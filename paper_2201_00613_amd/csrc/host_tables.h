@@ -130,6 +130,22 @@ void host_lambda(const FractalHost &F, int level, uint64_t c, int64_t &x, int64_
 int64_t host_nu(const FractalHost &F, int level, int64_t x, int64_t y);
 
 // ---------------------------------------------------------------------------
+// Launch sizes of a run of `steps` steps with at most K per launch (temporal
+// blocking).  Every launch swaps the two buffers, so the launch count must have
+// the parity of `steps` for the result to land where one-step launches would
+// leave it.
+// ---------------------------------------------------------------------------
+// Launches of nearly equal size (K < 1: any number of steps in one); one more
+// where the parity differs.
+std::vector<int> plan_launches(int32_t steps, int K);
+// Launches of K steps and one of the remainder; where the parity differs the last
+// one of two or more steps is split into (n - 1) + 1.  For the expanded tiles,
+// whose one-step kernel costs less than a two-step launch saves (K = 3, nearly
+// equal and this: 4 steps, level-9 triangle 17.4 and 15.7 us; 8 steps, level-9
+// carpet at odd addresses 872 and 772).
+std::vector<int> plan_full_launches(int32_t steps, int K);
+
+// ---------------------------------------------------------------------------
 // Bit-sliced tile tables (Section "Moving from Thread-level to Block-level"):
 // a tile is a level-M subtree, a block a level-J subtree held as one LDS word.
 // ---------------------------------------------------------------------------

@@ -1,0 +1,63 @@
+// CPU checks of the launch plans (host_tables.cpp), built with AddressSanitizer
+// and UndefinedBehaviorSanitizer by tests/test_host_plans.py.
+#include <stdio.h>
+#include <stdlib.h>
+
+#include <vector>
+
+#include "host_tables.h"
+
+using namespace sqz;
+
+static int g_fail = 0;
+#define EXPECT(cond, ...)                                   \
+    do {                                                    \
+        if (!(cond)) {                                      \
+            fprintf(stderr, "FAILED %s:%d: ", __FILE__, __LINE__); \
+            fprintf(stderr, __VA_ARGS__);                   \
+            fprintf(stderr, "\n");                          \
+            if (++g_fail > 20) exit(1);                     \
+        }                                                   \
+    } while (0)
+
+// Sum, parity, bound, and as few launches as these allow.
+static void check_plan(const std::vector<int> &plan, int32_t steps, int K, const char *what)
+{
+    int64_t sum = 0;
+    for (int k : plan) {
+        EXPECT(k >= 1 && (K < 1 || k <= K), "%s steps %d K %d: a launch of %d", what, steps, K, k);
+        sum += k;
+    }
+    EXPECT(sum == steps, "%s steps %d K %d: %lld steps planned", what, steps, K, (long long)sum);
+    EXPECT((plan.size() & 1) == (size_t)(steps & 1), "%s steps %d K %d: parity of %zu launches", what, steps, K, plan.size());
+    int64_t n = steps < 1 ? 0 : (K < 1 ? 1 : ((int64_t)steps + K - 1) / K);
+    n += (n ^ steps) & 1;
+    EXPECT((int64_t)plan.size() == n, "%s steps %d K %d: %zu launches, want %lld", what, steps, K, plan.size(), (long long)n);
+}
+
+static void expect_full(int32_t steps, int K, const std::vector<int> &want)
+{
+    EXPECT(plan_full_launches(steps, K) == want, "full launches, steps %d K %d", steps, K);
+}
+
+int main()
+{
+    for (int K = 0; K <= 40; ++K)
+        for (int32_t steps = 0; steps <= 200; ++steps) {
+            check_plan(plan_launches(steps, K), steps, K, "equal");
+            if (K >= 2) check_plan(plan_full_launches(steps, K), steps, K, "full");
+        }
+    expect_full(4, 3, {3, 1});
+    expect_full(5, 3, {3, 1, 1});
+    expect_full(7, 3, {3, 3, 1});
+    expect_full(8, 3, {3, 3, 1, 1});
+    expect_full(9, 3, {3, 3, 3});
+    expect_full(2, 3, {1, 1});
+    expect_full(6, 4, {4, 2});
+    if (g_fail) {
+        fprintf(stderr, "%d check(s) failed\n", g_fail);
+        return 1;
+    }
+    printf("launch plans: all checks passed\n");
+    return 0;
+}
