@@ -332,7 +332,7 @@ static bool auto_resident(const FractalHost &h, int32_t steps)
     if (steps < 2 || !resident(h)) return false;
     if (steps >= kAutoResidentSteps) return true;
     const int K = tile_steps_per_launch(h);
-    return plan_launches(steps, K).size() > (size_t)((steps + K - 1) / K);
+    return (int64_t)plan_launches(steps, K).size() > launch_count(steps, K);
 }
 
 static sqz_status run_resident(const FractalHost &h, uint8_t *a, uint8_t *b, int32_t steps, hipStream_t st)

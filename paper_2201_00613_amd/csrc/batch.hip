@@ -989,7 +989,7 @@ static sqz_status launch_all(const BatchHost *H, const uint8_t *a, const uint8_t
             std::vector<int> plan = plan_launches(steps, K);
             // a launch that only sets the parity takes one step where that has a faster kernel
             // (256 fractals, 4 steps: 2 + 2 458 us, 3 + 1 430)
-            if (G.kind != kBBits && steps > 1 && K != 1 && (int)plan.size() > (K < 1 ? 1 : (steps + K - 1) / K)) {
+            if (G.kind != kBBits && steps > 1 && K != 1 && (int64_t)plan.size() > launch_count(steps, K)) {
                 plan = plan_launches(steps - 1, K);
                 plan.push_back(1);
             }

@@ -301,13 +301,23 @@ static std::vector<Pos> ring_subtrees(const FractalHost &F, int level, int64_t r
 // ---------------------------------------------------------------------------
 // Launch sizes
 // ---------------------------------------------------------------------------
+int64_t launch_count(int32_t steps, int K)
+{
+    return steps < 1 ? 0 : (K < 1 ? 1 : ((int64_t)steps + K - 1) / K);
+}
+
+int32_t launch_share(int32_t steps, int64_t n, int64_t i)
+{
+    return (int32_t)(steps * (i + 1) / n - steps * i / n);
+}
+
 std::vector<int> plan_launches(int32_t steps, int K)
 {
-    if (steps < 1) return {};
-    int n = K < 1 ? 1 : (int)(((int64_t)steps + K - 1) / K);
+    int64_t n = launch_count(steps, K);
     if ((n ^ steps) & 1) ++n;
     std::vector<int> plan;
-    for (int i = 0; i < n; ++i) plan.push_back((int)((int64_t)steps * (i + 1) / n - (int64_t)steps * i / n));
+    if (steps < 1) return plan;
+    for (int64_t i = 0; i < n; ++i) plan.push_back(launch_share(steps, n, i));
     return plan;
 }
 

@@ -135,6 +135,10 @@ int64_t host_nu(const FractalHost &F, int level, int64_t x, int64_t y);
 // the parity of `steps` for the result to land where one-step launches would
 // leave it.
 // ---------------------------------------------------------------------------
+// Least number of launches (K < 1: one for any number of steps), without regard
+// to parity, and steps of launch i of n nearly equal ones.
+int64_t launch_count(int32_t steps, int K);
+int32_t launch_share(int32_t steps, int64_t n, int64_t i);
 // Launches of nearly equal size (K < 1: any number of steps in one); one more
 // where the parity differs.
 std::vector<int> plan_launches(int32_t steps, int K);

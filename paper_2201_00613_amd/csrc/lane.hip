@@ -188,14 +188,15 @@ sqz_status lane_diffuse_run(const FractalHost &F, int dtype, float coef, int rou
 {
     const LaneConfig &L = *F.lane;
     if (steps < 1) return SQZ_OK;
-    int n = L.K ? (steps + L.K - 1) / L.K : 1;
+    int64_t n = launch_count(steps, L.K);
     if ((n ^ steps) & 1) ++n;
     XOp op;
     op.coef = coef;
     op.rounding = (uint32_t)rounding;
     op.seed = seed;
-    for (int i = 0, done = 0; i < n; ++i) {
-        const int k = (int)((int64_t)steps * (i + 1) / n) - done;
+    int32_t done = 0;
+    for (int64_t i = 0; i < n; ++i) {
+        const int32_t k = launch_share(steps, n, i);
         op.step = first + (uint64_t)done;
         const void *in = (i & 1) ? b : a;
         void *out = (i & 1) ? const_cast<void *>(a) : b;

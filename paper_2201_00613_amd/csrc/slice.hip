@@ -343,10 +343,10 @@ sqz_status slice_run_launches(const FractalHost &F, uint8_t *a, uint8_t *b, int 
 {
     const SliceConfig &S = *F.slice;
     if (steps < 1) return SQZ_OK;
-    const int K = S.K ? (int)S.K : steps, n = (steps + K - 1) / K;
+    const int64_t n = launch_count(steps, (int)S.K);
     uint8_t *cur = a, *other = b;
-    for (int i = 0, done = 0; i < n; ++i) {
-        const int k = (int)((int64_t)steps * (i + 1) / n) - done;
+    for (int64_t i = 0; i < n; ++i) {
+        const int32_t k = launch_share(steps, n, i);
         const bool in_place = i == n - 1 && ((n ^ steps) & 1);
         if (in_place && S.A.nring)
             hipLaunchKernelGGL(k_slice_corners, dim3((unsigned)((S.A.ntiles * S.A.ncorner + 3) / 4)), dim3(256), 0, st,
@@ -361,7 +361,6 @@ sqz_status slice_run_launches(const FractalHost &F, uint8_t *a, uint8_t *b, int 
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return hip_error(e, "compact run (slice) launch");
         if (!in_place) std::swap(cur, other);
-        done += k;
     }
     return SQZ_OK;
 }

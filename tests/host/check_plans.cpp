@@ -47,6 +47,20 @@ int main()
             check_plan(plan_launches(steps, K), steps, K, "equal");
             if (K >= 2) check_plan(plan_full_launches(steps, K), steps, K, "full");
         }
+    // counts near the largest int32, where steps + K - 1 leaves its range
+    for (int K : {0, 1, 15, 27, 31})
+        for (int32_t steps : {1 << 30, (1 << 30) + 1, 0x7FFFFFFF - 14, 0x7FFFFFFF}) {
+            const int64_t n = launch_count(steps, K);
+            EXPECT(n >= 1 && (K < 1 ? n == 1 : n * K >= steps && (n - 1) * K < steps), "launches of %d steps, K %d", steps, K);
+            int64_t first = 0, last = 0;
+            for (int64_t i = 0; i < n && i < 1000; ++i) {
+                first += launch_share(steps, n, i);
+                last += launch_share(steps, n, n - 1 - i);
+                EXPECT(launch_share(steps, n, i) >= 1 && (K < 1 || launch_share(steps, n, i) <= K), "share of %d steps, K %d", steps, K);
+            }
+            const int64_t m = n < 1000 ? n : 1000;
+            EXPECT(first == steps * m / n && last == steps - steps * (n - m) / n, "shares of %d steps, K %d", steps, K);
+        }
     expect_full(4, 3, {3, 1});
     expect_full(5, 3, {3, 1, 1});
     expect_full(7, 3, {3, 3, 1});
