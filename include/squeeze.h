@@ -420,8 +420,9 @@ SQZ_API sqz_status sqz_batch_step(const sqz_batch *b, const uint8_t *d_in, uint8
  * the same buffers and step count) and replayed. */
 SQZ_API sqz_status sqz_batch_run(sqz_batch *b, uint8_t *d_a, uint8_t *d_b, int32_t steps, void *stream);
 
-/* Steps every instance advances per launch of sqz_batch_run at least: the smallest steps per
- * launch over the launch forms in use (1 when some instance has no multi-step tiles). */
+/* Steps every instance advances per launch of sqz_batch_run at least, where the run has as many:
+ * the smallest steps per launch over the launch forms in use (1 when some instance has no
+ * multi-step tiles). */
 SQZ_API sqz_status sqz_batch_steps_per_launch(const sqz_batch *b, int32_t *steps);
 
 /* Launch form of the instances with a tiled kernel (triangle, its mirror image, Vicsek cross:
@@ -431,7 +432,8 @@ SQZ_API sqz_status sqz_batch_steps_per_launch(const sqz_batch *b, int32_t *steps
  *                   each taking an equal share of the tiles' cells;
  *   persistent = 2: one launch over all of them, one workgroup per tile (wg_per_cu unused).
  * steps_per_launch: 0 keeps the current value, else 1 .. the most the instances allow (for
- * groups, capped at each group's most).  wg_per_cu: 0 keeps the current value, else 1 .. the
+ * groups, capped at each group's most; groups for which none was chosen take as many steps as
+ * their tiles can, 15 and more).  wg_per_cu: 0 keeps the current value, else 1 .. the
  * most that are resident.  Other values: SQZ_ERR_INVALID.  Results do not depend on the form. */
 SQZ_API sqz_status sqz_batch_set_tiled_launch(sqz_batch *b, int32_t persistent, int32_t steps_per_launch,
                                               int32_t wg_per_cu);

@@ -420,8 +420,8 @@ k_batch_tiles(TiledArgs B, const uint8_t *in, uint8_t *out, int32_t steps)
 // ---------------------------------------------------------------------------
 struct BatchGroup {
     uint32_t kind;  // kBTri, kBTriPaper, kBVicsek or kBBits
-    int K, K_max;   // steps per launch: chosen, most that can be chosen
-    int K_full;     // steps a launch can take at most (bit-sliced tiles: more than K_max; 0: any number)
+    int K, K_max;   // steps per launch: chosen (0: none, a launch takes K_full), most that can be chosen
+    int K_full;     // steps a launch can take at most (more than K_max; 0: any number)
     unsigned threads;
     std::vector<uint32_t> members;
     uint64_t ntiles, ntiles1;  // tiles; of launches of one step (but kBBits)
@@ -627,7 +627,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
             for (BatchGroup &g : H->groups)
                 if (g.kind == I.kind) G = &g;
             if (!G) {
-                H->groups.push_back(BatchGroup{I.kind, kMaxSteps, kMaxSteps, 0, 64, {}, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr});
+                H->groups.push_back(BatchGroup{I.kind, 0, kMaxSteps, 0, 64, {}, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr});
                 G = &H->groups.back();
             }
             if (I.kind == kBBits) {
@@ -640,7 +640,6 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
             }
             G->members.push_back((uint32_t)i);
             G->K_max = std::min(G->K_max, I.kind == kBBits ? kMaxSteps : tile_steps_per_launch(F));
-            G->K = G->K_max;
             I.units = 0;  // not in the expanded-tile / thread-level launch
             I.unit_cells = 1;
         } else if (I.kind != kBCell) {
@@ -983,18 +982,10 @@ static sqz_status launch_all(const BatchHost *H, const uint8_t *a, const uint8_t
             s2 = launch_tiled(H, H->tiled_form, H->twg, (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
     } else {
         for (size_t g = 0; g < H->groups.size() && s2 == SQZ_OK; ++g) {
-            // the most the tiles can take, unless fewer were chosen
             const BatchGroup &G = H->groups[g];
-            const int K = G.K < G.K_max ? G.K : G.K_full;
-            std::vector<int> plan = plan_launches(steps, K);
-            // a launch that only sets the parity takes one step where that has a faster kernel
-            // (256 fractals, 4 steps: 2 + 2 458 us, 3 + 1 430)
-            if (G.kind != kBBits && steps > 1 && K != 1 && (int64_t)plan.size() > launch_count(steps, K)) {
-                plan = plan_launches(steps - 1, K);
-                plan.push_back(1);
-            }
+            const std::vector<int> plan = plan_group_launches(steps, G.K, G.K_full, G.kind != kBBits);
             for (size_t i = 0; i < plan.size() && s2 == SQZ_OK; ++i)
-                s2 = launch_group(H->groups[g], (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
+                s2 = launch_group(G, (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
         }
     }
     if (H->has_rest) {
@@ -1198,7 +1189,7 @@ int batch_steps_per_launch(const BatchHost *H)
     if (!H->tiled.empty() && H->tiled_form != 0)
         k = std::min(k, H->Kt);
     else
-        for (const BatchGroup &G : H->groups) k = std::min(k, G.K);
+        for (const BatchGroup &G : H->groups) k = std::min(k, G.K ? G.K : G.K_max);
     return k < 1 ? 1 : k;
 }
 uint64_t batch_total_cells(const BatchHost *H) { return H->total_cells; }

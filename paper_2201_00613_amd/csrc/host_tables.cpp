@@ -336,6 +336,17 @@ std::vector<int> plan_full_launches(int32_t steps, int K)
     return plan;
 }
 
+std::vector<int> plan_group_launches(int32_t steps, int chosen, int full, bool one_step)
+{
+    const int K = chosen ? chosen : full;
+    std::vector<int> plan = plan_launches(steps, K);
+    if (one_step && steps > 1 && K != 1 && (int64_t)plan.size() > launch_count(steps, K)) {
+        plan = plan_launches(steps - 1, K);
+        plan.push_back(1);
+    }
+    return plan;
+}
+
 // ---------------------------------------------------------------------------
 // Bit-sliced tiles
 // ---------------------------------------------------------------------------

@@ -148,6 +148,11 @@ std::vector<int> plan_launches(int32_t steps, int K);
 // equal and this: 4 steps, level-9 triangle 17.4 and 15.7 us; 8 steps, level-9
 // carpet at odd addresses 872 and 772).
 std::vector<int> plan_full_launches(int32_t steps, int K);
+// Launches of a batch's pattern group: at most `chosen` steps each, or (0: none
+// chosen) the `full` ones its tiles can take (0: any number).  With one_step a
+// launch that only sets the parity takes one step, which has a faster kernel
+// (256 fractals, 4 steps: 2 + 2 458 us, 3 + 1 430).
+std::vector<int> plan_group_launches(int32_t steps, int chosen, int full, bool one_step);
 
 // ---------------------------------------------------------------------------
 // Bit-sliced tile tables (Section "Moving from Thread-level to Block-level"):

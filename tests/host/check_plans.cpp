@@ -47,6 +47,14 @@ int main()
             check_plan(plan_launches(steps, K), steps, K, "equal");
             if (K >= 2) check_plan(plan_full_launches(steps, K), steps, K, "full");
         }
+    // a group's launches: no more steps than chosen, the tiles' most without a choice
+    for (int chosen : {0, 1, 2, 7, 10})
+        for (int full : {0, 15, 27, 31})
+            for (int32_t steps = 0; steps <= 200; ++steps)
+                for (bool one : {false, true})
+                    check_plan(plan_group_launches(steps, chosen, full, one), steps, chosen ? chosen : full, "group");
+    EXPECT(plan_group_launches(30, 10, 31, true) == (std::vector<int>{9, 10, 10, 1}), "ten chosen");
+    EXPECT(plan_group_launches(30, 0, 31, true) == (std::vector<int>{29, 1}), "none chosen");
     // counts near the largest int32, where steps + K - 1 leaves its range
     for (int K : {0, 1, 15, 27, 31})
         for (int32_t steps : {1 << 30, (1 << 30) + 1, 0x7FFFFFFF - 14, 0x7FFFFFFF}) {
