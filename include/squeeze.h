@@ -446,7 +446,8 @@ SQZ_API sqz_status sqz_batch_tiled_launch(const sqz_batch *b, int32_t *form, int
 
 /* Time candidate launch shapes on the given buffers (their contents are advanced by a few steps)
  * and keep the fastest for this batch and for later batches of the same composition in this
- * process: for the tiled instances, steps per launch of each pattern group against one launch
+ * process: for the tiled instances, steps per launch of each pattern group (none chosen, or up to
+ * the most that can be) against one launch
  * over all of them (steps per launch x one workgroup per tile or persistent workgroups per
  * compute unit); for the others, workgroups
  * per compute unit and the expanded-tile cost weight.  *wg_per_cu (may be NULL) receives the

@@ -1055,25 +1055,25 @@ sqz_status batch_autotune(BatchHost *H, uint8_t *a, uint8_t *b, hipStream_t st, 
         return set_error(SQZ_ERR_HIP, "hipEventCreate failed");
     sqz_status st2 = SQZ_OK;
     // (1) the tiled instances, each candidate timed per step over four
-    // launches of its steps per launch: one launch per pattern group (steps
-    // per launch per group), against one persistent launch (workgroups per CU
-    // x steps per launch)
+    // launches of its steps per launch: one launch per pattern group (per group
+    // the steps an untuned run takes, or fewer), against one launch over all of
+    // them (steps per launch x workgroups per CU or one per tile)
     if (!H->tiled.empty()) {
         const int ks[] = {1, 2, 3, 4, 5, 6, 8, 10};
         float grouped_ms = 0.0f;
         for (BatchGroup &G : H->groups) {
             float best_ms = 1e30f;
             int bk = G.K;
-            for (int K : ks) {
-                if (K > G.K_max || (K == 1 && G.K_max > 1) || st2 != SQZ_OK) continue;
+            for (const GroupChoice &C : group_choices(G.K_max, G.K_full)) {
+                if (st2 != SQZ_OK) continue;
                 float ms = 0.0f;
                 st2 = time_launches(st, e0, e1, [&](int i) {
-                    return launch_group(G, (i & 1) ? b : a, (i & 1) ? a : b, K, st);
+                    return launch_group(G, (i & 1) ? b : a, (i & 1) ? a : b, C.steps, st);
                 }, 4, &ms);
-                ms /= 4.0f * K;
+                ms /= 4.0f * C.steps;
                 if (st2 == SQZ_OK && ms < best_ms) {
                     best_ms = ms;
-                    bk = K;
+                    bk = C.chosen;
                 }
             }
             G.K = bk;

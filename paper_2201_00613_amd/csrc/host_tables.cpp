@@ -347,6 +347,14 @@ std::vector<int> plan_group_launches(int32_t steps, int chosen, int full, bool o
     return plan;
 }
 
+std::vector<GroupChoice> group_choices(int most, int full)
+{
+    std::vector<GroupChoice> v(1, GroupChoice{0, full ? full : 32});  // any number: a long launch
+    for (int K : {1, 2, 3, 4, 5, 6, 8, 10})
+        if (K <= most && (K > 1 || most == 1)) v.push_back(GroupChoice{K, K});
+    return v;
+}
+
 // ---------------------------------------------------------------------------
 // Bit-sliced tiles
 // ---------------------------------------------------------------------------

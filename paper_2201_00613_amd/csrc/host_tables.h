@@ -153,6 +153,13 @@ std::vector<int> plan_full_launches(int32_t steps, int K);
 // launch that only sets the parity takes one step, which has a faster kernel
 // (256 fractals, 4 steps: 2 + 2 458 us, 3 + 1 430).
 std::vector<int> plan_group_launches(int32_t steps, int chosen, int full, bool one_step);
+// What the batch tuner times for a group: choices of steps per launch and the steps
+// a launch then takes in a long run.  The first is no choice (0), what an untuned
+// batch runs; most: the most that can be chosen.
+struct GroupChoice {
+    int chosen, steps;
+};
+std::vector<GroupChoice> group_choices(int most, int full);
 
 // ---------------------------------------------------------------------------
 // Bit-sliced tile tables (Section "Moving from Thread-level to Block-level"):

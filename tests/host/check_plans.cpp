@@ -55,6 +55,18 @@ int main()
                     check_plan(plan_group_launches(steps, chosen, full, one), steps, chosen ? chosen : full, "group");
     EXPECT(plan_group_launches(30, 10, 31, true) == (std::vector<int>{9, 10, 10, 1}), "ten chosen");
     EXPECT(plan_group_launches(30, 0, 31, true) == (std::vector<int>{29, 1}), "none chosen");
+    // the tuner times what an untuned run takes, and every choice as it would run
+    for (int most : {1, 7, 8, 10})
+        for (int full : {0, 15, 27, 31}) {
+            const std::vector<GroupChoice> v = group_choices(most, full);
+            EXPECT(v[0].chosen == 0 && (full ? v[0].steps == full : v[0].steps > 10), "no choice is timed, full %d", full);
+            for (size_t i = 1; i < v.size(); ++i)
+                EXPECT(v[i].chosen >= 1 && v[i].chosen <= most && v[i].steps == v[i].chosen, "choice %zu of at most %d", i, most);
+            for (const GroupChoice &c : v) {
+                const std::vector<int> plan = plan_group_launches(8 * c.steps, c.chosen, full, false);
+                for (int k : plan) EXPECT(full ? k == c.steps : k >= c.steps, "choice %d runs %d steps, timed %d", c.chosen, k, c.steps);
+            }
+        }
     // counts near the largest int32, where steps + K - 1 leaves its range
     for (int K : {0, 1, 15, 27, 31})
         for (int32_t steps : {1 << 30, (1 << 30) + 1, 0x7FFFFFFF - 14, 0x7FFFFFFF}) {
