@@ -428,9 +428,11 @@ SQZ_API sqz_status sqz_batch_steps_per_launch(const sqz_batch *b, int32_t *steps
 /* Launch form of the instances with a tiled kernel (triangle, its mirror image, Vicsek cross:
  * bit-sliced tiles; carpet: bit rows):
  *   persistent = 0: one launch per pattern group, one workgroup per tile (the default);
- *   persistent = 1: one persistent launch over all of them, wg_per_cu workgroups per compute unit,
+ *   persistent = 1: one persistent launch over all of them, wg_per_cu workgroups per compute unit
+ *                   (as many as are resident),
  *                   each taking an equal share of the tiles' cells;
- *   persistent = 2: one launch over all of them, one workgroup per tile (wg_per_cu unused).
+ *   persistent = 2: one launch over all of them, one workgroup per tile or few tiles (wg_per_cu
+ *                   unused).
  * steps_per_launch: 0 keeps the current value, else 1 .. the most the instances allow (for
  * groups, capped at each group's most; groups for which none was chosen take as many steps as
  * their tiles can, 15 and more).  wg_per_cu: 0 keeps the current value, else 1 .. the

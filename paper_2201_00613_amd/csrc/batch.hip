@@ -223,16 +223,26 @@ __device__ __forceinline__ void tiny_tile(const SliceArgs &A, const uint8_t *in,
         if (c[t] < N) out[c[t]] = v[(steps & 1) * kTinyCells + c[t]];
 }
 
-// One tile of an instance.
-template <class P>
-__device__ __forceinline__ void slice_unit(const SliceArgs &A, const uint8_t *in, uint8_t *out, uint64_t t,
+// Unit u of an instance: one tile on all lanes of the workgroup or, PACKED, a tile
+// per SliceCfg<P>::LANES lanes (lane groups past the last tile repeat it).
+constexpr uint32_t kTiledThreads = 256;  // of the launches over all tiled instances
+
+template <class P, bool PACKED>
+__device__ __forceinline__ void slice_unit(const SliceArgs &A, const uint8_t *in, uint8_t *out, uint64_t u,
                                            int32_t steps, uint32_t *sm)
 {
     static_assert(SliceCfg<P>::LDS >= 2 * kTinyCells, "LDS of a small fractal");
-    if (A.words == 0)
+    if (A.words == 0) {
         tiny_tile(A, in, out, steps, sm);
-    else
-        slice_tile<P, false>(A, in, out, t, SliceRing{in, false}, steps, SliceRes{}, sm);
+    } else if constexpr (PACKED) {
+        constexpr uint32_t L = SliceCfg<P>::LANES;
+        const uint32_t g = __builtin_amdgcn_readfirstlane(threadIdx.x / L);
+        const uint64_t t = u * (kTiledThreads / L) + g;
+        slice_tile<P, false>(A, in, out, t < A.ntiles ? t : A.ntiles - 1, SliceRing{in, false}, steps, SliceRes{},
+                             sm + g * (SliceCfg<P>::LDS / 4), threadIdx.x % L, L);
+    } else {
+        slice_tile<P, false>(A, in, out, u, SliceRing{in, false}, steps, SliceRes{}, sm, threadIdx.x, blockDim.x);
+    }
 }
 
 // One group: instances of one tiled pattern, one workgroup per tile.
@@ -271,7 +281,7 @@ k_batch_slice(GroupArgs G, const uint8_t *in, uint8_t *out, int32_t steps)
     const uint32_t i = group_instance(G, b);
     const SliceArgs A = reinterpret_cast<const SliceArgs *>(G.args)[i];
     const uint64_t base = G.base[i];
-    slice_unit<P>(A, in + base, out + base, b - G.tstart[i], steps, sm);
+    slice_unit<P, false>(A, in + base, out + base, b - G.tstart[i], steps, sm);
 }
 
 // A launch of one step: the bit-sliced blocks, whose loads and stores are 16
@@ -303,63 +313,91 @@ k_batch_bitbox(GroupArgs G, const uint8_t *__restrict__ in, uint8_t *__restrict_
     bitbox_tile<Pat>(A, in + base, out + base, b - G.tstart[i], steps, sm);
 }
 
-// Instance of the persistent tiled launch (patterns with a tiled kernel).
+// Instance of a launch over all tiled instances (patterns with a tiled kernel).
+// A unit is what a workgroup takes at a time: a tile, or as many triangle tiles as
+// it has waves.  A level-8 triangle tile has lanes for one wave of four, which the
+// others help only to load and store: alone they are ahead while a workgroup per
+// tile leaves room on the chip (32 level-10 triangles, 10 steps at 3 a launch: 29.6
+// against 42 us), together where it does not (512 mixed fractals, 50 steps: 3.66 ->
+// 2.99 ms, with the carpet's tiles at normal priority).
 struct TiledInst {
     uint32_t kind;        // kBTri, kBTriPaper, kBVicsek or kBBits
     uint32_t pad;
     uint64_t base;        // byte offset of the instance in the state buffer
-    uint64_t units;       // tiles
-    uint64_t unit_cells;  // cells per tile
+    uint64_t units;       // units of the instance
+    uint64_t unit_cells;  // cells per unit
     uint64_t cost_start;  // first cost unit (cell) of the instance
-    SliceArgs t;
+    SliceArgs t;          // launches of several steps
+    TileArgs t1;          // launches of one step (see k_batch_tile)
     BitboxArgs x;
 };
+
+enum TiledMode { kTiledOne, kTiledSingle, kTiledPacked };  // one step; several, a tile or a tile per wave
+constexpr int kTiledWaves = 6;  // waves per SIMD of the workgroup-per-unit form, packed
+constexpr int tiled_waves(bool per_tile, TiledMode m)
+{
+    return m == kTiledOne ? (per_tile ? 8 : 6) : (m == kTiledPacked && per_tile ? kTiledWaves : 5);
+}
 
 struct TiledArgs {
     const TiledInst *inst;
     const uint64_t *cost_start;  // ninst + 1 entries
-    const uint64_t *tile_start;  // ninst + 1 prefix sums of tile counts
-    const uint32_t *tile_map;    // workgroup-per-tile form: instance << 20 | tile, one entry per tile (or null)
+    const uint64_t *tile_start;  // ninst + 1 prefix sums of unit counts
+    const uint32_t *tile_map;    // workgroup-per-unit form: instance << 20 | unit, one entry per unit (or null)
     uint32_t ninst;
     uint64_t total_cost;
 };
 
-template <class P>
-__device__ __forceinline__ void tiled_unit(const TiledInst &I, const uint8_t *in, uint8_t *out, uint64_t t, int32_t steps,
-                                           unsigned char *smem)
+template <class P, bool PACKED>
+__device__ __forceinline__ void tiled_unit(const TiledInst &I, const uint8_t *in, uint8_t *out, uint64_t u, int32_t steps,
+                                           uint32_t *sm)
 {
-    slice_unit<P>(I.t, in, out, t, steps, reinterpret_cast<uint32_t *>(smem));
-    __syncthreads();  // LDS is free for the next tile
+    slice_unit<P, PACKED>(I.t, in, out, u, steps, sm);
+    __syncthreads();  // LDS is free for the next unit
 }
 
-__device__ __forceinline__ void tiled_run(const TiledInst &I, const uint8_t *in, uint8_t *out, uint64_t j, int32_t steps,
-                                          unsigned char *smem)
+template <class Pat>
+__device__ __forceinline__ void tiled_unit1(const TiledInst &I, const uint8_t *in, uint8_t *out, uint64_t u, uint32_t *sm)
+{
+    tile_body<Pat, kTiledThreads>(I.t1, in, out, u, sm, sm + TileLds<Pat>::WORDS);
+}
+
+template <TiledMode MODE>
+__device__ __forceinline__ void tiled_run(const TiledInst &I, const uint8_t *in, uint8_t *out, uint64_t u, int32_t steps,
+                                          uint32_t *sm)
 {
     const uint8_t *ii = in + I.base;
     uint8_t *oo = out + I.base;
-    switch (I.kind) {
-    case kBTri: tiled_unit<SliceTriSmall>(I, ii, oo, j, steps, smem); break;
-    case kBTriPaper: tiled_unit<SlicePaperSmall>(I, ii, oo, j, steps, smem); break;
-    case kBVicsek: tiled_unit<SliceVicsekSmall>(I, ii, oo, j, steps, smem); break;
-    default:
-        bitbox_tile<PatCarpet>(I.x, ii, oo, j, steps, reinterpret_cast<uint32_t *>(smem));
+    if (I.kind == kBBits) {
+        bitbox_tile<PatCarpet, false>(I.x, ii, oo, u, steps, sm);
         __syncthreads();
-        break;
+    } else if constexpr (MODE == kTiledOne) {
+        switch (I.kind) {
+        case kBTri: tiled_unit1<PatTriangle>(I, ii, oo, u, sm); break;
+        case kBTriPaper: tiled_unit1<PatTrianglePaper>(I, ii, oo, u, sm); break;
+        default: tiled_unit1<PatVicsek>(I, ii, oo, u, sm); break;
+        }
+    } else {
+        switch (I.kind) {
+        case kBTri: tiled_unit<SliceTriSmall, MODE == kTiledPacked>(I, ii, oo, u, steps, sm); break;
+        case kBTriPaper: tiled_unit<SlicePaperSmall, MODE == kTiledPacked>(I, ii, oo, u, steps, sm); break;
+        default: tiled_unit<SliceVicsekSmall, false>(I, ii, oo, u, steps, sm); break;
+        }
     }
 }
 
-// `steps` Life steps of every instance with a tiled kernel in one launch: the tiles
-// of all such instances form one sequence, each run with its pattern's tile
-// body (bit-sliced tiles of the triangle, its mirror image and the Vicsek
-// cross; bit rows of the carpet).  Persistent (PerTile false): the sequence
-// is weighted by cells and workgroup b takes the tiles whose first cell falls
-// in the b-th equal share.  PerTile: one workgroup per tile, dealt to the
+// `steps` Life steps (kTiledOne: one) of every instance with a tiled kernel in one
+// launch: the units of all such instances form one sequence, each run with its
+// pattern's tile body (bit-sliced tiles of the triangle, its mirror image and the
+// Vicsek cross; bit rows of the carpet).  Persistent (PerTile false): the sequence
+// is weighted by cells and workgroup b takes the units whose first cell falls
+// in the b-th equal share.  PerTile: one workgroup per unit, dealt to the
 // XCDs in contiguous runs.
-template <bool PerTile>
-__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(5)))
+template <bool PerTile, TiledMode MODE>
+__global__ void __launch_bounds__(kTiledThreads) __attribute__((amdgpu_waves_per_eu(tiled_waves(PerTile, MODE))))
 k_batch_tiles(TiledArgs B, const uint8_t *in, uint8_t *out, int32_t steps)
 {
-    extern __shared__ __align__(16) unsigned char smem[];
+    extern __shared__ __align__(16) uint32_t smem32[];
     if constexpr (PerTile) {
         // one call site of the tile bodies (each inlined once: the kernel's
         // code must stay small enough for the instruction cache)
@@ -381,7 +419,7 @@ k_batch_tiles(TiledArgs B, const uint8_t *in, uint8_t *out, int32_t steps)
             }
             j = b - B.tile_start[a];
         }
-        tiled_run(B.inst[a], in, out, j, steps, smem);
+        tiled_run<MODE>(B.inst[a], in, out, j, steps, smem32);
         return;
     }
     const uint64_t lo = B.total_cost * blockIdx.x / gridDim.x;
@@ -408,7 +446,7 @@ k_batch_tiles(TiledArgs B, const uint8_t *in, uint8_t *out, int32_t steps)
             continue;
         }
         if (I.cost_start + j * I.unit_cells >= hi) break;
-        tiled_run(I, in, out, j, steps, smem);
+        tiled_run<MODE>(I, in, out, j, steps, smem32);
         ++j;  // every tile body ends with a barrier: LDS is free for the next tile
     }
 }
@@ -429,6 +467,17 @@ struct BatchGroup {
     uint64_t *d_base, *d_tstart, *d_tstart1;
 };
 
+// The launches over all tiled instances, of several steps or of one.
+struct TiledLaunch {
+    TiledInst *d_inst;
+    uint64_t *d_cost, *d_start;
+    uint32_t *d_map;  // unit order of the workgroup-per-unit form (null: instance order)
+    uint64_t cost_total, units_total;
+    size_t lds;
+    TiledMode mode;
+    unsigned wg_max;     // workgroups per CU of the persistent form that are on the chip at once
+};
+
 struct BatchHost {
     // instances with a tiled kernel run as one launch per pattern group
     // (tiled_form 0), one persistent launch over all of them (1) or one launch
@@ -438,11 +487,7 @@ struct BatchHost {
     std::vector<SliceConfig *> slices;  // tile configurations that are not a fractal's own
     int tiled_form;
     std::vector<TiledInst> tiled;
-    TiledInst *d_tiled;
-    uint64_t *d_tcost, *d_ttiles;
-    uint32_t *d_tmap;  // tile order of the workgroup-per-tile form (null: instance order)
-    uint64_t tcost_total, ttiles_total;
-    size_t tlds;
+    TiledLaunch tmulti, tone;   // of several steps, of one step
     int Kt_max, Kt;             // steps per launch: most allowed, chosen
     unsigned twg, twg_max;      // workgroups per CU: chosen, most resident
     bool has_rest;  // instances for the persistent expanded-tile / thread-level launch
@@ -543,6 +588,100 @@ static hipError_t upload_costs(BatchHost *H)
     return e;
 }
 
+// Units, order and prefix sums of a launch over all tiled instances.
+static hipError_t tiled_setup(const std::vector<TiledInst> &all, int cus, bool one_step, TiledLaunch *L)
+{
+    std::vector<TiledInst> inst(all);
+    const size_t m = inst.size();
+    auto tiles = [&](const TiledInst &T) {
+        return T.kind == kBBits ? T.x.ntiles : (one_step ? T.t1.ntiles : T.t.ntiles);
+    };
+    uint64_t total = 0;
+    for (const TiledInst &T : inst) total += tiles(T);
+    constexpr uint32_t TL = SliceCfg<SliceTriSmall>::LANES;
+    static_assert(TL == SliceCfg<SlicePaperSmall>::LANES && kTiledThreads % TL == 0, "lanes of a triangle tile");
+    L->mode = one_step ? kTiledOne : (total > (uint64_t)kTiledWaves * (uint64_t)cus ? kTiledPacked : kTiledSingle);
+    for (TiledInst &T : inst) {
+        const bool tri = T.kind == kBTri || T.kind == kBTriPaper;
+        const uint32_t pack = tri && L->mode == kTiledPacked ? kTiledThreads / TL : 1;
+        auto lds = [&](auto slice, auto pat) {
+            return one_step ? 8u * TileLds<decltype(pat)>::WORDS : pack * SliceCfg<decltype(slice)>::LDS;
+        };
+        size_t need = 0;
+        switch (T.kind) {
+        case kBBits: need = kBxLds * 4; break;
+        case kBTri: need = lds(SliceTriSmall{}, PatTriangle{}); break;
+        case kBTriPaper: need = lds(SlicePaperSmall{}, PatTrianglePaper{}); break;
+        default: need = lds(SliceVicsekSmall{}, PatVicsek{}); break;
+        }
+        L->lds = std::max(L->lds, need);
+        T.units = (tiles(T) + pack - 1) / pack;
+        T.unit_cells = (uint64_t)pack * (T.kind == kBBits ? T.x.tile : (one_step ? T.t1.tile : T.t.cells));
+    }
+    // The instances in an order that spreads every pattern kind evenly over the
+    // launch (each instance keyed by the middle of its share of its kind's cells),
+    // so that the workgroups on the chip at any time mix tile bodies that load
+    // different units (vector ALU, LDS, memory); instances of one kind keep their
+    // relative order.
+    if (SQZ_BATCH_INTERLEAVE) {
+        std::map<uint32_t, uint64_t> kind_total, kind_seen;
+        for (const TiledInst &T : inst) kind_total[T.kind] += T.units * T.unit_cells;
+        std::vector<std::pair<double, size_t>> key(m);
+        for (size_t q = 0; q < m; ++q) {
+            const TiledInst &T = inst[q];
+            const uint64_t c = T.units * T.unit_cells;
+            key[q] = {(kind_seen[T.kind] + 0.5 * (double)c) / (double)kind_total[T.kind], q};
+            kind_seen[T.kind] += c;
+        }
+        std::stable_sort(key.begin(), key.end());
+        std::vector<TiledInst> ord;
+        ord.reserve(m);
+        for (const auto &k : key) ord.push_back(inst[k.second]);
+        inst.swap(ord);
+    }
+    std::vector<uint64_t> cs(m + 1), us(m + 1);
+    for (size_t q = 0; q < m; ++q) {
+        TiledInst &T = inst[q];
+        T.cost_start = cs[q] = L->cost_total;
+        us[q] = L->units_total;
+        L->cost_total += T.units * T.unit_cells;
+        L->units_total += T.units;
+    }
+    cs[m] = L->cost_total;
+    us[m] = L->units_total;
+    auto upload = [](auto **d, const auto &h) {
+        const size_t bytes = h.size() * sizeof(h[0]);
+        hipError_t e = hipMalloc(d, bytes);
+        return e == hipSuccess ? hipMemcpy(*d, h.data(), bytes, hipMemcpyHostToDevice) : e;
+    };
+    hipError_t e = upload(&L->d_inst, inst);
+    if (e == hipSuccess) e = upload(&L->d_cost, cs);
+    if (e == hipSuccess) e = upload(&L->d_start, us);
+    // workgroup-per-unit order: the units of every pattern kind spread evenly over
+    // the launch, each keyed by the middle of its place among its kind's units
+    bool fits = m < 4096;
+    for (size_t q = 0; q < m && fits; ++q) fits = inst[q].units <= 0xFFFFFu;
+    if (e == hipSuccess && fits && SQZ_BATCH_TILE_MAP) {
+        std::map<uint32_t, uint64_t> kind_units, kind_seen;
+        for (const TiledInst &T : inst) kind_units[T.kind] += T.units;
+        std::vector<std::pair<double, uint32_t>> key;
+        key.reserve(L->units_total);
+        for (size_t q = 0; q < m; ++q) {
+            const double n = (double)kind_units[inst[q].kind];
+            for (uint64_t j = 0; j < inst[q].units; ++j)
+                key.push_back({((double)kind_seen[inst[q].kind]++ + 0.5) / n, (uint32_t)(q << 20 | j)});
+        }
+        std::stable_sort(key.begin(), key.end(),
+                         [](const std::pair<double, uint32_t> &x, const std::pair<double, uint32_t> &y) {
+                             return x.first < y.first;
+                         });
+        std::vector<uint32_t> map(key.size());
+        for (size_t i = 0; i < key.size(); ++i) map[i] = key[i].second;
+        e = upload(&L->d_map, map);
+    }
+    return e;
+}
+
 sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost **out)
 {
     BatchHost *H = new BatchHost();
@@ -599,9 +738,6 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
             T.base = off;
             if (I.kind == kBBits) {
                 T.x = bitbox_args(F);
-                T.units = T.x.ntiles;
-                T.unit_cells = T.x.tile;
-                H->tlds = std::max<size_t>(H->tlds, kBxLds * 4);
             } else {
                 SliceConfig *&C = slice_of[&F];
                 if (!C && F.slice) {
@@ -614,14 +750,9 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
                     }
                 }
                 T.t = C ? C->A : tiny_args(F, H->d_tiny + tiny_of[&F]);
-                T.units = T.t.ntiles;
-                T.unit_cells = T.t.cells;
+                T.t1 = tile_args(F);
                 H->Kt_max = std::min(H->Kt_max, tile_steps_per_launch(F));
-                H->tlds = std::max<size_t>(H->tlds, I.kind == kBVicsek ? SliceCfg<SliceVicsekSmall>::LDS
-                                                                       : SliceCfg<SliceTriSmall>::LDS);
             }
-            T.cost_start = H->tcost_total;
-            H->tcost_total += T.units * T.unit_cells;
             H->tiled.push_back(T);
             BatchGroup *G = nullptr;
             for (BatchGroup &g : H->groups)
@@ -689,32 +820,6 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
     }
     cell_start[count] = cstart;
     H->offsets[count] = off;
-    // The tiled launch forms take the instances in an order that spreads every
-    // pattern kind evenly over the launch (each instance keyed by the middle
-    // of its share of its kind's cells), so that the workgroups on the chip at
-    // any time mix tile bodies that load different units (vector ALU, LDS,
-    // memory); instances of one kind keep their relative order.
-    if (SQZ_BATCH_INTERLEAVE) {
-        std::map<uint32_t, uint64_t> kind_total, kind_seen;
-        for (const TiledInst &T : H->tiled) kind_total[T.kind] += T.units * T.unit_cells;
-        std::vector<std::pair<double, size_t>> key(H->tiled.size());
-        for (size_t q = 0; q < H->tiled.size(); ++q) {
-            const TiledInst &T = H->tiled[q];
-            const uint64_t c = T.units * T.unit_cells;
-            key[q] = {(kind_seen[T.kind] + 0.5 * (double)c) / (double)kind_total[T.kind], q};
-            kind_seen[T.kind] += c;
-        }
-        std::stable_sort(key.begin(), key.end());
-        std::vector<TiledInst> ord;
-        ord.reserve(H->tiled.size());
-        for (const auto &k : key) ord.push_back(H->tiled[k.second]);
-        H->tiled.swap(ord);
-        H->tcost_total = 0;
-        for (TiledInst &T : H->tiled) {
-            T.cost_start = H->tcost_total;
-            H->tcost_total += T.units * T.unit_cells;
-        }
-    }
     H->total_cells = cstart;
     H->total_bytes = off;
     H->lds = std::max<size_t>(lds, 16);
@@ -726,55 +831,21 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
     H->gexec = nullptr;
     e = hipMalloc(&H->d_inst, sizeof(BatchInst) * count);
     if (e == hipSuccess) e = hipMalloc(&H->d_cost_start, sizeof(uint64_t) * (count + 1));
-    // the persistent tiled launch: instances and cost prefix sums
     if (e == hipSuccess && !H->tiled.empty()) {
-        const size_t m = H->tiled.size();
-        std::vector<uint64_t> cs(m + 1);
-        std::vector<uint64_t> ts(m + 1);
-        for (size_t q = 0; q < m; ++q) {
-            cs[q] = H->tiled[q].cost_start;
-            ts[q] = H->ttiles_total;
-            H->ttiles_total += H->tiled[q].units;
-        }
-        cs[m] = H->tcost_total;
-        ts[m] = H->ttiles_total;
-        e = hipMalloc(&H->d_tiled, sizeof(TiledInst) * m);
-        if (e == hipSuccess) e = hipMemcpy(H->d_tiled, H->tiled.data(), sizeof(TiledInst) * m, hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMalloc(&H->d_tcost, sizeof(uint64_t) * (m + 1));
-        if (e == hipSuccess) e = hipMemcpy(H->d_tcost, cs.data(), sizeof(uint64_t) * (m + 1), hipMemcpyHostToDevice);
-        if (e == hipSuccess) e = hipMalloc(&H->d_ttiles, sizeof(uint64_t) * (m + 1));
-        if (e == hipSuccess) e = hipMemcpy(H->d_ttiles, ts.data(), sizeof(uint64_t) * (m + 1), hipMemcpyHostToDevice);
-        // workgroup-per-tile order: the tiles of every pattern kind spread evenly over
-        // the launch, each tile keyed by the middle of its place among its kind's tiles
-        H->d_tmap = nullptr;
-        bool fits = m < 4096;
-        for (size_t q = 0; q < m && fits; ++q) fits = H->tiled[q].units <= 0xFFFFFu;
-        if (e == hipSuccess && fits && SQZ_BATCH_TILE_MAP) {
-            std::map<uint32_t, uint64_t> kind_tiles, kind_seen;
-            for (const TiledInst &T : H->tiled) kind_tiles[T.kind] += T.units;
-            std::vector<std::pair<double, uint32_t>> key;
-            key.reserve(H->ttiles_total);
-            for (size_t q = 0; q < m; ++q) {
-                const TiledInst &T = H->tiled[q];
-                const double n = (double)kind_tiles[T.kind];
-                for (uint64_t j = 0; j < T.units; ++j)
-                    key.push_back({((double)kind_seen[T.kind]++ + 0.5) / n, (uint32_t)(q << 20 | j)});
-            }
-            std::stable_sort(key.begin(), key.end(),
-                             [](const std::pair<double, uint32_t> &x, const std::pair<double, uint32_t> &y) {
-                                 return x.first < y.first;
-                             });
-            std::vector<uint32_t> map(key.size());
-            for (size_t i = 0; i < key.size(); ++i) map[i] = key[i].second;
-            e = hipMalloc(&H->d_tmap, sizeof(uint32_t) * map.size());
-            if (e == hipSuccess)
-                e = hipMemcpy(H->d_tmap, map.data(), sizeof(uint32_t) * map.size(), hipMemcpyHostToDevice);
-        }
+        e = tiled_setup(H->tiled, H->cus, false, &H->tmulti);
+        if (e == hipSuccess) e = tiled_setup(H->tiled, H->cus, true, &H->tone);
         H->Kt = H->Kt_max;
-        int per_cu = 0;
-        if (e == hipSuccess)
-            e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_batch_tiles<false>, 256, H->tlds);
-        H->twg_max = per_cu < 1 ? 1u : (unsigned)per_cu;
+        auto resident = [&](TiledLaunch &L, auto kernel) {
+            int per_cu = 0;
+            if (e == hipSuccess) e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kernel, kTiledThreads, L.lds);
+            L.wg_max = per_cu < 1 ? 1u : (unsigned)per_cu;
+            H->twg_max = std::max(H->twg_max, L.wg_max);
+        };
+        if (H->tmulti.mode == kTiledPacked)
+            resident(H->tmulti, k_batch_tiles<false, kTiledPacked>);
+        else
+            resident(H->tmulti, k_batch_tiles<false, kTiledSingle>);
+        resident(H->tone, k_batch_tiles<false, kTiledOne>);
         H->twg = H->twg_max;
     }
     // groups: per-instance kernel arguments, bases and tile prefix sums
@@ -872,10 +943,12 @@ void batch_destroy(BatchHost *H)
     if (H->d_tiny) (void)hipFree(H->d_tiny);
     (void)hipFree(H->d_inst);
     (void)hipFree(H->d_cost_start);
-    (void)hipFree(H->d_tiled);
-    (void)hipFree(H->d_tcost);
-    (void)hipFree(H->d_ttiles);
-    if (H->d_tmap) (void)hipFree(H->d_tmap);
+    for (TiledLaunch *L : {&H->tmulti, &H->tone}) {
+        (void)hipFree(L->d_inst);
+        (void)hipFree(L->d_cost);
+        (void)hipFree(L->d_start);
+        (void)hipFree(L->d_map);
+    }
     for (BatchGroup &G : H->groups) {
         (void)hipFree(G.d_args);
         (void)hipFree(G.d_base);
@@ -937,34 +1010,32 @@ static sqz_status launch_group(const BatchGroup &G, const uint8_t *in, uint8_t *
     return e == hipSuccess ? SQZ_OK : hip_error(e, "batch group launch");
 }
 
-template <bool PerTile>
-static void launch_tiles_k(int steps, dim3 g, dim3 b, size_t L, hipStream_t st, const TiledArgs &A, const uint8_t *in,
-                           uint8_t *out)
-{
-    hipLaunchKernelGGL(k_batch_tiles<PerTile>, g, b, L, st, A, in, out, steps);
-}
-
 // One launch of `steps` (1..H->Kt_max) steps for every tiled instance: form 1
-// persistent (wg_per_cu workgroups per CU), form 2 one workgroup per tile.
+// persistent (wg_per_cu workgroups per CU, as far as they are resident), form 2 one
+// workgroup per unit.
 static sqz_status launch_tiled(const BatchHost *H, int form, unsigned wg_per_cu, const uint8_t *in, uint8_t *out,
                                int steps, hipStream_t st)
 {
+    const TiledLaunch &L = steps == 1 ? H->tone : H->tmulti;
     TiledArgs A;
-    A.inst = H->d_tiled;
-    A.cost_start = H->d_tcost;
-    A.tile_start = H->d_ttiles;
-    A.tile_map = H->d_tmap;
+    A.inst = L.d_inst;
+    A.cost_start = L.d_cost;
+    A.tile_start = L.d_start;
+    A.tile_map = L.d_map;
     A.ninst = (uint32_t)H->tiled.size();
-    A.total_cost = H->tcost_total;
-    uint64_t grid = form == 2 ? H->ttiles_total : (uint64_t)H->cus * wg_per_cu;
+    A.total_cost = L.cost_total;
+    uint64_t grid = L.units_total;
+    if (form == 1) grid = std::min(grid, (uint64_t)H->cus * std::min(wg_per_cu, L.wg_max));
     if (grid < 1) grid = 1;
     if (grid > 0xFFFFFFFFull) return set_error(SQZ_ERR_RANGE, "%llu tiles exceed one launch", (unsigned long long)grid);
-    const dim3 g((unsigned)grid), b(256);
-    const size_t L = H->tlds;
-    if (form == 2)
-        launch_tiles_k<true>(steps, g, b, L, st, A, in, out);
-    else
-        launch_tiles_k<false>(steps, g, b, L, st, A, in, out);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)grid), dim3(kTiledThreads), L.lds, st, A, in, out, steps);
+    };
+    switch (L.mode) {
+    case kTiledOne: launch(form == 2 ? k_batch_tiles<true, kTiledOne> : k_batch_tiles<false, kTiledOne>); break;
+    case kTiledSingle: launch(form == 2 ? k_batch_tiles<true, kTiledSingle> : k_batch_tiles<false, kTiledSingle>); break;
+    default: launch(form == 2 ? k_batch_tiles<true, kTiledPacked> : k_batch_tiles<false, kTiledPacked>); break;
+    }
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? SQZ_OK : hip_error(e, "batch tiled launch");
 }
@@ -977,7 +1048,7 @@ static sqz_status launch_all(const BatchHost *H, const uint8_t *a, const uint8_t
     sqz_status s2 = SQZ_OK;
     uint8_t *const A = const_cast<uint8_t *>(a), *const B = const_cast<uint8_t *>(b);
     if (!H->tiled.empty() && H->tiled_form != 0) {
-        const std::vector<int> plan = plan_launches(steps, H->Kt);
+        const std::vector<int> plan = plan_full_launches(steps, H->Kt);
         for (size_t i = 0; i < plan.size() && s2 == SQZ_OK; ++i)
             s2 = launch_tiled(H, H->tiled_form, H->twg, (i & 1) ? B : A, (i & 1) ? A : B, plan[i], st);
     } else {

@@ -232,8 +232,9 @@ __device__ __forceinline__ BxRow bx_wave_row(uint32_t C)
 }
 
 // One tile, `steps` steps (phases A to D); sm: kBxLds words.  Called by every
-// lane of a workgroup of kBxThreads lanes.
-template <class Pat>
+// lane of a workgroup of kBxThreads lanes.  Prio: loads and stores before the
+// rounds of other workgroups (not beside other kinds of tiles, which wait then).
+template <class Pat, bool Prio = true>
 __device__ __forceinline__ void bitbox_tile(const BitboxArgs &A, const uint8_t *__restrict__ in,
                                             uint8_t *__restrict__ out, uint64_t t, int32_t steps, uint32_t *sm)
 {
@@ -248,7 +249,7 @@ __device__ __forceinline__ void bitbox_tile(const BitboxArgs &A, const uint8_t *
     const int side = (int)A.side;
     const uint64_t base = t * A.tile;
     const uint32_t grow = A.side / 3 + 2 * kBxBorder;  // block-grid rows in use
-    __builtin_amdgcn_s_setprio(3);
+    if constexpr (Prio) __builtin_amdgcn_s_setprio(3);
     // membership of this lane's words with the adjacent tiles present (tile-invariant table)
     uint32_t eff[kBxSR];
 #pragma unroll
@@ -314,7 +315,7 @@ __device__ __forceinline__ void bitbox_tile(const BitboxArgs &A, const uint8_t *
     __syncthreads();
 
     // (C) the rounds, behind the loads and stores of the workgroups beside
-    __builtin_amdgcn_s_setprio(0);
+    if constexpr (Prio) __builtin_amdgcn_s_setprio(0);
     uint32_t x[kBxSR];
     uint32_t *const mine = sm + kBxSR * ls * kBxW + lw;
 #pragma unroll
@@ -347,7 +348,7 @@ __device__ __forceinline__ void bitbox_tile(const BitboxArgs &A, const uint8_t *
     }
 
     // (D) rows -> block grid (unit: block row R of the tile, four columns) -> bytes
-    __builtin_amdgcn_s_setprio(3);
+    if constexpr (Prio) __builtin_amdgcn_s_setprio(3);
     if (act) {
 #pragma unroll
         for (int r = 0; r < kBxSR; ++r) mine[r * kBxW] = x[r];

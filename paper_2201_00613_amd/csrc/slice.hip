@@ -12,7 +12,8 @@ __global__ void __launch_bounds__(SliceCfg<P>::LANES)
 k_slice(SliceArgs A, const uint8_t *in, uint8_t *out, SliceRing G, int32_t steps)
 {
     __shared__ __align__(16) uint32_t sm[SliceCfg<P>::LDS / 4];
-    slice_tile<P, false>(A, in, out, xcd_remap(blockIdx.x, gridDim.x), G, steps, SliceRes{}, sm);
+    slice_tile<P, false>(A, in, out, xcd_remap(blockIdx.x, gridDim.x), G, steps, SliceRes{}, sm, threadIdx.x,
+                         blockDim.x);
 }
 
 // Resident run: one workgroup per tile, all on the chip at once.
@@ -21,7 +22,8 @@ __global__ void __launch_bounds__(SliceCfg<P>::LANES)
 k_slice_run(SliceArgs A, uint8_t *a, uint8_t *b, int32_t steps, SliceRes R)
 {
     __shared__ __align__(16) uint32_t sm[SliceCfg<P>::LDS / 4];
-    slice_tile<P, true>(A, a, (steps & 1) ? b : a, xcd_remap(blockIdx.x, gridDim.x), SliceRing{a, false}, steps, R, sm);
+    slice_tile<P, true>(A, a, (steps & 1) ? b : a, xcd_remap(blockIdx.x, gridDim.x), SliceRing{a, false}, steps, R, sm,
+                        threadIdx.x, blockDim.x);
 }
 
 // Every tile's corner subtrees, kSliceCornerPitch bytes each: a wave per subtree.

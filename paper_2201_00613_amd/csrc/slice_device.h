@@ -497,16 +497,18 @@ __device__ __forceinline__ void slice_wait(const SliceRes &R, F &&ready)
 
 // One tile, `steps` >= 1 steps (at most K without RES; any number when the
 // fractal is one tile).  in, out: the whole compact arrays, the same one for
-// an update in place.  Every lane of the workgroup calls it.
+// an update in place.  tid, NT: this lane and the lanes (whole waves) of the tile;
+// several tiles of one launch may share a workgroup, since the barriers depend on
+// `steps` alone.  Every lane of the workgroup calls it.
 template <class P, bool RES>
 __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in, uint8_t *out, uint64_t t,
-                                           const SliceRing &G, int32_t steps, const SliceRes &R, uint32_t *sm)
+                                           const SliceRing &G, int32_t steps, const SliceRes &R, uint32_t *sm,
+                                           const uint32_t tid, const uint32_t NT)
 {
     using C = SliceCfg<P>;
     constexpr int J = C::J;
     using PO = SlicePlanOf<P, J>;
     constexpr int NC = PO::value.nc, NH = PO::value.nh, NE = PO::value.ne, NPT = C::NPT;
-    const uint32_t tid = threadIdx.x, NT = blockDim.x;
     const uint32_t rblk = A.rwords / NC;
     const bool active = tid < A.lanes;
     const uint32_t *nbt = A.nbtile + t * kSliceMaxRing;
