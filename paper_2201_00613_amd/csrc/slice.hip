@@ -72,13 +72,14 @@ namespace {
 // 100 steps).  Above: level-11 tiles with level-3 blocks, several workgroups
 // per CU, where the chip is full anyway and the larger block publishes and
 // reads a third of the words (level 20, 20 steps: 1.58 against 2.31 ms).
-// Vicsek crosses: level-6 tiles to level 9, level-7 above (at most 125 tiles
-// to level 10), level-1 and level-2 blocks in the same way.
+// Vicsek crosses: level-6 tiles with level-1 blocks to level 10 (there 625 of them,
+// three per CU: 3 steps 7.4 us and 100 steps 41.7, with 125 level-7 tiles 9.7 and
+// 42.5), level-7 tiles with level-2 blocks above.
 void slice_levels(int kind, int r, int &M, int &var)
 {
     if (kind == 3) {
-        M = r <= 9 ? std::min(r, 6) : 7;
-        var = r <= 9 ? 0 : (r == 10 ? 1 : 2);
+        M = r <= 10 ? std::min(r, 6) : 7;
+        var = r <= 10 ? 0 : 2;
     } else {
         M = r >= 17 ? 11 : std::min(r, std::max(8, r - 5));
         var = r >= 17 ? 2 : (M <= 8 ? 0 : 1);
@@ -134,8 +135,7 @@ auto slice_dispatch(int kind, int var, F &&f)
     case 7: return f(SlicePaper{});
     case 8: return f(SlicePaperWide{});
     case 9: return f(SliceVicsekSmall{});
-    case 10: return f(SliceVicsek{});
-    default: return f(SliceVicsekWide{});
+    default: return f(SliceVicsekWide{});  // 11
     }
 }
 

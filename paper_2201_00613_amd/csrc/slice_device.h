@@ -574,7 +574,7 @@ __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in
     // a step's second half is the halo words alone (100 steps: level-16
     // triangle 69.7 -> 66.3 us, level 8 34.8 -> 33.5, level-6 Vicsek 28.6 -> 27.2).
     // Not where the sums cost more registers than they save time (27-cell
-    // blocks; level-10 Vicsek 45.5 -> 47.6).  In the first wave they come after
+    // blocks).  In the first wave they come after
     // the chain: between its reads and ballots they lengthen it (level 8 36.0),
     // and so does raised priority for that wave (level 16 69.8).
     auto publish = [&](auto pp) {
@@ -657,7 +657,7 @@ __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in
     if (tid < 2) *reinterpret_cast<uint32_t *>(lds + tid * C::BUF + C::ZERO) = 0;
     // Steps between exchanges in a loop of their own: with the exchange inside
     // it, every step was slower (100 steps: level-16 triangle 66.3 -> 61.2 us,
-    // level 13 44.3 -> 41.3, level-10 Vicsek 45.5 -> 43.0).
+    // level 13 44.3 -> 41.3).
     for (int32_t left = steps;;) {
         const int32_t m = RES && A.nring && left > (int32_t)R.K ? (int32_t)R.K : left;
         publish(std::integral_constant<uint32_t, 0>{});
@@ -698,8 +698,7 @@ __device__ __forceinline__ void slice_tile(const SliceArgs &A, const uint8_t *in
     // The wide kernels stream over arrays that outgrow the last-level cache:
     // nontemporal stores (level 20: 1580 -> 1508 us per 20 steps).  The level-16
     // triangle fits it and is read again by the next launch: plain ones (three
-    // steps 23.8 -> 20.0 us, 100 steps resident 1.3 us less).  The level-10 Vicsek
-    // cross, whose 125 tiles leave half of the CUs idle, keeps them (9.9 -> 9.5).
+    // steps 23.8 -> 20.0 us, 100 steps resident 1.3 us less).
     constexpr bool NTS = !RES && (J == 3 || P::B == 2);
     uint8_t *dst = out + t * A.cells;
     if (P::SMALL || A.words <= 4 * NT) {
