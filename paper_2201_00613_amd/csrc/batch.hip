@@ -467,6 +467,20 @@ struct BatchGroup {
     uint64_t *d_base, *d_tstart, *d_tstart1;
 };
 
+// The captured run and those it replaced.  A graph may still be running when
+// another takes its place, so graphs are destroyed behind an event on the stream
+// they were launched on.  One event for every kKeepGraphs of them: an event behind
+// every launch costs each run 4.5 us (8 fractals, 2 steps: 69 -> 74).
+constexpr size_t kKeepGraphs = 8;
+struct RunGraphs {
+    hipGraphExec_t exec;
+    std::vector<hipGraphExec_t> old;      // replaced since
+    std::vector<hipGraphExec_t> closing;  // finished once `event` has passed
+    hipEvent_t event;
+    hipStream_t stream;                   // of the last launch
+    bool launched, mixed;                 // there was one; graphs of old were launched on other streams as well
+};
+
 // The launches over all tiled instances, of several steps or of one.
 struct TiledLaunch {
     TiledInst *d_inst;
@@ -506,10 +520,9 @@ struct BatchHost {
     unsigned wg_per_cu, max_wg_per_cu;
     std::string key;
     hipStream_t cap;
-    hipGraphExec_t gexec;
+    RunGraphs graphs;
     const void *g_a, *g_b;
     int32_t g_steps;
-    void *g_stream;
 };
 
 static std::mutex g_tune_mu;
@@ -828,7 +841,6 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
     H->d_inst = nullptr;
     H->d_cost_start = nullptr;
     H->cap = nullptr;
-    H->gexec = nullptr;
     e = hipMalloc(&H->d_inst, sizeof(BatchInst) * count);
     if (e == hipSuccess) e = hipMalloc(&H->d_cost_start, sizeof(uint64_t) * (count + 1));
     if (e == hipSuccess && !H->tiled.empty()) {
@@ -934,10 +946,51 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
     return SQZ_OK;
 }
 
+static void destroy_graphs(std::vector<hipGraphExec_t> &v)
+{
+    for (hipGraphExec_t g : v) (void)hipGraphExecDestroy(g);
+    v.clear();
+}
+
+// The present graph is not launched again.
+static void retire_graph(RunGraphs &G)
+{
+    if (G.exec) G.old.push_back(G.exec);
+    G.exec = nullptr;
+}
+
+// Destroys replaced graphs that have finished, before a launch on `st`.
+static hipError_t close_graphs(RunGraphs &G, hipStream_t st)
+{
+    hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+    if (G.old.size() < kKeepGraphs || hipStreamIsCapturing(st, &cs) != hipSuccess || cs != hipStreamCaptureStatusNone)
+        return hipSuccess;
+    hipError_t e = hipSuccess;
+    if (G.mixed || st != G.stream) {  // an event on one stream does not tell for the others
+        e = hipDeviceSynchronize();
+        if (e != hipSuccess) return e;
+        destroy_graphs(G.closing);
+        destroy_graphs(G.old);
+        G.mixed = false;
+        return e;
+    }
+    if (!G.event) e = hipEventCreateWithFlags(&G.event, hipEventDisableTiming);
+    if (e == hipSuccess && !G.closing.empty()) e = hipEventSynchronize(G.event);
+    if (e != hipSuccess) return e;
+    destroy_graphs(G.closing);
+    e = hipEventRecord(G.event, st);
+    if (e == hipSuccess) G.closing.swap(G.old);
+    return e;
+}
+
 void batch_destroy(BatchHost *H)
 {
     if (!H) return;
-    if (H->gexec) (void)hipGraphExecDestroy(H->gexec);
+    retire_graph(H->graphs);
+    if (!H->graphs.old.empty() || !H->graphs.closing.empty()) (void)hipDeviceSynchronize();
+    destroy_graphs(H->graphs.old);
+    destroy_graphs(H->graphs.closing);
+    if (H->graphs.event) (void)hipEventDestroy(H->graphs.event);
     if (H->cap) (void)hipStreamDestroy(H->cap);
     for (SliceConfig *S : H->slices) slice_free(S);
     if (H->d_tiny) (void)hipFree(H->d_tiny);
@@ -1076,12 +1129,12 @@ sqz_status batch_run(BatchHost *H, uint8_t *a, uint8_t *b, int32_t steps, hipStr
 {
     if (steps == 0) return SQZ_OK;
     if (steps == 1) return batch_step(H, a, b, st);
-    if (!(H->gexec && H->g_a == a && H->g_b == b && H->g_steps == steps)) {
-        if (H->gexec) {
-            (void)hipGraphExecDestroy(H->gexec);
-            H->gexec = nullptr;
-        }
-        hipError_t e = hipStreamBeginCapture(H->cap, hipStreamCaptureModeThreadLocal);
+    RunGraphs &G = H->graphs;
+    if (!(G.exec && H->g_a == a && H->g_b == b && H->g_steps == steps)) {
+        retire_graph(G);
+        hipError_t e = close_graphs(G, st);
+        if (e != hipSuccess) return hip_error(e, "replaced graphs");
+        e = hipStreamBeginCapture(H->cap, hipStreamCaptureModeThreadLocal);
         if (e != hipSuccess) return hip_error(e, "hipStreamBeginCapture");
         const sqz_status s2 = launch_all(H, a, b, steps, H->cap);
         hipGraph_t g = nullptr;
@@ -1091,17 +1144,20 @@ sqz_status batch_run(BatchHost *H, uint8_t *a, uint8_t *b, int32_t steps, hipStr
             return s2;
         }
         if (e != hipSuccess) return hip_error(e, "hipStreamEndCapture");
-        e = hipGraphInstantiate(&H->gexec, g, nullptr, nullptr, 0);
+        e = hipGraphInstantiate(&G.exec, g, nullptr, nullptr, 0);
         (void)hipGraphDestroy(g);
         if (e != hipSuccess) {
-            H->gexec = nullptr;
+            G.exec = nullptr;
             return hip_error(e, "hipGraphInstantiate");
         }
         H->g_a = a;
         H->g_b = b;
         H->g_steps = steps;
     }
-    hipError_t e = hipGraphLaunch(H->gexec, st);
+    G.mixed = G.mixed || (G.stream != st && G.launched);
+    G.stream = st;
+    G.launched = true;
+    hipError_t e = hipGraphLaunch(G.exec, st);
     return e == hipSuccess ? SQZ_OK : hip_error(e, "hipGraphLaunch");
 }
 
@@ -1215,10 +1271,7 @@ sqz_status batch_autotune(BatchHost *H, uint8_t *a, uint8_t *b, hipStream_t st, 
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     if (st2 != SQZ_OK) return st2;
-    if (H->gexec) {
-        (void)hipGraphExecDestroy(H->gexec);
-        H->gexec = nullptr;
-    }
+    retire_graph(H->graphs);
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         std::vector<int> gk;
@@ -1243,10 +1296,7 @@ sqz_status batch_set_tiled(BatchHost *H, int32_t persistent, int32_t steps_per_l
         for (BatchGroup &G : H->groups) G.K = std::min(steps_per_launch, G.K_max);
     }
     if (wg_per_cu > 0) H->twg = (unsigned)wg_per_cu;
-    if (H->gexec) {
-        (void)hipGraphExecDestroy(H->gexec);
-        H->gexec = nullptr;
-    }
+    retire_graph(H->graphs);
     return SQZ_OK;
 }
 
