@@ -45,28 +45,34 @@ constexpr int kMapUnroll = SQZ_MAP_UNROLL;
 // elements, level-16 triangle: lambda 180 -> 120 us, nu 140 -> 130 (5.7 and 5.3
 // TB/s).  Below, copying the tables costs lambda what it saves (1e6 elements:
 // 6.8 us without, 6.0 with; 7-digit carpet 5.6 and 6.0; 3e4: 5.7 and 6.0).
-typedef uint64_t map_u64x2 __attribute__((ext_vector_type(2), aligned(8)));
-typedef int32_t map_i32x4 __attribute__((ext_vector_type(4), aligned(4)));
-typedef int32_t map_i32x2 __attribute__((ext_vector_type(2), aligned(4)));
+template <class G, int N>
+struct MapVec {  // N elements at any element address
+    typedef G T __attribute__((ext_vector_type(N), aligned(sizeof(G))));
+};
+using map_u64x2 = MapVec<uint64_t, 2>::T;
+using map_i32x4 = MapVec<int32_t, 4>::T;
+using map_i32x2 = MapVec<int32_t, 2>::T;
 static_assert(kMapUnroll % 2 == 0, "pairs");
 constexpr int64_t kMapLarge = 1 << 20;
 
-template <bool LARGE, class T>
-__device__ __forceinline__ T map_load(const T *p)
+template <bool LARGE, int N, class G>
+__device__ __forceinline__ typename MapVec<G, N>::T map_load(const G *p)
 {
+    const auto *q = reinterpret_cast<const typename MapVec<G, N>::T *>(p);
     if constexpr (LARGE)
-        return __builtin_nontemporal_load(p);
+        return __builtin_nontemporal_load(q);
     else
-        return *p;
+        return *q;
 }
 
-template <bool LARGE, class T>
-__device__ __forceinline__ void map_store(T v, T *p)
+template <bool LARGE, int N, class G>
+__device__ __forceinline__ void map_store(const typename MapVec<G, N>::T &v, G *p)
 {
+    auto *q = reinterpret_cast<typename MapVec<G, N>::T *>(p);
     if constexpr (LARGE)
-        __builtin_nontemporal_store(v, p);
+        __builtin_nontemporal_store(v, q);
     else
-        *p = v;
+        *q = v;
 }
 
 template <bool LARGE>
@@ -93,12 +99,12 @@ __global__ void __launch_bounds__(kBlock) k_lambda(MapParams P, const uint64_t *
             map_u64x2 c[kMapUnroll / 2];
 #pragma unroll
             for (int u = 0; u < kMapUnroll / 2; ++u)
-                c[u] = map_load<LARGE>(reinterpret_cast<const map_u64x2 *>(idx + i0 + 2 * u * kBlock));
+                c[u] = map_load<LARGE, 2>(idx + i0 + 2 * u * kBlock);
 #pragma unroll
             for (int u = 0; u < kMapUnroll / 2; ++u) {
                 const int2 p = map(c[u].x), q = map(c[u].y);
                 const map_i32x4 o = {p.x, p.y, q.x, q.y};
-                map_store<LARGE>(o, reinterpret_cast<map_i32x4 *>(xy + 2 * (i0 + 2 * u * kBlock)));
+                map_store<LARGE, 4>(o, xy + 2 * (i0 + 2 * u * kBlock));
             }
         } else {
             uint64_t c[kMapUnroll];
@@ -139,11 +145,11 @@ __global__ void __launch_bounds__(kBlock) k_nu(MapParams P, const int32_t *__res
             map_i32x4 p[kMapUnroll / 2];
 #pragma unroll
             for (int u = 0; u < kMapUnroll / 2; ++u)
-                p[u] = map_load<LARGE>(reinterpret_cast<const map_i32x4 *>(xy + 2 * (i0 + 2 * u * kBlock)));
+                p[u] = map_load<LARGE, 4>(xy + 2 * (i0 + 2 * u * kBlock));
 #pragma unroll
             for (int u = 0; u < kMapUnroll / 2; ++u) {
                 const map_u64x2 o = {nu_map(L, p[u].x, p[u].y), nu_map(L, p[u].z, p[u].w)};
-                map_store<LARGE>(o, reinterpret_cast<map_u64x2 *>(idx + i0 + 2 * u * kBlock));
+                map_store<LARGE, 2>(o, idx + i0 + 2 * u * kBlock);
             }
         } else {
             map_i32x2 p[kMapUnroll];
