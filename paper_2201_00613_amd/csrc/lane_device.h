@@ -32,6 +32,7 @@
 // twice the launches: 6.64 ms.
 #pragma once
 
+#include <algorithm>
 #include <utility>
 
 #include "bitbox_device.h"
@@ -563,6 +564,94 @@ __device__ __forceinline__ void lane_tile(const LaneArgs &A, const typename Op::
             }
         }
     }
+}
+
+// ---------------------------------------------------------------------------
+// Host side: kernel, tile level and table layout of a fractal.
+// ---------------------------------------------------------------------------
+template <class F>
+auto lane_dispatch(int kind, F &&f)
+{
+    switch (kind) {
+    case 1: return f(LaneTriangle{});
+    case 2: return f(LaneTrianglePaper{});
+    case 3: return f(LaneVicsek{});
+    case 4: return f(LaneCarpet{});
+    case 5: return f(LaneCarpetSmall{});
+    case 6: return f(LaneTriangleFine{});
+    case 7: return f(LaneTrianglePaperFine{});
+    case 8: return f(LaneVicsekFine{});
+    default: return f(LaneCarpetFine{});
+    }
+}
+
+template <class P>
+bool lane_matches(const FractalHost &F)
+{
+    if (F.s != P::S || F.k != P::K || F.r < P::J) return false;
+    for (int j = 0; j < P::K; ++j)
+        if (F.ox[j] != P::OX[j] || F.oy[j] != P::OY[j]) return false;
+    return true;
+}
+
+// Kernel.  Level-1 blocks where a fractal does not fill the chip and a step
+// takes the latency of one lane's work (30 steps, binary32 / bfloat16 with
+// stochastic rounding: level-9 triangle 16.8 / 21.5 -> 12.1 / 13.6 us, level 12
+// 18.9 / 28.0 -> 18.5 / 22.3; Vicsek level 6 22.6 / 39.0 -> 14.5 / 16.5; carpet
+// level 6 50 / 75 -> 27 / 40), level-2 blocks above, where the wider frames and
+// the halo reads per cell cost more (triangle level 13 24.4 against 36.1, Vicsek
+// level 9 36 against 40, carpet level 7 58 against 127).
+inline int lane_kind(const FractalHost &F)
+{
+    if (lane_matches<LaneTriangleFine>(F)) return F.r >= 13 ? 1 : 6;
+    if (lane_matches<LaneTrianglePaperFine>(F)) return F.r >= 13 ? 2 : 7;
+    if (lane_matches<LaneVicsekFine>(F)) return F.r >= 9 ? 3 : 8;
+    if (lane_matches<LaneCarpetFine>(F)) return F.r >= 8 ? 4 : (F.r == 7 ? 5 : 9);
+    return 0;
+}
+
+// Tile level.  A fractal of at most one full workgroup is one tile (no ring,
+// any number of steps per launch), except where several small ones have the
+// shorter step (triangle level 7: 13.9 us as one tile of 729 lanes, 11.6 as
+// nine; level 6: 10.0 and 10.5).  Above, the largest tiles that still leave
+// tens to hundreds of them: until the chip is full a step takes as long as one
+// tile of any size.
+inline int lane_level(int kind, int r)
+{
+    switch (kind) {
+    case 1:
+    case 2: return r <= 13 ? 7 : 8;
+    case 3: return 6;
+    case 4: return 5;
+    case 5: return 4;
+    case 6:
+    case 7: return r <= 6 ? r : (r <= 9 ? 5 : (r <= 11 ? 6 : 7));
+    case 8: return std::min(r, 4);
+    default: return r <= 4 ? r : 3;
+    }
+}
+
+// What the table builder needs; most: lanes a tile can have.
+inline LaneSpec lane_spec(int kind, int r, uint32_t &most)
+{
+    LaneSpec S{};
+    S.M = lane_level(kind, r);
+    lane_dispatch(kind, [&](auto p) {
+        using P = decltype(p);
+        using PO = LanePlanOf<P, P::J>;
+        S.J = P::J;
+        S.ng = PO::value.ng;
+        for (int g = 0; g < S.ng; ++g) {
+            S.g_dx[g] = PO::value.g_dx[g];
+            S.g_dy[g] = PO::value.g_dy[g];
+        }
+        S.steps = P::STEPS;
+        S.RL = P::RL;
+        S.frame = P::FRAME;
+        most = P::LANES - 1;
+        return 0;
+    });
+    return S;
 }
 
 }  // namespace sqz

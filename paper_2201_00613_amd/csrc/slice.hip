@@ -65,80 +65,6 @@ __global__ void __launch_bounds__(256) k_slice_clear(uint32_t *p, uint64_t n)
 
 namespace {
 
-// Tile level and kernel.  Triangles to level 16: at most 243 tiles, one per
-// CU, of at least level 8, with level-2 blocks (more waves per SIMD: at level
-// 16 three waves of 45 instructions per step rather than one of 121, which
-// alone on its SIMD issues at less than half the rate: 70 against 87 us per
-// 100 steps).  Above: level-11 tiles with level-3 blocks, several workgroups
-// per CU, where the chip is full anyway and the larger block publishes and
-// reads a third of the words (level 20, 20 steps: 1.58 against 2.31 ms).
-// Vicsek crosses: level-6 tiles with level-1 blocks to level 10 (there 625 of them,
-// three per CU: 3 steps 7.4 us and 100 steps 41.7, with 125 level-7 tiles 9.7 and
-// 42.5), level-7 tiles with level-2 blocks above.
-void slice_levels(int kind, int r, int &M, int &var)
-{
-    if (kind == 3) {
-        M = r <= 10 ? std::min(r, 6) : 7;
-        var = r <= 10 ? 0 : 2;
-    } else {
-        M = r >= 17 ? 11 : std::min(r, std::max(8, r - 5));
-        var = r >= 17 ? 2 : (M <= 8 ? 0 : 1);
-    }
-}
-
-template <class P>
-SliceSpec slice_spec(int M)
-{
-    using C = SliceCfg<P>;
-    constexpr int J = P::J;
-    constexpr const SlicePlan &PL = C::PL;
-    SliceSpec S{};
-    S.M = M;
-    S.B = P::B;
-    S.J = J;
-    S.RL = P::RL;
-    S.steps = P::STEPS;
-    S.nc = PL.nc;
-    S.box = PL.box;
-    S.nh = PL.nh;
-    for (int c = 0; c < 32; ++c) S.cell_exp[c] = -1;
-    for (int h = 0; h < PL.nh; ++h) {
-        S.h_dx[h] = PL.h_dx[h];
-        S.h_dy[h] = PL.h_dy[h];
-        S.h_idx[h] = PL.h_idx[h];
-        S.h_exp[h] = PL.h_exp[h];
-    }
-    for (int e = 0; e < PL.ne; ++e) S.cell_exp[PL.e_cell[e]] = e;
-    for (int c = 0; c < PL.nc; ++c) {
-        S.cell_x[c] = PL.lx[c];
-        S.cell_y[c] = PL.ly[c];
-    }
-    S.max_ring = kSliceMaxRing;
-    S.zero = C::ZERO;
-    S.ex0 = C::EX0;
-    S.pitch = C::PITCH;
-    S.halo = C::HALO;
-    S.rhalo = C::RHALO;
-    S.passes = C::NPT;
-    return S;
-}
-
-// Calls f with the kernel's pattern type.
-template <class F>
-auto slice_dispatch(int kind, int var, F &&f)
-{
-    switch (3 * kind + var) {
-    case 3: return f(SliceTriSmall{});
-    case 4: return f(SliceTri{});
-    case 5: return f(SliceTriWide{});
-    case 6: return f(SlicePaperSmall{});
-    case 7: return f(SlicePaper{});
-    case 8: return f(SlicePaperWide{});
-    case 9: return f(SliceVicsekSmall{});
-    default: return f(SliceVicsekWide{});  // 11
-    }
-}
-
 unsigned slice_threads(const SliceConfig &S) { return (S.A.lanes + 63) / 64 * 64; }
 
 }  // namespace
@@ -157,8 +83,6 @@ void slice_release(FractalHost &F)
     slice_free(F.slice);
     F.slice = nullptr;
 }
-
-static int slice_kind(const FractalHost &F) { return F.tile_kind == 4 ? 1 : F.tile_kind; }
 
 // Tables of tiles of level M for kernel `var`; *out stays null where a subtile
 // would be smaller than a block.
