@@ -106,12 +106,10 @@ typedef enum sqz_map_impl { SQZ_MAP_SCALAR = 0, SQZ_MAP_MFMA = 1 } sqz_map_impl;
 
 /* How sqz_compact_run_form advances a run.
  *   SQZ_RUN_AUTO: RESIDENT when the fractal offers it (sqz_info.resident_run),
- *                 the buffers are 16-byte aligned, and either steps >= 10 or
- *                 LAUNCHES would need an extra launch to leave the result in the
- *                 buffer the step count's parity names (steps >= 2); else
- *                 LAUNCHES.  The resident run's fixed cost (loading and storing
- *                 every subtree once) pays from about 10 steps, measured on an
- *                 MI355X; sqz_run_form_auto reports the choice.
+ *                 the buffers are 16-byte aligned, and the steps are at least 10
+ *                 or an even number (2 to 8), after which LAUNCHES leave the
+ *                 result in place at the cost of a launch more; else LAUNCHES.
+ *                 sqz_run_form_auto reports the choice.
  *   SQZ_RUN_LAUNCHES: one kernel launch per group of steps (at least
  *                 sqz_info.run_steps_per_launch of them where the run has as
  *                 many), each reading the state whole and writing it whole

@@ -3,11 +3,12 @@
 //
 // Every instance owns a 256-byte aligned range of one state buffer.
 // Instances with a tiled kernel (bit-sliced tiles of the triangle, its mirror
-// image and the Vicsek cross; bit rows of the carpet) run in one of two
+// image and the Vicsek cross; bit rows of the carpet) run in one of three
 // forms: one launch per pattern group, with one workgroup per tile of any of
-// the group's instances and the group's own steps per launch; or one
-// persistent launch over all of them, in which workgroup b takes the tiles
-// whose first cell falls in the b-th equal share of their cells.  The tile
+// the group's instances and the group's own steps per launch; one
+// persistent launch over all of them, in which workgroup b takes the units
+// whose first cell falls in the b-th equal share of their cells; or one launch
+// over all of them with a workgroup per unit (a tile or few).  The tile
 // bodies are the single-fractal kernels' device functions.  The remaining
 // instances (expanded tiles of any pattern, runs of 4096 cells of the
 // thread-level path for instances too small to tile) share one persistent
@@ -224,15 +225,16 @@ __device__ __forceinline__ void tiny_tile(const SliceArgs &A, const uint8_t *in,
 }
 
 // Unit u of an instance: one tile on all lanes of the workgroup or, PACKED, a tile
-// per SliceCfg<P>::LANES lanes (lane groups past the last tile repeat it).
+// per SliceCfg<P>::LANES lanes (lane groups past the last tile repeat it).  TINY:
+// the instance may be a fractal too small to tile.
 constexpr uint32_t kTiledThreads = 256;  // of the launches over all tiled instances
 
-template <class P, bool PACKED>
+template <class P, bool PACKED, bool TINY>
 __device__ __forceinline__ void slice_unit(const SliceArgs &A, const uint8_t *in, uint8_t *out, uint64_t u,
                                            int32_t steps, uint32_t *sm)
 {
     static_assert(SliceCfg<P>::LDS >= 2 * kTinyCells, "LDS of a small fractal");
-    if (A.words == 0) {
+    if (TINY && A.words == 0) {
         tiny_tile(A, in, out, steps, sm);
     } else if constexpr (PACKED) {
         constexpr uint32_t L = SliceCfg<P>::LANES;
@@ -272,7 +274,8 @@ __device__ __forceinline__ uint32_t group_instance(const GroupArgs &G, uint64_t 
 // a launch.  512 mixed fractals, 50 steps: 3.86 ms with the 27-cell blocks
 // (five launches of ten, bound by vector issue) -> 1.22 ms, of which the
 // carpets' bit rows take 0.40.
-template <class P>
+// TINY: with fractals too small to tile (their branch costs the others 0.4 %).
+template <class P, bool TINY>
 __global__ void __launch_bounds__(SliceCfg<P>::LANES)
 k_batch_slice(GroupArgs G, const uint8_t *in, uint8_t *out, int32_t steps)
 {
@@ -281,7 +284,7 @@ k_batch_slice(GroupArgs G, const uint8_t *in, uint8_t *out, int32_t steps)
     const uint32_t i = group_instance(G, b);
     const SliceArgs A = reinterpret_cast<const SliceArgs *>(G.args)[i];
     const uint64_t base = G.base[i];
-    slice_unit<P, false>(A, in + base, out + base, b - G.tstart[i], steps, sm);
+    slice_unit<P, false, TINY>(A, in + base, out + base, b - G.tstart[i], steps, sm);
 }
 
 // A launch of one step: the bit-sliced blocks, whose loads and stores are 16
@@ -352,7 +355,7 @@ template <class P, bool PACKED>
 __device__ __forceinline__ void tiled_unit(const TiledInst &I, const uint8_t *in, uint8_t *out, uint64_t u, int32_t steps,
                                            uint32_t *sm)
 {
-    slice_unit<P, PACKED>(I.t, in, out, u, steps, sm);
+    slice_unit<P, PACKED, true>(I.t, in, out, u, steps, sm);
     __syncthreads();  // LDS is free for the next unit
 }
 
@@ -461,6 +464,7 @@ struct BatchGroup {
     int K, K_max;   // steps per launch: chosen (0: none, a launch takes K_full), most that can be chosen
     int K_full;     // steps a launch can take at most (more than K_max; 0: any number)
     unsigned threads;
+    bool tiny;      // some member is too small to tile
     std::vector<uint32_t> members;
     uint64_t ntiles, ntiles1;  // tiles; of launches of one step (but kBBits)
     void *d_args, *d_args1;
@@ -771,7 +775,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
             for (BatchGroup &g : H->groups)
                 if (g.kind == I.kind) G = &g;
             if (!G) {
-                H->groups.push_back(BatchGroup{I.kind, 0, kMaxSteps, 0, 64, {}, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr});
+                H->groups.push_back(BatchGroup{I.kind, 0, kMaxSteps, 0, 64, false, {}, 0, 0, nullptr, nullptr, nullptr, nullptr, nullptr});
                 G = &H->groups.back();
             }
             if (I.kind == kBBits) {
@@ -780,6 +784,7 @@ sqz_status batch_create(const sqz_fractal *const *fr, int32_t count, BatchHost *
             } else {
                 const SliceConfig *C = slice_of[&F];
                 if (C && C->K) G->K_full = (int)C->K;  // the same for every fractal of more than one tile
+                G->tiny = G->tiny || !C;
                 if (C) G->threads = std::max(G->threads, (C->A.lanes + 63) / 64 * 64);
             }
             G->members.push_back((uint32_t)i);
@@ -1045,16 +1050,15 @@ static sqz_status launch_group(const BatchGroup &G, const uint8_t *in, uint8_t *
         const hipError_t e = hipGetLastError();
         return e == hipSuccess ? SQZ_OK : hip_error(e, "batch group launch");
     }
+    auto slice = [&](auto p) {
+        using P = decltype(p);
+        const auto kernel = G.tiny ? k_batch_slice<P, true> : k_batch_slice<P, false>;
+        hipLaunchKernelGGL(kernel, dim3(grid), dim3(G.threads), 0, st, A, in, out, steps);
+    };
     switch (G.kind) {
-    case kBTri:
-        hipLaunchKernelGGL(k_batch_slice<SliceTriSmall>, dim3(grid), dim3(G.threads), 0, st, A, in, out, steps);
-        break;
-    case kBTriPaper:
-        hipLaunchKernelGGL(k_batch_slice<SlicePaperSmall>, dim3(grid), dim3(G.threads), 0, st, A, in, out, steps);
-        break;
-    case kBVicsek:
-        hipLaunchKernelGGL(k_batch_slice<SliceVicsekSmall>, dim3(grid), dim3(G.threads), 0, st, A, in, out, steps);
-        break;
+    case kBTri: slice(SliceTriSmall{}); break;
+    case kBTriPaper: slice(SlicePaperSmall{}); break;
+    case kBVicsek: slice(SliceVicsekSmall{}); break;
     default:
         hipLaunchKernelGGL(k_batch_bitbox<PatCarpet>, dim3(grid), dim3(kBxThreads), 0, st, A, in, out, steps);
         break;

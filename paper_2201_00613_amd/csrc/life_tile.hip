@@ -227,8 +227,8 @@ int tile_steps_per_launch(const FractalHost &F)
     return (int)std::min<int64_t>(kMaxSteps, side - 1);
 }
 
-// Fractals whose tiles, at most eight (of the large ones three) per CU, are
-// few enough for a run that keeps all state on the chip.
+// Fractals whose one-step tiles are at most eight (of the large ones three) per
+// CU: those a resident run is offered for, where the tiles of the run fit too.
 bool tile_few(const FractalHost &F)
 {
     int cus = 0;

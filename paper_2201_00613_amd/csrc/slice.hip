@@ -194,7 +194,7 @@ void slice_prepare_resident(FractalHost &F)
         using P = decltype(p);
         nc = SlicePlanOf<P, P::J>::value.nc;
         if constexpr (P::J == (P::B == 2 ? 2 : 3)) {
-            return hipErrorNotSupported;  // wide kernels: more tiles than the chip holds
+            return hipErrorNotSupported;  // the wide kernels have no resident form
         } else {
         hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_slice_run<P>, (int)nt, 0);
         hipFuncAttributes fa;

@@ -478,8 +478,9 @@ struct SliceRes {
     uint32_t K;       // steps between exchanges
 };
 
-// Waits until ready() holds for every active lane; bounded as grid_barrier's
-// wait.  Returns with the run marked as timed out when it gives up.
+// Waits until ready() holds for every active lane, for at most kSpinLimit polls
+// and no longer than until another wait of the run has given up (`dead`).  Giving
+// up marks the run as timed out and returns, so that every wave ends.
 template <class F>
 __device__ __forceinline__ void slice_wait(const SliceRes &R, F &&ready)
 {
