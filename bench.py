@@ -5,21 +5,22 @@ Workload (N=1): level-16 Sierpinski triangle, replicas (0,0),(1,0),(0,1),
 (seed 2201), B3/S23 steps ping-ponging between two compact buffers.  One
 "step" is one B3/S23 update of every cell.  The K timed steps are one
 sqz_compact_run call, in the run form the library picks for K steps: from 10
-steps (and where launches would need an extra one-step launch) one launch
-that holds all 243 tiles on the chip for all K steps, exchanging ring subtrees
-every 31 steps; otherwise launches of up to 31 steps.  The other form is timed
-beside it.  The
+steps (and for even counts below) one launch that holds all 243 tiles on the
+chip for all K steps, exchanging ring subtrees every 31 steps; otherwise
+launches of up to 31 steps.  The other form is timed beside it.  The
 same steps on the 65536 x 65536 bounding-box grid give the speedup (these
 comparison runs go first, so the headline is not the process's first GPU
 work); the
 level-20 triangle (3.49e9 cells, 20 steps, Bernoulli(0.3)) gives the largest
 workload.
 
-Roofline: the tiled Life kernels are bound by vector-ALU issue, so `roofline`
-reports counter-measured VALU wave-instructions per dispatch (from the
-committed rocprofv3 summary of the same kernel source and dispatch size) over
-the live dispatch time, against the chip's peak of two wave64 instructions per
-CU per clock; HBM bytes are secondary fields.
+Roofline: a level-16 run touches HBM at its ends only; it is bound by the
+vector-ALU issue of a step and by the latency of its chain of LDS accesses.
+`roofline` reports counter-measured VALU wave-instructions per dispatch (from
+the committed rocprofv3 summary of the same kernel source and dispatch size)
+over the live dispatch time, against the chip's peak of two wave64 instructions
+per CU per clock; HBM bytes are secondary fields.  The level-20 run is bound by
+HBM and reports the counters' bytes.
 
 Prints one JSON line.  Inputs are resident in HBM before timing starts.
 """
@@ -116,20 +117,20 @@ def bb_run(torch, F, seed, p, steps, warmup):
     return sec
 
 
-def tile_source_hash() -> str:
+def run_source_hash() -> str:
     import hashlib
 
     src = os.path.join(ROOT, "paper_2201_00613_amd", "csrc")
     h = hashlib.sha256()
-    for f in ("life_tile.hip", "tile_device.h", "common.h"):
+    for f in ("slice.hip", "slice_device.h", "tile_device.h", "common.h"):
         h.update(open(os.path.join(src, f), "rb").read())
     return h.hexdigest()[:16]
 
 
 def profiled_counters(profile: str, workload: str):
-    """Counter figures of a tiled kernel (bytes and vector-ALU instructions per
+    """Counter figures of a run kernel (bytes and vector-ALU instructions per
     dispatch) from a committed rocprofv3 summary under profiles/, if the kernel
-    source is unchanged since it was taken (sha256 prefix of the tile sources)."""
+    source is unchanged since it was taken (sha256 prefix of the run kernels' sources)."""
     import re
 
     path = os.path.join(ROOT, "profiles", profile)
@@ -139,7 +140,7 @@ def profiled_counters(profile: str, workload: str):
     if not m:
         return None
     rec = json.loads(m.group(1))
-    if rec["workload"] != workload or rec["source_sha256_16"] != tile_source_hash():
+    if rec["workload"] != workload or rec["source_sha256_16"] != run_source_hash():
         return None
     return rec
 
@@ -151,12 +152,12 @@ VALU_PEAK_PER_CU_CLOCK = 157.3e12 / (NUM_CUS * CLOCK_HZ) / 128
 VALU_PEAK_G = VALU_PEAK_PER_CU_CLOCK * NUM_CUS * CLOCK_HZ / 1e9
 
 
-def alu_roofline(rec, steps: int, sec: float, launches: int, cells: int, profile: str):
-    """Roofline of a tiled Life run bound by vector-ALU issue: counter-measured VALU
-    wave-instructions per dispatch (from the committed profile, for a dispatch of the
-    same number of steps) over the live launch time, against the chip's peak; HBM
-    counter bytes per dispatch over the same time as `traffic`.  None when the
-    profile does not hold a dispatch of this many steps."""
+def counter_roofline(rec, steps: int, sec: float, launches: int, cells: int, profile: str):
+    """Roofline of a Life run from a committed profile's counters per dispatch (of the
+    same number of steps) over the live launch time: VALU wave-instructions against the
+    chip's peak or, where the profile says that HBM bounds the kernel, its HBM bytes
+    against the peak bandwidth.  None when the profile does not hold a dispatch of this
+    many steps."""
     if not rec:
         return None
     per = steps // launches if launches and steps % launches == 0 else None
@@ -164,20 +165,17 @@ def alu_roofline(rec, steps: int, sec: float, launches: int, cells: int, profile
     if entry is None:
         return None
     launch_s = sec / launches
-    achieved = entry["valu_insts"] / launch_s / 1e9
-    ceiling = rec["valu_mix_ceiling_per_cu_clock"] * NUM_CUS * CLOCK_HZ / 1e9
-    out = {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK_G, "unit": "G VALU wave-instructions/s",
-           "frac": achieved / VALU_PEAK_G, "traffic": entry["traffic_bytes"] / launch_s / 1e9,
-           "traffic_unit": "GB/s", "traffic_vs_algorithmic": entry["traffic_bytes"] / (BYTES_PER_UPDATE * cells),
-           "per_cu_clock": achieved * 1e9 / NUM_CUS / CLOCK_HZ,
-           "measured_mix_ceiling": ceiling, "frac_of_measured_mix_ceiling": achieved / ceiling,
+    valu = entry["valu_insts"] / launch_s / 1e9
+    traffic = entry["traffic_bytes"] / launch_s / 1e9
+    out = {"traffic": traffic, "traffic_unit": "GB/s",
+           "traffic_vs_algorithmic": entry["traffic_bytes"] / (BYTES_PER_UPDATE * cells),
+           "valu_per_cu_clock": valu * 1e9 / NUM_CUS / CLOCK_HZ,
            "counters_from": f"profiles/{profile} (dispatches of {per} steps; source hash {rec['source_sha256_16']})"}
-    if "valu_mix_ceiling_at_occupancy" in rec:
-        # the same mix at the kernel's own occupancy (waves per SIMD its workgroups allow)
-        occ = rec["valu_mix_ceiling_at_occupancy"] * NUM_CUS * CLOCK_HZ / 1e9
-        out.update({"waves_per_simd": rec.get("waves_per_simd"), "mix_ceiling_at_occupancy": occ,
-                    "frac_of_mix_ceiling_at_occupancy": achieved / occ})
-    return out
+    if rec["bound"] == "hbm":
+        return {"bound": "hbm", "achieved": traffic, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                "frac": traffic / HBM_PEAK_GBS, **out}
+    return {"bound": "alu", "achieved": valu, "peak": VALU_PEAK_G, "unit": "G VALU wave-instructions/s",
+            "frac": valu / VALU_PEAK_G, "note": rec["note"], **out}
 
 
 def cpu_baseline(r: int, seed: int, p: float, min_sec: float, max_steps: int) -> dict:
@@ -564,30 +562,36 @@ def main() -> int:
     hbm = {"algorithmic_gbs_per_launch": gbs, "frac_of_hbm_peak": gbs / HBM_PEAK_GBS,
            # 2 B per cell-update over the step time: the bytes one-step launches would move
            "step_equivalent_gbs": BYTES_PER_UPDATE * F.cells * args.steps / sec / 1e9}
-    profile = {"resident": "k_life_tileR_triangle_r16.md", "launches": "k_life_tileK_triangle_r16.md"}.get(used)
+    profiles = {"resident": "k_slice_run_triangle_r16.md", "launches": "k_slice_triangle_r16.md"}
+    profile = profiles.get(used)
     rec = profiled_counters(profile, out["config"]["workload"]) if profile else None
-    out["roofline"] = alu_roofline(rec, args.steps, sec, launches, F.cells, profile) or {
-        "bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s", "frac": gbs / HBM_PEAK_GBS,
-        "traffic": None, "note": "no committed counter profile for this kernel source and step count"}
+    note = "no committed counter profile for this kernel source and step count"
+    out["roofline"] = counter_roofline(rec, args.steps, sec, launches, F.cells, profile)
+    if not out["roofline"] and used == "resident":  # HBM is touched at the ends of the run only
+        out["roofline"] = {"bound": "alu", "achieved": None, "peak": VALU_PEAK_G, "unit": "G VALU wave-instructions/s",
+                           "frac": None, "traffic": None, "note": note}
+    elif not out["roofline"]:
+        out["roofline"] = {"bound": "hbm", "achieved": gbs, "peak": HBM_PEAK_GBS, "unit": "GB/s",
+                           "frac": gbs / HBM_PEAK_GBS, "traffic": None, "note": note}
     out["roofline"]["hbm"] = hbm
     if other and other[0] == "launches":
         sl = other[1]
         nl = run_launches(F, args.steps)
         out["launches_form"] = {"ms_per_step": sl * 1e3 / args.steps, "cell_updates_per_s": F.cells * args.steps / sl,
                                 "launches": nl, "algorithmic_gbs_per_launch": BYTES_PER_UPDATE * F.cells * nl / sl / 1e9}
-        rl = profiled_counters("k_life_tileK_triangle_r16.md", out["config"]["workload"])
-        alu = alu_roofline(rl, args.steps, sl, nl, F.cells, "k_life_tileK_triangle_r16.md")
-        if alu:
-            out["launches_form"]["roofline"] = alu
+        rl = profiled_counters(profiles["launches"], out["config"]["workload"])
+        roof = counter_roofline(rl, args.steps, sl, nl, F.cells, profiles["launches"])
+        if roof:
+            out["launches_form"]["roofline"] = roof
         log(f"[bench] {nl} launches: {sl * 1e3 / args.steps:.4f} ms/step")
     elif other and other[0] == "resident":
         sr = other[1]
         out["resident_form"] = {"ms_per_step": sr * 1e3 / args.steps, "cell_updates_per_s": F.cells * args.steps / sr,
                                 "launches": 1}
-        rr = profiled_counters("k_life_tileR_triangle_r16.md", out["config"]["workload"])
-        alu = alu_roofline(rr, args.steps, sr, 1, F.cells, "k_life_tileR_triangle_r16.md")
-        if alu:
-            out["resident_form"]["roofline"] = alu
+        rr = profiled_counters(profiles["resident"], out["config"]["workload"])
+        roof = counter_roofline(rr, args.steps, sr, 1, F.cells, profiles["resident"])
+        if roof:
+            out["resident_form"]["roofline"] = roof
         log(f"[bench] resident run: {sr * 1e3 / args.steps:.4f} ms/step")
     if s1 is not None:
         out["one_step_per_launch"] = {"ms_per_step": s1 * 1e3 / args.steps,
@@ -632,10 +636,11 @@ def main() -> int:
                       "algorithmic_gbs_per_launch": gbs20, "hbm_frac": gbs20 / HBM_PEAK_GBS,
                       "step_equivalent_gbs": BYTES_PER_UPDATE * F20.cells * args.r20_steps / s20 / 1e9,
                       "bernoulli_p": 0.3}
-        r20_alu = alu_roofline(profiled_counters("k_life_tileK_triangle_r20.md", "sierpinski-triangle-r20-life-b3s23"),
-                               args.r20_steps, s20, l20, F20.cells, "k_life_tileK_triangle_r20.md")
-        if r20_alu:
-            out["r20"]["roofline"] = r20_alu
+        p20 = "k_slice_triangle_r20.md"
+        roof = counter_roofline(profiled_counters(p20, "sierpinski-triangle-r20-life-b3s23"), args.r20_steps, s20, l20,
+                                F20.cells, p20)
+        if roof:
+            out["r20"]["roofline"] = roof
         log(f"[bench] r=20: {ms20:.3f} ms/step, {l20} launches, {gbs20:.1f} GB/s per launch "
             f"({100 * gbs20 / HBM_PEAK_GBS:.1f}% of HBM peak)")
         del F20
