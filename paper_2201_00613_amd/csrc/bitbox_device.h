@@ -33,15 +33,14 @@
 // Measured (level-9 carpet, 134 million cells): with the rows in LDS (36 words
 // read and 10 written per lane and round) and a border of twelve cells, ten
 // steps took 112 us and 30 steps, four launches, 400; now 61 us for one step,
-// 102 for fifteen and 205 for 30.  A launch moves 2 B per cell and a quarter
+// 107 for fifteen and 218 for 30.  A launch moves 2 B per cell and a quarter
 // more for borders, 58 us at the rate of a large copy; a round is bound by
 // vector issue (168 instructions a wave, 3.3 us), most of which comes on top:
 // the tiles fill the chip twice, and the workgroups beside each other load and
 // compute at about the same time.  Raised priority outside the rounds keeps
-// loads and stores ahead of them (30 steps: 217 -> 209).  Loads held in
+// loads and stores ahead of them (30 steps: 233 -> 218).  Loads held in
 // registers over the table look-up cost more than they hide (63 -> 76 us for
-// one step), as do fewer workgroups per CU (five: 228, four: 247 us for 30
-// steps).
+// one step), as do fewer workgroups per CU (30 steps: five 9 % more, four 18 %).
 #pragma once
 
 #include "common.h"
